@@ -5,7 +5,8 @@
 // Kernels of the PCMM path:
 //   pack_w_kernel   (plan time)  W -> int8 slices in MFMA A-operand fragment order
 //   split_kernel    (every run)  uint64 residues -> D signed base-256 digit planes in MFMA
-//                                B-operand fragment order
+//                                B-operand fragment order (split_pair_kernel: two limbs joined into one
+//                                integer of nine digits)
 //   gemm_kernel     (every run)  v_mfma_i32_16x16x64_i8 main loop, then recombination of the digit
 //                                accumulators and reduction modulo q_j
 // Beside it:
@@ -77,6 +78,11 @@ __device__ __forceinline__ void mfma_drain()
 {
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
 }
+
+// the constants of every limb pair, passed to the split kernel by value
+struct PairConsts {
+    pcmm_host::PairConst c[pcmm_host::kMaxLimbs / 2];
+};
 
 // ------------------------------------------------------------------------------------------------
 // plan-time kernel: pack W
@@ -174,6 +180,87 @@ __global__ __launch_bounds__(256) void split_kernel(const uint64_t *__restrict__
     }
 }
 
+// Digit split of TWO limbs at once (S = 1, primes of 33 to 36 bits).  One residue x_i < q_i < 2^36 takes five
+// base-256 digits, so two limbs cost ten digit products although they hold only 72 bits, nine bytes.  The two
+// residues are therefore joined by the Chinese remainder theorem into one integer X with X = x1 mod q1 and
+// X = x2 mod q2, and X is cut into nine balanced digits; the product sum W X reduced modulo q1 and modulo q2 gives both
+// outputs.  One digit product in ten is saved: in the matrix products, in the digit planes and in every copy of them.
+//   t = ((x2 - x1) q1^-1 + s) mod q2,   s = floor(Bias / q1),   Y = q1 t + x1 + (Bias mod q1)
+// is X + Bias for X = q1 (t - s) + x1, and 0 <= Y < q1 q2 + q1 <= 256^9, so the bytes of Y, each xor 0x80, are the
+// balanced digits of X (pcmm_host.hpp decides which primes qualify and derives the constants).
+// Bound: HBM, 16 bytes read and 9 written per pair of residues; about 45 vector instructions per pair, a third of what
+// the memory time hides.  Layout as in split_kernel with one 16-column fragment per tile (NT = 1) and nine digits.
+__global__ __launch_bounds__(256) void split_pair_kernel(const uint64_t *__restrict__ A, int8_t *__restrict__ Ad,
+                                                         int64_t K, int64_t Ncols, int64_t nkb, int64_t ntiles,
+                                                         PairConsts pcs)
+{
+    constexpr int D = pcmm_host::kPairDigits;
+    const int lane = threadIdx.x & 63;
+    const int g = threadIdx.x >> 6;
+    const int64_t kb = blockIdx.y;
+    const int64_t pair = blockIdx.z;
+    const int64_t n = (int64_t)blockIdx.x * 64 + lane;
+    const int64_t ntile = n >> 4;
+    if (ntile >= ntiles) return;
+    const pcmm_host::PairConst pc = pcs.c[pair];
+
+    const int64_t k0 = kb * 64 + g * 16;
+    const uint64_t *src1 = A + (2 * pair * K + k0) * Ncols + n;
+    const uint64_t *src2 = src1 + K * Ncols;
+    uint64_t x1[16], x2[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+        const bool in = k0 + j < K && n < Ncols;
+        x1[j] = in ? src1[(int64_t)j * Ncols] : 0;
+        x2[j] = in ? src2[(int64_t)j * Ncols] : 0;
+    }
+    uint32_t out[D][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        uint32_t y0[4], y1[4], y2[4];               // Y = y0 + 2^32 y1 + 2^64 y2
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const uint64_t u1 = x1[4 * i + r], u2 = x2[4 * i + r];
+            // residues as doubles: placed in the low mantissa bits of 2^52 + x, whose difference is exact
+            constexpr uint64_t kMagic = 0x4330000000000000ull;
+            const double dx = __longlong_as_double(u2 | kMagic) - __longlong_as_double(u1 | kMagic);
+            // |dx| < 2^36 < 2 q2, so |mulmod| <= 0.75 q2 + 1; s < 2.01 q2 (q1 > 2^35)
+            const double v = mulmod(pc.inv, dx, pc.q2, pc.invq2) + pc.s;
+            const uint64_t t = (uint64_t)__double_as_longlong(canonical(v, pc.q2, pc.invq2, pc.half_invq2) + 4503599627370496.0);
+            const uint32_t tl = (uint32_t)t, th = (uint32_t)(t >> 32) & 0xFu;
+            const uint64_t c = u1 + pc.bias_mod_q1;
+            const uint32_t ql = (uint32_t)pc.q1, qh = (uint32_t)(pc.q1 >> 32);
+            const uint64_t p0 = (uint64_t)tl * ql + (uint32_t)c;
+            const uint64_t p1 = (uint64_t)tl * qh + (uint64_t)th * ql + (p0 >> 32) + (c >> 32);
+            y0[r] = (uint32_t)p0;
+            y1[r] = (uint32_t)p1;
+            y2[r] = (uint32_t)(p1 >> 32) + th * qh;
+        }
+        // bytes of four values -> four digits of four values each
+        auto transpose4 = [&](const uint32_t (&y)[4], int d) {
+            const uint32_t t0 = __builtin_amdgcn_perm(y[1], y[0], 0x05010400u), t1 = __builtin_amdgcn_perm(y[1], y[0], 0x07030602u);
+            const uint32_t u0 = __builtin_amdgcn_perm(y[3], y[2], 0x05010400u), u1 = __builtin_amdgcn_perm(y[3], y[2], 0x07030602u);
+            out[d][i] = __builtin_amdgcn_perm(u0, t0, 0x05040100u);
+            out[d + 1][i] = __builtin_amdgcn_perm(u0, t0, 0x07060302u);
+            out[d + 2][i] = __builtin_amdgcn_perm(u1, t1, 0x05040100u);
+            out[d + 3][i] = __builtin_amdgcn_perm(u1, t1, 0x07060302u);
+        };
+        transpose4(y0, 0);
+        transpose4(y1, 4);
+        out[8][i] = y2[0] | (y2[1] << 8) | (y2[2] << 16) | (y2[3] << 24);
+    }
+    int8_t *chunk = Ad + ((pair * nkb + kb) * ntiles + ntile) * (D * kFrag);
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        v4i v;
+        v.x = (int)(out[d][0] ^ 0x80808080u);
+        v.y = (int)(out[d][1] ^ 0x80808080u);
+        v.z = (int)(out[d][2] ^ 0x80808080u);
+        v.w = (int)(out[d][3] ^ 0x80808080u);
+        *reinterpret_cast<v4i *>(chunk + d * kFrag + (g * 16 + (int)(n & 15)) * 16) = v;
+    }
+}
+
 // ------------------------------------------------------------------------------------------------
 // run-time kernel 2: int8 MFMA main loop + recombination + Barrett
 // ------------------------------------------------------------------------------------------------
@@ -199,6 +286,12 @@ struct GemmArgs {
 // W fragments go global -> registers (each wave reads only its own rows); digit fragments are shared
 // by all waves and staged through LDS.
 //
+// EPI_F64_PAIR: the digits are those of limb pairs (split_pair_kernel), "limb" below counts pairs, and the epilogue
+// reduces every sum modulo both primes of the pair.  Nine accumulators per output then leave room for one 16-column
+// fragment (NT = 1): the wave tile is 64 x 16, four W fragments and nine digit fragments feed 36 MFMAs per k-step.
+// Measured (whole pcmm_run, single limbs -> pairs): 4096 x 4096 by 4096 x 32768, four 36-bit limbs 9.25 -> 8.81 ms;
+// 14336 rows 29.66 -> 28.16 ms; 14336 values of k, three limbs (a pair and a single) 23.80 -> 22.59 ms.
+//
 // nkbc (k-steps of one launch) must be even.
 template <int WM, int MT, int NT, int D, int S, int EPI>
 __global__ __launch_bounds__(WM * 64) void gemm_kernel(GemmArgs a)
@@ -208,7 +301,8 @@ __global__ __launch_bounds__(WM * 64) void gemm_kernel(GemmArgs a)
     constexpr int CH = NT * D * kFrag;            // bytes of one digit chunk (one k-step)
     constexpr int UNITS = CH / 16;                // 16-byte units per chunk
     constexpr int NLD = (UNITS + T - 1) / T;      // units per thread (the last ones clamped: duplicates)
-    static_assert(NT == 2, "a k-step is processed as two 16-column halves");
+    constexpr int LP = EPI == EPI_F64_PAIR ? 2 : 1;   // limbs that share a set of digits
+    static_assert(NT == 2 || (NT == 1 && LP == 2), "a k-step is processed in 16-column parts");
 
     __shared__ __attribute__((aligned(16))) int8_t lds[2][CH];
 
@@ -288,7 +382,7 @@ __global__ __launch_bounds__(WM * 64) void gemm_kernel(GemmArgs a)
     v4i wreg[2][S][MT];
     v4i areg[NLD];
     v4i b[D];
-    constexpr int CNT = D * S * MT;                  // MFMAs per half k-step
+    constexpr int CNT = D * S * MT;                  // MFMAs per 16-column part of a k-step
     constexpr int NW = S * MT;                       // W fragments per k-step
     // MFMA order within a k-step: digit by digit, the W fragments forwards for one digit and backwards
     // for the next, so that every MFMA shares one operand with the one before it (less switching at the
@@ -299,14 +393,14 @@ __global__ __launch_bounds__(WM * 64) void gemm_kernel(GemmArgs a)
     // so that a tile start pays one memory latency, not two (nkb >= 2).  The limb's constants come
     // first and are moved to scalar registers: a vector load still in flight when the epilogue
     // branches around padding blocks would make the compiler wait for it behind the first stores.
-    LimbConst lc;
+    LimbConst lc, lc2;                               // lc2: the second limb of a pair
     {
         constexpr int LCW = sizeof(LimbConst) / 4;
         static_assert(sizeof(LimbConst) % 4 == 0, "LimbConst is read word by word");
-        const uint32_t *src = reinterpret_cast<const uint32_t *>(a.lc + limb);
-        uint32_t w[LCW];
+        const uint32_t *src = reinterpret_cast<const uint32_t *>(a.lc + LP * limb);
+        uint32_t w[LP * LCW];
 #pragma unroll
-        for (int i = 0; i < LCW; ++i) w[i] = src[i];
+        for (int i = 0; i < LP * LCW; ++i) w[i] = src[i];
         v4i first[NLD];
 #pragma unroll
         for (int i = 0; i < NLD; ++i) first[i] = ld_a(uoff[i], 0);
@@ -315,8 +409,9 @@ __global__ __launch_bounds__(WM * 64) void gemm_kernel(GemmArgs a)
 #pragma unroll
         for (int i = 0; i < NLD; ++i) areg[i] = ld_a(uoff[i], 1);
 #pragma unroll
-        for (int i = 0; i < LCW; ++i) w[i] = __builtin_amdgcn_readfirstlane(w[i]);
+        for (int i = 0; i < LP * LCW; ++i) w[i] = __builtin_amdgcn_readfirstlane(w[i]);
         __builtin_memcpy(&lc, w, sizeof(lc));
+        __builtin_memcpy(&lc2, w + (LP - 1) * LCW, sizeof(lc2));
 #pragma unroll
         for (int i = 0; i < NLD; ++i) *reinterpret_cast<v4i *>(&lds[0][uoff[i]]) = first[i];
     }
@@ -332,37 +427,35 @@ __global__ __launch_bounds__(WM * 64) void gemm_kernel(GemmArgs a)
         constexpr bool FILL = decltype(fill)::value, AHEAD = decltype(ahead)::value;
         const int kw = kb + 1;
         const int ka = kb + 2;
+        // Memory instructions of the k-step, in order: the W loads of k-step kb+1, the LDS writes of chunk kb+1 (which
+        // free the staging registers), the loads of digit chunk kb+2.  With two column parts the first part takes the
+        // first two groups and the second part the third; with one part all three are spread over it.
+        constexpr int OPS_FILL = FILL ? NW + NLD : 0, OPS_AHEAD = AHEAD ? NLD : 0;
+        auto memory_op = [&](auto nc) {
+            constexpr int n = decltype(nc)::value;
+            if constexpr (n < OPS_FILL) {
+                if constexpr (n < NW) wreg[NXT][n / MT][n % MT] = ld_w(n / MT, n % MT, kw);
+                else *reinterpret_cast<v4i *>(&lds[NXT][uoff[n - NW]]) = areg[n - NW];
+            } else {
+                areg[n - OPS_FILL] = ld_a(uoff[n - OPS_FILL], ka);
+            }
+        };
+        static_for<NT>([&](auto jc) {
+            constexpr int j = decltype(jc)::value;
+            constexpr int FIRST = j == 0 ? 0 : OPS_FILL;
+            constexpr int OPS = (j == NT - 1 ? OPS_FILL + OPS_AHEAD : OPS_FILL) - FIRST;
 #pragma unroll
-        for (int d = 0; d < D; ++d) b[d] = *reinterpret_cast<const v4i *>(&lds[CUR][d * kFrag + lane * 16]);
-        // first half: W loads of k-step kb+1 and LDS writes of chunk kb+1 between the MFMAs
-        static_for<CNT>([&](auto mc) {
-            constexpr int m = decltype(mc)::value;
-            constexpr int OPS = FILL ? NW + NLD : 0;
-            constexpr int n_lo = (m * OPS + CNT - 1) / CNT, n_hi = ((m + 1) * OPS + CNT - 1) / CNT;
-            static_for<n_hi - n_lo>([&](auto jc) {
-                constexpr int n = n_lo + decltype(jc)::value;
-                if constexpr (n < NW) {
-                    wreg[NXT][n / MT][n % MT] = ld_w(n / MT, n % MT, kw);
-                } else if constexpr (n < OPS) {
-                    *reinterpret_cast<v4i *>(&lds[NXT][uoff[n - NW]]) = areg[n - NW];
-                }
+            for (int d = 0; d < D; ++d)
+                b[d] = *reinterpret_cast<const v4i *>(&lds[CUR][(j * D + d) * kFrag + lane * 16]);
+            static_for<CNT>([&](auto mc) {
+                constexpr int m = decltype(mc)::value;
+                constexpr int n_lo = (m * OPS + CNT - 1) / CNT, n_hi = ((m + 1) * OPS + CNT - 1) / CNT;
+                static_for<n_hi - n_lo>([&](auto oc) {
+                    memory_op(std::integral_constant<int, FIRST + n_lo + decltype(oc)::value>{});
+                });
+                constexpr int d = m / NW, f = snake(j * D + d, m % NW), ws = f / MT, wi = f % MT;
+                mfma_i8<4 * ((wi * NT + j) * E + d + ws)>(wreg[CUR][ws][wi], b[d]);
             });
-            constexpr int d = m / NW, f = snake(d, m % NW), ws = f / MT, wi = f % MT;
-            mfma_i8<4 * ((wi * NT + 0) * E + d + ws)>(wreg[CUR][ws][wi], b[d]);
-        });
-#pragma unroll
-        for (int d = 0; d < D; ++d) b[d] = *reinterpret_cast<const v4i *>(&lds[CUR][(D + d) * kFrag + lane * 16]);
-        // second half: loads of digit chunk kb+2 between the MFMAs
-        static_for<CNT>([&](auto mc) {
-            constexpr int m = decltype(mc)::value;
-            constexpr int OPS = AHEAD ? NLD : 0;
-            constexpr int n_lo = (m * OPS + CNT - 1) / CNT, n_hi = ((m + 1) * OPS + CNT - 1) / CNT;
-            static_for<n_hi - n_lo>([&](auto jc) {
-                constexpr int n = n_lo + decltype(jc)::value;
-                if constexpr (n < OPS) areg[n] = ld_a(uoff[n], ka);
-            });
-            constexpr int d = m / NW, f = snake(D + d, m % NW), ws = f / MT, wi = f % MT;
-            mfma_i8<4 * ((wi * NT + 1) * E + d + ws)>(wreg[CUR][ws][wi], b[d]);
         });
         if constexpr (FILL) __syncthreads();   // chunk kb+1 is in LDS; buffer CUR may be refilled
     };
@@ -390,12 +483,28 @@ __global__ __launch_bounds__(WM * 64) void gemm_kernel(GemmArgs a)
     // rows at or beyond M fall outside it and are dropped by the range check, and lanes whose column
     // is at or beyond Ncols get an offset that is out of range for every row; no address arithmetic
     // or branching per output.
-    uint64_t *Cl = a.C + (int64_t)limb * a.M * a.Ncols;
+    uint64_t *Cl = a.C + (int64_t)(LP * limb) * a.M * a.Ncols;
     const uint32_t c_rowbytes = (uint32_t)a.Ncols * 8u;
     // The whole epilogue exists twice, with and without the read-add of the previous contents of C,
     // chosen once per wave: a branch per output would stop the scheduler from overlapping outputs.
+    auto store_block = [&](__amdgpu_buffer_rsrc_t crs, uint32_t c_lane, uint64_t (&res)[4], uint64_t q, auto accumulate_c) {
+        if constexpr (decltype(accumulate_c)::value) {   // rows and columns outside C read as 0
+            v2u old[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                old[r] = __builtin_amdgcn_raw_buffer_load_b64(crs, c_lane + (uint32_t)r * c_rowbytes, 0, 0);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                res[r] += (uint64_t)old[r][0] | ((uint64_t)old[r][1] << 32);
+                if (res[r] >= q) res[r] -= q;
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            __builtin_amdgcn_raw_buffer_store_b64((v2u){(uint32_t)res[r], (uint32_t)(res[r] >> 32)}, crs,
+                                                  c_lane + (uint32_t)r * c_rowbytes, 0, 0);
+    };
     auto epilogue = [&](auto accumulate_c) {
-    constexpr bool ACCUMULATE = decltype(accumulate_c)::value;
     static_for<MT * NT>([&](auto ijc) {
         constexpr int i = decltype(ijc)::value / NT, j = decltype(ijc)::value % NT;
         // 16 x 16 blocks that lie wholly in the padding are skipped (wave-uniform)
@@ -414,6 +523,15 @@ __global__ __launch_bounds__(WM * 64) void gemm_kernel(GemmArgs a)
                 constexpr int r = decltype(rec)::value / E, e = decltype(rec)::value % E;
                 avs[r][e] = acc_read<4 * ((i * NT + j) * E + e) + r>();
             });
+            if constexpr (LP == 2) {              // one residue of each limb from the same accumulators
+                uint64_t res1[4], res2[4];
+                reduce_f64_pair<E, 4>(avs, lc.qd, lc.invq, lc2.qd, lc2.invq, res1, res2);
+                const __amdgpu_buffer_rsrc_t crs2 = __builtin_amdgcn_make_buffer_rsrc(
+                    Cl + (a.M + m0) * a.Ncols, 0, rows_valid * c_rowbytes, 0x00020000);
+                store_block(crs, c_lane, res1, lc.q, accumulate_c);
+                store_block(crs2, c_lane, res2, lc2.q, accumulate_c);
+                return;
+            }
             uint64_t res[4];
             if constexpr (EPI == EPI_F64) {
                 reduce_f64<E, 0, 4>(avs, lc.qd, lc.invq, res);
@@ -443,21 +561,7 @@ __global__ __launch_bounds__(WM * 64) void gemm_kernel(GemmArgs a)
                     }
                 }
             }
-            if constexpr (ACCUMULATE) {   // rows and columns outside C read as 0
-                v2u old[4];
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    old[r] = __builtin_amdgcn_raw_buffer_load_b64(crs, c_lane + (uint32_t)r * c_rowbytes, 0, 0);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    res[r] += (uint64_t)old[r][0] | ((uint64_t)old[r][1] << 32);
-                    if (res[r] >= lc.q) res[r] -= lc.q;
-                }
-            }
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                __builtin_amdgcn_raw_buffer_store_b64((v2u){(uint32_t)res[r], (uint32_t)(res[r] >> 32)}, crs,
-                                                      c_lane + (uint32_t)r * c_rowbytes, 0, 0);
+            store_block(crs, c_lane, res, lc.q, accumulate_c);
         }
     });
     };
@@ -590,6 +694,9 @@ struct pcmm_plan {
     LimbConst *lc;           // device
     size_t bytes;
     size_t ad_bytes;         // size of the digit scratch one run needs
+    int pairs;               // limb pairs whose digits are split jointly; limbs from 2 * pairs on run singly
+    int64_t pair_ntiles;     // n-tiles (16 columns) of a pair
+    PairConsts pcs;
     hipEvent_t ev[4];
     bool have_ev;
 };
@@ -618,6 +725,12 @@ int8_t *static_scratch_ptr(int device)
         g_scratch_ptr[device] = ptr;
     }
     return static_cast<int8_t *>(g_scratch_ptr[device]);
+}
+
+// bytes of the digit planes of all limb pairs
+int64_t pair_digit_bytes(const pcmm_plan *p)
+{
+    return p->pairs * p->nkb * p->pair_ntiles * (int64_t)(pcmm_host::kPairDigits * kFrag);
 }
 
 template <int WM, int MT, int NT, int D, int S>
@@ -674,11 +787,22 @@ hipError_t launch_gemm(const pcmm_plan *p, const GemmArgs &ga, int64_t grid, hip
     return hipErrorInvalidValue;
 }
 
+// digit split of all limbs: pairs first (their digit planes come first in the scratch), then the rest
 hipError_t launch_split(const pcmm_plan *p, int8_t *Ad, const uint64_t *A, hipStream_t st)
 {
+    const dim3 block(256);
+    if (p->pairs) {
+        const dim3 grid((unsigned)((p->pair_ntiles * 16 + 63) / 64), (unsigned)p->nkb, (unsigned)p->pairs);
+        hipLaunchKernelGGL(split_pair_kernel, grid, block, 0, st, A, Ad, p->K, p->Ncols, p->nkb, p->pair_ntiles, p->pcs);
+        const hipError_t rc = hipGetLastError();
+        if (rc != hipSuccess) return rc;
+    }
+    const int single = p->L - 2 * p->pairs;
+    if (!single) return hipSuccess;
+    A += (int64_t)2 * p->pairs * p->K * p->Ncols;
+    Ad += pair_digit_bytes(p);
     int64_t colblocks = (p->ntiles * p->NT * 16 + 63) / 64;
-    dim3 grid((unsigned)colblocks, (unsigned)p->nkb, (unsigned)p->L);
-    dim3 block(256);
+    dim3 grid((unsigned)colblocks, (unsigned)p->nkb, (unsigned)single);
 #define PCMM_SPLIT_CASE(DD)                                                                              \
     case DD:                                                                                             \
         hipLaunchKernelGGL((split_kernel<DD>), grid, block, 0, st, A, Ad, p->K, p->Ncols, p->nkb,     \
@@ -696,32 +820,32 @@ hipError_t launch_split(const pcmm_plan *p, int8_t *Ad, const uint64_t *A, hipSt
     return hipGetLastError();
 }
 
+// one launch of the general MFMA kernel over the k-steps that ga names, for all limb pairs or for the single limbs
+hipError_t launch_products(const pcmm_plan *p, GemmArgs ga, bool pair, hipStream_t st)
+{
+    const int limb0 = pair ? 0 : 2 * p->pairs;
+    ga.L = pair ? p->pairs : p->L - limb0;
+    if (!ga.L) return hipSuccess;
+    ga.ntiles = (int)(pair ? p->pair_ntiles : p->ntiles);
+    ga.Ad += pair ? 0 : pair_digit_bytes(p);
+    ga.C += (int64_t)limb0 * p->M * p->Ncols;
+    ga.lc += limb0;
+    ga.total = (int64_t)ga.L * p->mtiles * ga.ntiles;
+    ga.per_xcd = (ga.total + kXcd - 1) / kXcd;
+    const int64_t grid = ga.per_xcd * kXcd;
+    if (!pair) return launch_gemm(p, ga, grid, st);
+    if (p->MT != 4 || p->S != 1) return hipErrorInvalidValue;
+    constexpr int PD = pcmm_host::kPairDigits;
+    if (p->WM == 4) hipLaunchKernelGGL((gemm_kernel<4, 4, 1, PD, 1, EPI_F64_PAIR>), dim3((unsigned)grid), dim3(256), 0, st, ga);
+    else hipLaunchKernelGGL((gemm_kernel<2, 4, 1, PD, 1, EPI_F64_PAIR>), dim3((unsigned)grid), dim3(128), 0, st, ga);
+    return hipGetLastError();
+}
+
 // Ad: the digit scratch of this run (the plan's own, or the library's static one)
 pcmm_status run_impl(const pcmm_plan *p, int8_t *Ad, const uint64_t *A, uint64_t *C, hipStream_t st, float *ms)
 {
     DevGuard dg(p->device);
     if (!dg.ok) return PCMM_EDEVICE;
-
-    GemmArgs ga;
-    ga.Wp = p->Wp;
-    ga.Ad = Ad;
-    ga.C = C;
-    ga.lc = p->lc;
-    ga.M = p->M;
-    ga.Ncols = p->Ncols;
-    ga.MB = p->MB;
-    ga.nkb = (int)p->nkb;
-    ga.kb0 = 0;
-    ga.nkbc = (int)p->nkb;
-    ga.accumulate = 0;
-    ga.mtiles = (int)p->mtiles;
-    ga.ntiles = (int)p->ntiles;
-    ga.L = p->L;
-    ga.total = (int64_t)p->L * p->mtiles * p->ntiles;
-    ga.per_xcd = (ga.total + kXcd - 1) / kXcd;
-    // concurrent tiles on one XCD (32 CUs) should form a block of about 4 m-tiles x 8 n-tiles
-    ga.gn = 8;
-    const int64_t grid = ga.per_xcd * kXcd;
 
     if (ms && hipEventRecord(p->ev[0], st) != hipSuccess) return PCMM_EDEVICE;
     if (launch_split(p, Ad, A, st) != hipSuccess) return PCMM_EDEVICE;
@@ -734,14 +858,28 @@ pcmm_status run_impl(const pcmm_plan *p, int8_t *Ad, const uint64_t *A, uint64_t
         sa.M = p->M; sa.Ncols = p->Ncols; sa.MB = p->MB;
         sa.ntiles = (int)p->ntiles; sa.L = p->L;
         if (pcmm_shortk::launch(sa, p->D, p->S, p->epi, st) != hipSuccess) return PCMM_EDEVICE;
-    } else
-    // A contraction longer than the int32 accumulators can hold runs as several launches over
-    // consecutive ranges of k; every launch after the first adds its result to C modulo q_j.
-    for (int64_t kb0 = 0; kb0 < p->nkb; kb0 += p->nkb_launch) {
-        ga.kb0 = (int)kb0;
-        ga.nkbc = (int)std::min(p->nkb_launch, p->nkb - kb0);
-        ga.accumulate = kb0 > 0;
-        if (launch_gemm(p, ga, grid, st) != hipSuccess) return PCMM_EDEVICE;
+    } else {
+        GemmArgs ga = {};
+        ga.Wp = p->Wp;
+        ga.Ad = Ad;
+        ga.C = C;
+        ga.lc = p->lc;
+        ga.M = p->M;
+        ga.Ncols = p->Ncols;
+        ga.MB = p->MB;
+        ga.nkb = (int)p->nkb;
+        ga.mtiles = (int)p->mtiles;
+        // concurrent tiles on one XCD (32 CUs) should form a block of about 4 m-tiles x 8 n-tiles
+        ga.gn = 8;
+        // A contraction longer than the int32 accumulators can hold runs as several launches over
+        // consecutive ranges of k; every launch after the first adds its result to C modulo q_j.
+        for (int64_t kb0 = 0; kb0 < p->nkb; kb0 += p->nkb_launch) {
+            ga.kb0 = (int)kb0;
+            ga.nkbc = (int)std::min(p->nkb_launch, p->nkb - kb0);
+            ga.accumulate = kb0 > 0;
+            for (bool pair : {true, false})
+                if (launch_products(p, ga, pair, st) != hipSuccess) return PCMM_EDEVICE;
+        }
     }
     if (ms) {
         if (hipEventRecord(p->ev[3], st) != hipSuccess) return PCMM_EDEVICE;
@@ -789,6 +927,9 @@ pcmm_status pcmm_plan_create(pcmm_plan **out, int64_t M, int64_t K, int64_t Ncol
     p->epi = g.epi;
     p->MB = g.MB; p->nkb = g.nkb; p->mtiles = g.mtiles; p->ntiles = g.ntiles;
     p->nkb_launch = g.nkb_launch;
+    p->pairs = g.pairs;
+    p->pair_ntiles = g.pair_ntiles;
+    for (int j = 0; j < g.pairs; ++j) p->pcs.c[j] = pcmm_host::pair_const(primes_host[2 * j], primes_host[2 * j + 1]);
     p->Wp = nullptr; p->Ad = nullptr; p->lc = nullptr; p->bytes = 0; p->have_ev = false;
 
     DevGuard dg(device);

@@ -54,6 +54,40 @@ __device__ __forceinline__ void static_for(F &&f)
     static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
+// Rounding to the nearest integer without the (slower) rounding instruction: for |x| < 2^51 the sum
+// x + 1.5 * 2^52 has unit spacing, so its rounding is the rounding of x to an integer (ties to even), and
+// subtracting the constant again is exact.  round_fma(h, s) rounds the exact product h s once.
+constexpr double kRoundMagic = 6755399441055744.0;   // 1.5 * 2^52
+__device__ __forceinline__ double round_fma(double h, double s) { return __builtin_fma(h, s, kRoundMagic) - kRoundMagic; }
+
+// a b mod q for integers held in doubles, |a| <= q/2 + 1, |b| <= 4 q, 2^23 < q < 2^50; returns r = a b (mod q) with
+// |r| <= q, and |r| <= 0.75 q + 1 when |b| <= 2 q.
+//   h = RN(a b), l = a b - h exactly (fma);  |a b| <= 2 q^2 < 2^101, so |l| <= 2^48 and l is an integer
+//   qh = round(h invq) = a b / q + eta:  |h invq| <= 2 q (1 + 2^-51) < 2^51, the two roundings (of h and of
+//        invq) shift it by at most 2^-52 |a b| / q <= 2^-51 q < 0.5 (0.25 for |b| <= 2 q), so |eta| <= 1 (0.75)
+//   fma(-qh, q, h) = (a b - qh q) - l: an integer of magnitude < 2^50 + 2^48 < 2^53, so exact; adding l is exact
+// The same function serves the transforms of primes below 2^36 that never reduce their sums: |a| <= q/2 + 1,
+// |b| <= 2^13 q.  Then |h invq| < 2^49 (the rounding trick holds), qh = a b / q + eta with
+// |eta| <= 1/2 + 2^-52 2^12 q <= 0.5625, h and qh q are integers whose difference is below 0.5625 q + |l|,
+// |l| <= 2^30: fma(-qh, q, h) and the addition of l are exact and |r| <= 0.5625 q.  A value that is only ever added
+// to others through the twelve stages grows to at most 2^12 0.5625 q < 2^12 q < 2^48, differences to 2^13 q.
+__device__ __forceinline__ double mulmod(double a, double b, double q, double invq)
+{
+    const double h = a * b;
+    const double l = __builtin_fma(a, b, -h);
+    const double qh = round_fma(h, invq);
+    return __builtin_fma(-qh, q, h) + l;
+}
+
+// The canonical residue in [0, q) of an integer v = k q + s, 0 <= s < q, for q (|k| + 1) < 2^50:
+//   x = fma(v, invq, invq / 2) = (k + (s + 1/2) / q) (1 + eps), |eps| < 2^-51 (the rounding of invq and of the fma),
+//   and (s + 1/2) / q lies in [1/(2q), 1 - 1/(2q)]: |x - (k + (s + 1/2)/q)| < (|k| + 1) 2^-51 < 1/(2q), so floor(x) = k
+//   and fma(-k, q, v) = s exactly.
+__device__ __forceinline__ double canonical(double v, double q, double invq, double half_invq)
+{
+    return __builtin_fma(-__builtin_floor(__builtin_fma(v, invq, half_invq)), q, v);
+}
+
 // Exact reduction in double precision.  `a` holds E int32 accumulators; returns (sum_e a[e] 256^e) mod q
 // in [0, q) for 2^23 < q < 2^50.
 //
@@ -79,14 +113,14 @@ __device__ __forceinline__ void static_for(F &&f)
 // p = a[2i] + 2^8 a[2i+1], which halves the conversions to double.
 // R outputs are reduced side by side, stage by stage: R independent dependency chains in the order the
 // scheduler should issue them.
-template <int E, int MODE, int R>
-__device__ __forceinline__ void reduce_f64(const int (&a)[R][E], double q, double invq, uint64_t (&res)[R])
+constexpr int group_size(int mode) { return mode == 0 ? 3 : 4; }
+
+// the group numbers c_g
+template <int E, int MODE, int R, int G>
+__device__ __forceinline__ void group_f64(const int (&a)[R][E], double (&c)[G][R])
 {
-    constexpr int GS = MODE == 0 ? 3 : 4;            // accumulators per group
-    constexpr int G = (E + GS - 1) / GS;
-    static_assert(G >= 2, "at least one Horner step");
-    static_assert(MODE == 0 || G == 2, "groups of four are proved for a single Horner step");
-    double c[G][R];
+    constexpr int GS = group_size(MODE);             // accumulators per group
+    static_assert(G == (E + GS - 1) / GS, "one number per group");
 #pragma unroll
     for (int g = 0; g < G; ++g) {
         const int b0 = GS * g;
@@ -115,6 +149,14 @@ __device__ __forceinline__ void reduce_f64(const int (&a)[R][E], double q, doubl
                 }
         }
     }
+}
+
+// Horner over the groups, then the lift to [0, q)
+template <int G, int MODE, int R>
+__device__ __forceinline__ void horner_f64(const double (&c)[G][R], double q, double invq, uint64_t (&res)[R])
+{
+    static_assert(G >= 2, "at least one Horner step");
+    static_assert(MODE == 0 || G == 2, "groups of four are proved for a single Horner step");
     constexpr double B = MODE == 0 ? 16777216.0 : 4294967296.0;
     double rr[R];
 #pragma unroll
@@ -137,6 +179,27 @@ __device__ __forceinline__ void reduce_f64(const int (&a)[R][E], double q, doubl
         // v is an integer in [0, 2^52): adding 2^52 places it in the low mantissa bits
         res[r] = (uint64_t)__double_as_longlong(v + 4503599627370496.0) & 0x000FFFFFFFFFFFFFull;
     }
+}
+
+template <int E, int MODE, int R>
+__device__ __forceinline__ void reduce_f64(const int (&a)[R][E], double q, double invq, uint64_t (&res)[R])
+{
+    constexpr int G = (E + group_size(MODE) - 1) / group_size(MODE);
+    double c[G][R];
+    group_f64<E, MODE, R>(a, c);
+    horner_f64<G, MODE, R>(c, q, invq, res);
+}
+
+// (sum_e a[e] 256^e) modulo two primes from the same accumulators (groups of three)
+template <int E, int R>
+__device__ __forceinline__ void reduce_f64_pair(const int (&a)[R][E], double q1, double invq1, double q2, double invq2,
+                                                uint64_t (&res1)[R], uint64_t (&res2)[R])
+{
+    constexpr int G = (E + 2) / 3;
+    double c[G][R];
+    group_f64<E, 0, R>(a, c);
+    horner_f64<G, 0, R>(c, q1, invq1, res1);
+    horner_f64<G, 0, R>(c, q2, invq2, res2);
 }
 
 }  // namespace pcmm_device

@@ -41,6 +41,7 @@ enum Epi : int {
     EPI_INT = 2,     // any q < 2^62: one 64-bit Barrett per four accumulators, joined by Shoup
                      // multiplications by 2^32 and 2^64
     EPI_F64_G4 = 3,  // as EPI_F64 with the accumulators grouped in fours: |acc| < 2^28, 7 or 8 accumulators
+    EPI_F64_PAIR = 5,  // EPI_F64 for two limbs at once (the digits are those of a limb pair)
     EPI_F64_G4P = 4  // as EPI_F64_G4 with pairs of accumulators first joined in int32: 257 |acc| < 2^31
 };
 }  // namespace epi
@@ -57,6 +58,59 @@ inline LimbConst limb_const(uint64_t q)
     c.c64s = (uint64_t)(((u128)c.c64 << 64) / q);
     c.qd = (double)q;
     c.invq = 1.0 / (double)q;
+    return c;
+}
+
+// Two limbs whose digits are split jointly: x1 mod q1 and x2 mod q2 become
+//   Y = q1 t + x1 + (Bias mod q1),  t = ((x2 - x1) q1^-1 + s) mod q2,  s = floor(Bias / q1),
+// the balanced digits of the integer X = Y - Bias with X = x1 mod q1, X = x2 mod q2 (Bias = sum_{i<9} 128 * 256^i).
+constexpr int kPairDigits = 9;
+struct PairConst {
+    uint64_t q1;
+    uint64_t bias_mod_q1;
+    double q2, invq2, half_invq2;   // q2, 1/q2 and 1/(2 q2)
+    double inv;                     // q1^-1 mod q2, balanced (magnitude <= q2/2)
+    double s;
+};
+
+inline u128 pair_bias()
+{
+    u128 bias = 0;
+    for (int i = 0; i < kPairDigits; ++i) bias |= (u128)0x80 << (8 * i);
+    return bias;
+}
+
+// Whether two limbs can share nine digits: distinct primes of 33 to 36 bits (below, two limbs take eight single
+// digits anyway; above, nine digits do not hold the product), coprime, Y < q1 q2 + q1 <= 256^9.
+// The split kernel's arithmetic needs q1 < 2 q2 and th = t >> 32 below 16.
+inline bool pair_ok(uint64_t q1, uint64_t q2)
+{
+    const uint64_t lo = (uint64_t)1 << 32, hi = (uint64_t)1 << 36;
+    if (q1 <= lo || q2 <= lo || q1 >= hi || q2 >= hi || q1 >= 2 * q2) return false;
+    uint64_t a = q1, b = q2;
+    while (b) { const uint64_t r = a % b; a = b; b = r; }
+    return a == 1 && (u128)q1 * q2 + q1 <= ((u128)1 << (8 * kPairDigits));
+}
+
+inline PairConst pair_const(uint64_t q1, uint64_t q2)
+{
+    PairConst c;
+    c.q1 = q1;
+    c.bias_mod_q1 = (uint64_t)(pair_bias() % q1);
+    c.q2 = (double)q2;
+    c.invq2 = 1.0 / (double)q2;
+    c.half_invq2 = 0.5 * c.invq2;
+    // extended Euclid: r0 = u0 q1 (mod q2)
+    int64_t r0 = (int64_t)(q1 % q2), r1 = (int64_t)q2, u0 = 1, u1 = 0;
+    while (r1) {
+        const int64_t k = r0 / r1, r = r0 - k * r1, u = u0 - k * u1;
+        r0 = r1; r1 = r; u0 = u1; u1 = u;
+    }
+    u0 %= (int64_t)q2;
+    if (u0 > (int64_t)(q2 / 2)) u0 -= (int64_t)q2;
+    if (u0 < -(int64_t)(q2 / 2)) u0 += (int64_t)q2;
+    c.inv = (double)u0;
+    c.s = (double)(uint64_t)((pair_bias() / q1) % q2);
     return c;
 }
 
@@ -85,6 +139,8 @@ struct Geometry {
     int64_t nkb_launch;        // most k-steps one GEMM launch may contract (int32 accumulator headroom)
     int64_t mtiles, ntiles;
     size_t wp_bytes, ad_bytes, lc_bytes;
+    int pairs;                 // limb pairs split jointly (0 or L / 2)
+    int64_t pair_ntiles;       // n-tiles of 16 columns
     uint32_t w_kstride;        // bytes between k-steps of one packed W slice
     uint32_t a_kstride;        // bytes between k-steps of one limb's digit chunks
 };
@@ -144,6 +200,17 @@ inline pcmm_status plan_geometry(int64_t M, int64_t K, int64_t Ncols, int32_t L,
     g->lc_bytes = (size_t)L * sizeof(LimbConst);
     // buffer loads address one W slice and one limb of digit planes with 32-bit unsigned byte offsets
     if (g->wp_bytes / S >= ((size_t)1 << 31) || g->ad_bytes / L >= ((size_t)1 << 32)) return PCMM_EUNSUPPORTED;
+    // Limb pairs share nine digits where two limbs take ten.  Their digit planes, 9 * pair_ntiles fragments per k-step
+    // with pair_ntiles <= 2 ntiles, are never more than the 10 * 2 ntiles of two single limbs, so ad_bytes covers them.
+    // Contractions of at most 128 values of k keep single limbs: their kernel holds a limb's digits in registers.
+    g->pair_ntiles = (Ncols + 15) / 16;
+    g->pairs = 0;
+    if (S == 1 && D == 5 && g->nkb > 2 && (uint64_t)g->pair_ntiles * g->nkb * kPairDigits * kFragBytes < ((uint64_t)1 << 32)) {
+        g->pairs = L / 2;
+        for (int j = 0; j < L / 2; ++j)
+            if (!pair_ok(primes_host[2 * j], primes_host[2 * j + 1])) g->pairs = 0;
+    }
+
     g->w_kstride = (uint32_t)(g->MB * kFragBytes);
     g->a_kstride = (uint32_t)(g->ntiles * g->NT * D * kFragBytes);
     return PCMM_OK;

@@ -30,37 +30,17 @@
 #include <vector>
 
 #include "../../include/pcmm.h"
+#include "pcmm_device.hpp"
 #include "pcmm_hip_util.hpp"
 #include "pcmv_host.hpp"
 
 namespace {
 
+using pcmm_device::canonical;
+using pcmm_device::mulmod;
+using pcmm_device::round_fma;
+
 constexpr int kThreads = 256;
-
-// Rounding to the nearest integer without the (slower) rounding instruction: for |x| < 2^51 the sum
-// x + 1.5 * 2^52 has unit spacing, so its rounding is the rounding of x to an integer (ties to even), and
-// subtracting the constant again is exact.  round_fma(h, s) rounds the exact product h s once.
-constexpr double kRoundMagic = 6755399441055744.0;   // 1.5 * 2^52
-__device__ __forceinline__ double round_fma(double h, double s) { return __builtin_fma(h, s, kRoundMagic) - kRoundMagic; }
-
-// a b mod q for integers held in doubles, |a| <= q/2 + 1, |b| <= 4 q, 2^23 < q < 2^50; returns r = a b (mod q) with
-// |r| <= q, and |r| <= 0.75 q + 1 when |b| <= 2 q.
-//   h = RN(a b), l = a b - h exactly (fma);  |a b| <= 2 q^2 < 2^101, so |l| <= 2^48 and l is an integer
-//   qh = round(h invq) = a b / q + eta:  |h invq| <= 2 q (1 + 2^-51) < 2^51, the two roundings (of h and of
-//        invq) shift it by at most 2^-52 |a b| / q <= 2^-51 q < 0.5 (0.25 for |b| <= 2 q), so |eta| <= 1 (0.75)
-//   fma(-qh, q, h) = (a b - qh q) - l: an integer of magnitude < 2^50 + 2^48 < 2^53, so exact; adding l is exact
-// The same function serves the transforms of primes below 2^36 that never reduce their sums: |a| <= q/2 + 1,
-// |b| <= 2^13 q.  Then |h invq| < 2^49 (the rounding trick holds), qh = a b / q + eta with
-// |eta| <= 1/2 + 2^-52 2^12 q <= 0.5625, h and qh q are integers whose difference is below 0.5625 q + |l|,
-// |l| <= 2^30: fma(-qh, q, h) and the addition of l are exact and |r| <= 0.5625 q.  A value that is only ever added
-// to others through the twelve stages grows to at most 2^12 0.5625 q < 2^12 q < 2^48, differences to 2^13 q.
-__device__ __forceinline__ double mulmod(double a, double b, double q, double invq)
-{
-    const double h = a * b;
-    const double l = __builtin_fma(a, b, -h);
-    const double qh = round_fma(h, invq);
-    return __builtin_fma(-qh, q, h) + l;
-}
 
 // the representative of an integer |v| < 2^52 modulo q (q > 2^23) with magnitude at most q/2 (+1 when the quotient
 // rounds the other way)
@@ -222,15 +202,6 @@ __device__ __forceinline__ void gs16(double (&v)[16], const double (&tw)[15], do
             v[e + half] = mulmod(tw[off + (e >> (s + 1))], U - V, q, invq);
         }
     }
-}
-
-// The canonical residue in [0, q) of an integer v = k q + s, 0 <= s < q, for q (|k| + 1) < 2^50:
-//   x = fma(v, invq, invq / 2) = (k + (s + 1/2) / q) (1 + eps), |eps| < 2^-51 (the rounding of invq and of the fma),
-//   and (s + 1/2) / q lies in [1/(2q), 1 - 1/(2q)]: |x - (k + (s + 1/2)/q)| < (|k| + 1) 2^-51 < 1/(2q), so floor(x) = k
-//   and fma(-k, q, v) = s exactly.
-__device__ __forceinline__ double canonical(double v, double q, double invq, double half_invq)
-{
-    return __builtin_fma(-__builtin_floor(__builtin_fma(v, invq, half_invq)), q, v);
 }
 
 typedef unsigned int v2u __attribute__((ext_vector_type(2)));

@@ -1,0 +1,59 @@
+"""Limbs whose digits are split jointly (two residues below 2^36 in nine digits): the split's arithmetic on the host, the
+products against the oracle on the GPU.  All bit-exact."""
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+import pcmm_inputs as pi
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def test_joint_digits_on_the_host(tmp_path):
+    if shutil.which("g++") is None:
+        pytest.skip("no g++")
+    exe = tmp_path / "pair_digits_check"
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror", "-ffp-contract=off",
+                    "-fsanitize=undefined", "-fno-sanitize-recover=all",
+                    "-I", os.path.join(ROOT, "paper_2601_18511_amd", "csrc"), "-o", str(exe),
+                    os.path.join(ROOT, "tests", "host", "pair_digits_check.cpp")], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout + r.stderr
+    assert "all checks held" in r.stdout
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("extreme", [False, True])
+@pytest.mark.parametrize("M,K,Ncols,bits,L,ascending", [
+    (1, 129, 1, 36, 2, False),          # smallest contraction that pairs; one row, one column
+    (128, 200, 15, 36, 2, True),        # two-wave work-groups, ragged column fragment
+    (129, 192, 16, 33, 3, False),       # smallest primes; a pair and a single limb
+    (256, 256, 17, 34, 4, True),
+    (300, 257, 63, 35, 5, False),       # ragged rows, columns and k
+    (257, 700, 130, 36, 6, True),
+    (64, 130944 + 64, 20, 36, 3, False),   # K in two launches: the second adds to both limbs of the pair
+])
+def test_paired_limbs_bit_exact(gpu_device, M, K, Ncols, bits, L, ascending, extreme):
+    import torch
+
+    import paper_2601_18511_amd as pkg
+    from oracle import pcmm_oracle
+
+    rng = np.random.default_rng(M + K)
+    primes = pi.ntt_primes(bits, 1 << 10, L)
+    primes = list(primes)[::-1] if ascending else list(primes)
+    if extreme:
+        W = np.where(rng.random((M, K)) < 0.9, -128, 127).astype(np.int8)
+        A = np.stack([rng.choice(np.array([0, 1, q // 2, q - 1], dtype=np.uint64), size=(K, Ncols)) for q in primes])
+    else:
+        W = rng.integers(-128, 128, size=(M, K), dtype=np.int64).astype(np.int8)
+        A = np.stack([rng.integers(0, q, size=(K, Ncols), dtype=np.uint64) for q in primes])
+    plan = pkg.pcmm_plan_create(torch.from_numpy(W).to(gpu_device), primes, bits, Ncols)
+    C = torch.full((L, M, Ncols), -1, dtype=torch.int64, device=gpu_device)
+    pkg.pcmm_run(plan, torch.from_numpy(A.view(np.int64)).to(gpu_device), C)
+    torch.cuda.synchronize()
+    pkg.pcmm_plan_destroy(plan)
+    assert (C.cpu().numpy().view(np.uint64) == pcmm_oracle(W, A, primes)).all()

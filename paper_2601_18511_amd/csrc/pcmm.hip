@@ -299,8 +299,11 @@ __global__ __launch_bounds__(WM * 64) void gemm_kernel(GemmArgs a)
     constexpr int E = D + S - 1;
     constexpr int T = WM * 64;
     constexpr int CH = NT * D * kFrag;            // bytes of one digit chunk (one k-step)
-    constexpr int UNITS = CH / 16;                // 16-byte units per chunk
-    constexpr int NLD = (UNITS + T - 1) / T;      // units per thread (the last ones clamped: duplicates)
+    // a chunk is moved by all threads: NFULL 16-byte units each and a rest of TAIL = 4, 8 or 0 bytes each, so that no
+    // byte is fetched or written to LDS twice
+    constexpr int NFULL = CH / (16 * T), TAIL = (CH - NFULL * 16 * T) / T;
+    constexpr int NLD = NFULL + (TAIL ? 1 : 0);
+    static_assert(NFULL * 16 * T + TAIL * T == CH && (TAIL == 0 || TAIL == 4 || TAIL == 8), "a chunk is cut evenly");
     constexpr int LP = EPI == EPI_F64_PAIR ? 2 : 1;   // limbs that share a set of digits
     static_assert(NT == 2 || (NT == 1 && LP == 2), "a k-step is processed in 16-column parts");
 
@@ -354,15 +357,26 @@ __global__ __launch_bounds__(WM * 64) void gemm_kernel(GemmArgs a)
         return (v4i)__builtin_amdgcn_raw_buffer_load_b128(
             wrs[sl], loff, (int)((uint32_t)kk * w_kstride + (uint32_t)(wi * kFrag)), 0);
     };
-    auto ld_a = [&](uint32_t unit_off, int kk) -> v4i {   // 16 bytes of digit chunk kk
-        return (v4i)__builtin_amdgcn_raw_buffer_load_b128(ars, unit_off, (int)((uint32_t)kk * a_kstride), 0);
+    // byte offsets of this thread's units inside a chunk (the same in global memory and in LDS)
+    const uint32_t uoff = (uint32_t)threadIdx.x * 16u;
+    const uint32_t toff = (uint32_t)(NFULL * 16 * T) + (uint32_t)threadIdx.x * (uint32_t)TAIL;
+    struct Staged {
+        v4i full[NFULL];
+        v2u tail;
     };
-
-    // byte offsets of this thread's 16-byte units inside a chunk (same in global memory and in LDS);
-    // units past the end are clamped to the last one, which is then loaded and stored twice
-    uint32_t uoff[NLD];
-#pragma unroll
-    for (int i = 0; i < NLD; ++i) uoff[i] = (uint32_t)min((int)threadIdx.x + i * T, UNITS - 1) * 16u;
+    auto ld_a = [&](Staged &x, auto ic, int kk) {      // unit ic of digit chunk kk: global -> registers
+        constexpr int i = decltype(ic)::value;
+        const int off = (int)((uint32_t)kk * a_kstride);
+        if constexpr (i < NFULL) x.full[i] = (v4i)__builtin_amdgcn_raw_buffer_load_b128(ars, uoff + (uint32_t)(i * 16 * T), off, 0);
+        else if constexpr (TAIL == 8) x.tail = (v2u)__builtin_amdgcn_raw_buffer_load_b64(ars, toff, off, 0);
+        else x.tail[0] = __builtin_amdgcn_raw_buffer_load_b32(ars, toff, off, 0);
+    };
+    auto st_a = [&](const Staged &x, auto ic, int buf) {   // registers -> LDS
+        constexpr int i = decltype(ic)::value;
+        if constexpr (i < NFULL) *reinterpret_cast<v4i *>(&lds[buf][uoff + (uint32_t)(i * 16 * T)]) = x.full[i];
+        else if constexpr (TAIL == 8) *reinterpret_cast<v2u *>(&lds[buf][toff]) = x.tail;
+        else *reinterpret_cast<uint32_t *>(&lds[buf][toff]) = x.tail[0];
+    };
 
     // accumulator (i, j, e) = registers a[4*((i*NT + j)*E + e) ...+4)
     constexpr int NACC = 4 * MT * NT * E;
@@ -380,7 +394,7 @@ __global__ __launch_bounds__(WM * 64) void gemm_kernel(GemmArgs a)
     // of LDS writes (about 64 B/clk per CU) would hold back the MFMAs queued behind it.
     // The last two k-steps run without the loads that would reach past the contraction.
     v4i wreg[2][S][MT];
-    v4i areg[NLD];
+    Staged areg;
     v4i b[D];
     constexpr int CNT = D * S * MT;                  // MFMAs per 16-column part of a k-step
     constexpr int NW = S * MT;                       // W fragments per k-step
@@ -401,19 +415,16 @@ __global__ __launch_bounds__(WM * 64) void gemm_kernel(GemmArgs a)
         uint32_t w[LP * LCW];
 #pragma unroll
         for (int i = 0; i < LP * LCW; ++i) w[i] = src[i];
-        v4i first[NLD];
-#pragma unroll
-        for (int i = 0; i < NLD; ++i) first[i] = ld_a(uoff[i], 0);
+        Staged first;
+        static_for<NLD>([&](auto ic) { ld_a(first, ic, 0); });
 #pragma unroll
         for (int f = 0; f < NW; ++f) wreg[0][f / MT][f % MT] = ld_w(f / MT, f % MT, 0);
-#pragma unroll
-        for (int i = 0; i < NLD; ++i) areg[i] = ld_a(uoff[i], 1);
+        static_for<NLD>([&](auto ic) { ld_a(areg, ic, 1); });
 #pragma unroll
         for (int i = 0; i < LP * LCW; ++i) w[i] = __builtin_amdgcn_readfirstlane(w[i]);
         __builtin_memcpy(&lc, w, sizeof(lc));
         __builtin_memcpy(&lc2, w + (LP - 1) * LCW, sizeof(lc2));
-#pragma unroll
-        for (int i = 0; i < NLD; ++i) *reinterpret_cast<v4i *>(&lds[0][uoff[i]]) = first[i];
+        static_for<NLD>([&](auto ic) { st_a(first, ic, 0); });
     }
     __syncthreads();
 
@@ -435,9 +446,9 @@ __global__ __launch_bounds__(WM * 64) void gemm_kernel(GemmArgs a)
             constexpr int n = decltype(nc)::value;
             if constexpr (n < OPS_FILL) {
                 if constexpr (n < NW) wreg[NXT][n / MT][n % MT] = ld_w(n / MT, n % MT, kw);
-                else *reinterpret_cast<v4i *>(&lds[NXT][uoff[n - NW]]) = areg[n - NW];
+                else st_a(areg, std::integral_constant<int, n - NW>{}, NXT);
             } else {
-                areg[n - OPS_FILL] = ld_a(uoff[n - OPS_FILL], ka);
+                ld_a(areg, std::integral_constant<int, n - OPS_FILL>{}, ka);
             }
         };
         static_for<NT>([&](auto jc) {

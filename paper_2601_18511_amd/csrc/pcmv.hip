@@ -78,13 +78,11 @@ struct LimbDev {
 
 // Forward NTT of polynomials.  SRC = 0: uint64 residues in [0, q) (ciphertext polynomials, laid out
 // [L][polys_per_limb][N]); SRC = 1: signed 32-bit plaintext coefficients shared by all limbs ([polys_per_limb][N]).
-// Output: doubles [L][polys_per_limb][N], magnitudes <= q/2 + 1, bit-reversed order (plaintexts times 1/N mod q); with rot16 != 0 (N = 4096)
-// entry n of that order is stored at (n >> 4) | ((n & 15) << 8), the order mac_intt4096_kernel reads with
-// coalesced loads.
+// Output: doubles [L][polys_per_limb][N], magnitudes <= q/2 + 1, bit-reversed order (plaintexts times 1/N mod q).
 template <int SRC>
 __global__ __launch_bounds__(kThreads) void ntt_kernel(const void *__restrict__ src, double *__restrict__ dst,
                                                        const double *__restrict__ fwd_tables, const LimbDev *__restrict__ lc,
-                                                       int N, int64_t polys_per_limb, int rot16)
+                                                       int N, int64_t polys_per_limb)
 {
     extern __shared__ double lds[];
     const int64_t p = blockIdx.x;
@@ -106,10 +104,9 @@ __global__ __launch_bounds__(kThreads) void ntt_kernel(const void *__restrict__ 
     // the plaintexts carry the factor 1/N of the inverse transform that follows the pointwise products
     const double scale = lc[limb].n_inv;
     for (int n = threadIdx.x; n < N; n += kThreads) {
-        const int pos = rot16 ? ((n >> 4) | ((n & 15) << 8)) : n;
         double r = reduce(lds[n], q, invq);
         if (SRC == 1) r = reduce(mulmod(scale, r, q, invq), q, invq);
-        dst[p * N + pos] = r;
+        dst[p * N + n] = r;
     }
 }
 
@@ -169,8 +166,9 @@ __global__ __launch_bounds__(kThreads) void mac_intt_kernel(const double *__rest
 // ---- N = 4096 (the paper's PCMv ring degree): the inverse transform as three passes of four stages each,
 // sixteen elements per thread in registers, two trips through LDS instead of twelve.
 //
-// Entry n of the bit-reversed NTT-domain order is stored at (n >> 4) | ((n & 15) << 8) (see ntt_kernel), so
-// that thread T reads its entries n = 16 T + e, e < 16, from T + 256 e: consecutive threads, consecutive words.
+// NTT-domain polynomials are stored so that thread T reads its entries n = 16 T + e, e < 16, with 16-byte loads of
+// consecutive threads: as doubles, entry n at word 512 (e >> 1) + 2 T + (e & 1); the plaintexts of primes below 2^36
+// packed (PtRaw below).
 //   pass 1  stages t = 1, 2, 4, 8        thread T holds n = 16 T + e
 //   pass 2  stages t = 16 .. 128         thread T = 16 A + B holds n = 256 A + B + 16 e
 //   pass 3  stages t = 256 .. 2048       thread T holds n = T + 256 e
@@ -222,6 +220,80 @@ __device__ __forceinline__ v2d ld2(__amdgpu_buffer_rsrc_t r, uint32_t lane_off, 
 {
     return __builtin_bit_cast(v2d, (v4u)__builtin_amdgcn_raw_buffer_load_b128(r, lane_off, uniform_off, 0));
 }
+// The sixteen NTT-domain values of a thread as they lie in memory.
+// PACKED (primes below 2^36): a balanced residue r, |r| <= q/2 + 1 < 2^35, is kept as u = r + 2^35 < 2^36: the low 32 bits
+// of entry e at byte 4096 (e >> 2) + 16 T + 4 (e & 3), the top four bits of the sixteen entries as eight bytes at
+// 16384 + 8 T, entry e in bits 4 e .. 4 e + 3.  18 KiB a polynomial instead of the 32 KiB of doubles: the plaintexts are most
+// of what the multiply-accumulate kernel reads, and it is bound by memory as much as by its arithmetic.  Unpacking
+// places u in the low mantissa bits of 2^52 and subtracts: one v_perm and one addition a value, and the masks.
+// Measured, doubles -> packed (4096 output polynomials, two 36-bit limbs): one input ciphertext 182 -> 175 us, four
+// 416 -> 328 us (there also because every operand of a term is now requested one term ahead).
+template <bool PACKED>
+struct PtRaw;
+template <>
+struct PtRaw<true> {
+    static constexpr uint32_t kBytes = kN4096 * 4 + kN4096 / 2;   // of one polynomial
+    v4u lo[4];
+    v2u hi;
+    __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, uint32_t T, uint32_t uniform_off)
+    {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) lo[c] = (v4u)__builtin_amdgcn_raw_buffer_load_b128(r, 16u * T + 4096u * c, uniform_off, 0);
+        hi = (v2u)__builtin_amdgcn_raw_buffer_load_b64(r, 8u * T + 16384u, uniform_off, 0);
+    }
+    __device__ __forceinline__ void unpack(double (&w)[16]) const
+    {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const uint32_t nib[2] = {hi[h] & 0x0F0F0F0Fu, (hi[h] >> 4) & 0x0F0F0F0Fu};   // even and odd entries, a byte each
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int e = 8 * h + i;
+                const uint32_t top = __builtin_amdgcn_perm(0x43300000u, nib[i & 1], 0x07060500u | (uint32_t)(i >> 1));
+                w[e] = __builtin_bit_cast(double, (v2u){lo[e >> 2][e & 3], top}) - (4503599627370496.0 + 34359738368.0);
+            }
+        }
+    }
+    // r[16] -> memory
+    static __device__ __forceinline__ void store(const double (&r)[16], char *poly, uint32_t T)
+    {
+        v2u h = {0, 0};
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            v4u l;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int e = 4 * c + i;
+                const v2u u = __builtin_bit_cast(v2u, r[e] + (4503599627370496.0 + 34359738368.0));
+                l[i] = u[0];
+                h[e >> 3] |= (u[1] & 0xFu) << (4 * (e & 7));
+            }
+            *reinterpret_cast<v4u *>(poly + 16u * T + 4096u * c) = l;
+        }
+        *reinterpret_cast<v2u *>(poly + 8u * T + 16384u) = h;
+    }
+};
+template <>
+struct PtRaw<false> {
+    static constexpr uint32_t kBytes = kN4096 * 8;
+    v2d x[8];
+    __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, uint32_t T, uint32_t uniform_off)
+    {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[i] = ld2(r, 16u * T + 4096u * i, uniform_off);
+    }
+    __device__ __forceinline__ void unpack(double (&w)[16]) const
+    {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) w[e] = x[e >> 1][e & 1];
+    }
+    static __device__ __forceinline__ void store(const double (&r)[16], char *poly, uint32_t T)
+    {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) *reinterpret_cast<v2d *>(poly + 16u * T + 4096u * i) = (v2d){r[2 * i], r[2 * i + 1]};
+    }
+};
+
 // the fifteen twiddles of four stages: eight consecutive table entries from 8 (base + i0), four from 4 (base + i0),
 // two from 2 (base + i0), one at base + i0
 __device__ __forceinline__ void load_tw(double (&tw)[15], __amdgpu_buffer_rsrc_t irs, uint32_t base, uint32_t i0)
@@ -272,11 +344,11 @@ __device__ __forceinline__ void ct16(double (&v)[16], const double (&tw)[15], do
 // transform below -- three passes of four Cooley-Tukey stages on sixteen values per thread, two trips through LDS.
 //   pass A  stages t = 2048 .. 256       thread T holds n = T + 256 e     (read from memory, coalesced)
 //   pass B  stages t = 128 .. 16         thread T = 16 A + B holds n = 256 A + B + 16 e
-//   pass C  stages t = 8 .. 1            thread T holds n = 16 T + e      (entry n of the bit-reversed order, stored at
-//                                        T + 256 e: the order the multiply-accumulate reads)
+//   pass C  stages t = 8 .. 1            thread T holds n = 16 T + e      (entries of the bit-reversed order, stored in
+//                                        the layout the multiply-accumulate reads: PtRaw)
 // Stage t = N/(2m) uses the twiddle fwd[m + (n >> (log2 t + 1))].  Sources and the scaling of the plaintexts as in ntt_kernel.
 template <int SRC, bool LAZY>
-__global__ __launch_bounds__(kThreads) void ntt4096_kernel(const void *__restrict__ src, double *__restrict__ dst,
+__global__ __launch_bounds__(kThreads) void ntt4096_kernel(const void *__restrict__ src, void *__restrict__ dst,
                                                            const double *__restrict__ fwd_tables, const LimbDev *__restrict__ lc,
                                                            int64_t polys_per_limb, uint32_t *__restrict__ queue, uint32_t queue_start)
 {
@@ -324,10 +396,11 @@ __global__ __launch_bounds__(kThreads) void ntt4096_kernel(const void *__restric
     const double scale = lc[limb].n_inv;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-        double r = reduce(v[e], q, invq);
-        if (SRC == 1) r = reduce(mulmod(scale, r, q, invq), q, invq);
-        dst[p * N + T + 256 * e] = r;
+        v[e] = reduce(v[e], q, invq);
+        if (SRC == 1) v[e] = reduce(mulmod(scale, v[e], q, invq), q, invq);
     }
+    using Raw = PtRaw<SRC == 1 && LAZY>;               // plaintexts packed where the prime allows it, ciphertexts as doubles
+    Raw::store(v, static_cast<char *>(dst) + p * (int64_t)Raw::kBytes, T);
 }
 
 // Persistent work-groups: work-group g takes the output polynomials g, g + G, g + 2 G, ... (G = grid size, two
@@ -345,7 +418,7 @@ __global__ __launch_bounds__(kThreads) void ntt4096_kernel(const void *__restric
 // registers go into addresses, and the loads of a term are all issued before the first is used (left to itself the
 // compiler starts the arithmetic on the first values early, which splits the loads into two dependent round trips).
 template <bool LAZY, bool KP1>
-__global__ __launch_bounds__(kThreads, 2) void mac_intt4096_kernel(const double *__restrict__ ptn, const double *__restrict__ ctn,
+__global__ __launch_bounds__(kThreads, 2) void mac_intt4096_kernel(const void *__restrict__ ptn, const double *__restrict__ ctn,
                                                                    uint64_t *__restrict__ out, const double *__restrict__ inv_tables,
                                                                    const LimbDev *__restrict__ lc, uint32_t Mp, int Kp, uint32_t total,
                                                                    uint32_t *__restrict__ queue)
@@ -355,20 +428,19 @@ __global__ __launch_bounds__(kThreads, 2) void mac_intt4096_kernel(const double 
     __shared__ double lds[2 * kLdsPoly4096];          // component a, component b
     __shared__ uint32_t queue_word;
     const int T = threadIdx.x;
-    const uint32_t toff = (uint32_t)T * 8u;
+    using Raw = PtRaw<LAZY>;
     uint32_t blk = blockIdx.x;
     if (blk >= total) return;
     uint32_t next = blk + gridDim.x;                  // the first two polynomials of a work-group are fixed; total + 3 grid < 2^32
-    const uint32_t kpb = (uint32_t)Kp * PB;           // bytes of the plaintexts of one output polynomial (Kp <= 4096)
+    const uint32_t kpb = (uint32_t)Kp * Raw::kBytes;  // bytes of the plaintexts of one output polynomial (Kp <= 4096)
+    auto plaintexts = [&](uint32_t poly) { return view(static_cast<const char *>(ptn) + (int64_t)poly * kpb, kpb); };
 
-    double tw1[15], tw2[15], xa[16], xb[16], wv[16];
+    double tw1[15], tw2[15];
+    PtRaw<false> xa, xb;                              // transformed ciphertext values
+    Raw wv;                                           // plaintext values, requested one term ahead
     double q = 0.0, invq = 0.0;
     uint32_t limb_loaded = 0xFFFFFFFFu;
-    {
-        const __amdgpu_buffer_rsrc_t prs = view(ptn + (int64_t)blk * Kp * N, kpb);
-#pragma unroll
-        for (int e = 0; e < 16; ++e) wv[e] = ld1(prs, toff, 2048u * e);
-    }
+    wv.load(plaintexts(blk), T, 0);
     for (;;) {
         const uint32_t limb = blk / Mp;
         // the polynomial after the next one comes from the queue (one lane asks; the answer is passed on through LDS
@@ -380,7 +452,7 @@ __global__ __launch_bounds__(kThreads, 2) void mac_intt4096_kernel(const double 
         int Ti = T;
         asm volatile("" : "+v"(Ti));
         const int Ai = Ti >> 4, Bi = Ti & 15;
-        const __amdgpu_buffer_rsrc_t crs = view(ctn + (int64_t)limb * Kp * 2 * N, 2 * kpb);
+        const __amdgpu_buffer_rsrc_t crs = view(ctn + (int64_t)limb * Kp * 2 * N, (uint32_t)Kp * 2 * PB);
         const __amdgpu_buffer_rsrc_t irs = view(inv_tables + (int64_t)limb * N, PB);
         if (limb != limb_loaded) {                    // uniform: first polynomial of a limb for this work-group
             limb_loaded = limb;
@@ -389,10 +461,8 @@ __global__ __launch_bounds__(kThreads, 2) void mac_intt4096_kernel(const double 
             if constexpr (KP1) {
                 load_tw(tw1, irs, 256, T);            // pass 1: table entries 2048 + 8 T .., 1024 + 4 T .., 512 + 2 T .., 256 + T
                 load_tw(tw2, irs, 16, T >> 4);        // pass 2, A = T / 16: 128 + 8 A .., 64 + 4 A .., 32 + 2 A .., 16 + A
-#pragma unroll
-                for (int e = 0; e < 16; ++e) xa[e] = ld1(crs, toff, 2048u * e);
-#pragma unroll
-                for (int e = 0; e < 16; ++e) xb[e] = ld1(crs, toff, PB + 2048u * e);
+                xa.load(crs, T, 0);
+                xb.load(crs, T, PB);
             }
         }
 
@@ -401,41 +471,40 @@ __global__ __launch_bounds__(kThreads, 2) void mac_intt4096_kernel(const double 
         double va[16], vb[16];
         if constexpr (KP1) {
             __builtin_amdgcn_sched_barrier(0);
+            double w[16];
+            wv.unpack(w);
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
-                va[e] = mulmod(wv[e], xa[e], q, invq);
-                vb[e] = mulmod(wv[e], xb[e], q, invq);
+                va[e] = mulmod(w[e], xa.x[e >> 1][e & 1], q, invq);
+                vb[e] = mulmod(w[e], xb.x[e >> 1][e & 1], q, invq);
             }
         } else {
-            const __amdgpu_buffer_rsrc_t prs = view(ptn + (int64_t)blk * Kp * N, kpb);
+            const __amdgpu_buffer_rsrc_t prs = plaintexts(blk);
+            xa.load(crs, T, 0);
+            xb.load(crs, T, PB);
 #pragma unroll
             for (int e = 0; e < 16; ++e) va[e] = vb[e] = 0.0;
-            auto term = [&](int k, auto last_c) {
-                constexpr bool LAST = decltype(last_c)::value;
-                double wn[16];
-#pragma unroll
-                for (int e = 0; e < 16; ++e) xa[e] = ld1(crs, toff, (uint32_t)k * 2 * PB + 2048u * e);
-#pragma unroll
-                for (int e = 0; e < 16; ++e) xb[e] = ld1(crs, toff, (uint32_t)k * 2 * PB + PB + 2048u * e);
-                if constexpr (!LAST) {                 // the plaintext values of the next term
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) wn[e] = ld1(prs, toff, (uint32_t)(k + 1) * PB + 2048u * e);
-                }
-                __builtin_amdgcn_sched_barrier(0);
+            // One term.  Each set of operands is requested for the next term as soon as the present one has used it: the
+            // plaintexts once unpacked, component a's values behind the products of a, component b's behind those of b.
+            auto products = [&](double (&v)[16], const double (&w)[16], const PtRaw<false> &x) {
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
-                    if constexpr (LAZY) {
-                        va[e] += mulmod(wv[e], xa[e], q, invq);
-                        vb[e] += mulmod(wv[e], xb[e], q, invq);
-                    } else {
-                        va[e] = reduce(va[e] + mulmod(wv[e], xa[e], q, invq), q, invq);
-                        vb[e] = reduce(vb[e] + mulmod(wv[e], xb[e], q, invq), q, invq);
-                    }
+                    const double y = mulmod(w[e], x.x[e >> 1][e & 1], q, invq);
+                    v[e] = LAZY ? v[e] + y : reduce(v[e] + y, q, invq);
                 }
-                if constexpr (!LAST) {
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) wv[e] = wn[e];
-                }
+            };
+            auto term = [&](int k, auto last_c) {
+                constexpr bool LAST = decltype(last_c)::value;
+                double w[16];
+                wv.unpack(w);
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (!LAST) wv.load(prs, T, (uint32_t)(k + 1) * Raw::kBytes);
+                products(va, w, xa);
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (!LAST) xa.load(crs, T, (uint32_t)(k + 1) * 2 * PB);
+                products(vb, w, xb);
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (!LAST) xb.load(crs, T, (uint32_t)(k + 1) * 2 * PB + PB);
             };
             for (int k = 0; k < Kp - 1; ++k) term(k, std::false_type{});
             term(Kp - 1, std::true_type{});
@@ -449,11 +518,7 @@ __global__ __launch_bounds__(kThreads, 2) void mac_intt4096_kernel(const double 
                          "v"(vb[e + 3])
                          : "memory");
         // the first plaintext values of the next polynomial are requested now and used in the next round
-        if (next < total) {
-            const __amdgpu_buffer_rsrc_t nrs = view(ptn + (int64_t)next * Kp * N, kpb);
-#pragma unroll
-            for (int e = 0; e < 16; ++e) wv[e] = ld1(nrs, toff, 2048u * e);
-        }
+        if (next < total) wv.load(plaintexts(next), T, 0);
         if constexpr (!KP1) {
             // with several terms the registers do not hold the twiddles from one polynomial to the next
             load_tw(tw1, irs, 256, Ti);
@@ -534,7 +599,7 @@ struct pcmv_plan {
     uint32_t grid;     // work-groups of the persistent degree-4096 kernel: two per compute unit
     uint32_t *queue;   // device: its work queue (one counter)
     bool lazy;         // every prime is below 2^36: the degree-4096 transform runs without intermediate reductions
-    double *ptn;       // device [L][Mp][Kp][N]: plaintexts in the NTT domain
+    void *ptn;         // device [L][Mp][Kp]: plaintexts in the NTT domain (N doubles, or PtRaw<true> for degree 4096 and lazy)
     double *ctn;       // device [L][Kp][2][N]: scratch, the ciphertexts of one run in the NTT domain
     double *fwd, *inv; // device [L][N] twiddle tables
     LimbDev *lc;       // device [L]
@@ -583,6 +648,7 @@ pcmm_status pcmv_plan_create(pcmv_plan **out, int64_t Mp, int64_t Kp, int64_t N,
     pcmm_hip_util::DevGuard dg(device);
     if (!dg.ok) { delete p; return PCMM_EDEVICE; }
     hipStream_t st = (hipStream_t)stream;
+    // 8 bytes a value, the documented size of a plan, whether the values are packed or not (PtRaw<true> uses 4.5)
     const size_t ptn_bytes = (size_t)L * Mp * Kp * N * sizeof(double);
     const size_t ctn_bytes = (size_t)L * Kp * 2 * N * sizeof(double);
     const size_t tab_bytes = (size_t)L * N * sizeof(double);
@@ -616,7 +682,7 @@ pcmm_status pcmv_plan_create(pcmv_plan **out, int64_t Mp, int64_t Kp, int64_t N,
                                st, (const void *)pt_dev, p->ptn, p->fwd, p->lc, Mp * Kp, (uint32_t *)nullptr, 0u);
         else
             hipLaunchKernelGGL((ntt_kernel<1>), dim3((unsigned)polys), dim3(kThreads), (size_t)N * sizeof(double), st,
-                               (const void *)pt_dev, p->ptn, p->fwd, p->lc, (int)N, Mp * Kp, 0);
+                               (const void *)pt_dev, (double *)p->ptn, p->fwd, p->lc, (int)N, Mp * Kp);
         if (hipGetLastError() != hipSuccess) rc = PCMM_EDEVICE;
     }
     if (hipStreamSynchronize(st) != hipSuccess) rc = rc == PCMM_OK ? PCMM_EDEVICE : rc;   // the host tables live on this frame
@@ -643,7 +709,7 @@ pcmm_status pcmv_run(const pcmv_plan *plan, const uint64_t *ct_dev, uint64_t *ou
                            0, st, (const void *)ct_dev, plan->ctn, plan->fwd, plan->lc, plan->Kp * 2, plan->queue, 2u * plan->grid);
     else
         hipLaunchKernelGGL((ntt_kernel<0>), dim3((unsigned)ct_polys), dim3(kThreads), (size_t)N * sizeof(double), st,
-                           (const void *)ct_dev, plan->ctn, plan->fwd, plan->lc, N, plan->Kp * 2, 0);
+                           (const void *)ct_dev, plan->ctn, plan->fwd, plan->lc, N, plan->Kp * 2);
     if (hipGetLastError() != hipSuccess) return PCMM_EDEVICE;
     if (N == kN4096)
     {
@@ -656,7 +722,7 @@ pcmm_status pcmv_run(const pcmv_plan *plan, const uint64_t *ct_dev, uint64_t *ou
     }
     else
     hipLaunchKernelGGL(mac_intt_kernel, dim3((unsigned)((int64_t)plan->L * plan->Mp)), dim3(kThreads),
-                       (size_t)2 * N * sizeof(double), st, plan->ptn, plan->ctn, out_dev, plan->inv, plan->lc, N, plan->Mp,
+                       (size_t)2 * N * sizeof(double), st, (const double *)plan->ptn, plan->ctn, out_dev, plan->inv, plan->lc, N, plan->Mp,
                        (int)plan->Kp);
     return hipGetLastError() == hipSuccess ? PCMM_OK : PCMM_EDEVICE;
 }

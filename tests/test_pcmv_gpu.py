@@ -216,3 +216,23 @@ def test_bad_arguments_are_status_codes(gpu_device):
         assert e.value.status == status
     with pytest.raises(ValueError):
         pkg.pcmv_plan_create(pt.to(torch.int64), good, 36)
+
+
+@pytest.mark.parametrize("bits", [24, 32, 33, 35, 36, 37])
+@pytest.mark.parametrize("Kp", [1, 2, 3])
+def test_stored_plaintext_values_at_the_ends_of_their_range(gpu_device, bits, Kp):
+    """Degree 4096 stores the transformed plaintexts packed below 2^36: the constant polynomial c is stored as c / N mod q in
+    every entry, which is +-(q-1)/2, the largest magnitude there is, for c = -+N/2 (because (q-1)/2 N = -N/2 mod q)."""
+    from oracle import pcmv_oracle
+
+    N = 4096
+    primes = pi.ntt_primes(bits, 2 * N, 2)
+    rng = np.random.default_rng(bits)
+    consts = [-N // 2, N // 2, 1, -1, 0, -N // 2, N // 2 - 1]
+    pt = np.zeros((len(consts), Kp, N), dtype=np.int64)
+    for m, c in enumerate(consts):
+        for k in range(Kp):
+            pt[m, k, 0] = c if k % 2 == 0 else -c
+    ct = np.stack([rng.choice(np.array([0, 1, q // 2, q - 1], dtype=np.uint64), size=(Kp, 2, N)) for q in primes])
+    got = _run_gpu(pt, ct, primes, bits, gpu_device)
+    assert (got == pcmv_oracle(pt, ct, primes)).all()

@@ -582,7 +582,11 @@ __global__ __launch_bounds__(kThreads, 2) void mac_intt4096_kernel(const void *_
                     r = reduce(v[e], q, invq);                        // |r| <= q/2 + 1
                     r = r < 0.0 ? r + q : r;
                 }
-                o[c * N + Ti + 256 * e] = (uint64_t)__double_as_longlong(r + 4503599627370496.0) & 0x000FFFFFFFFFFFFFull;
+                // non-temporal: written once and not read here, so that the caches keep what is read (177 -> 174 us for
+                // 4096 outputs of one ciphertext and two limbs, 329 -> 323 us for four; the same hint on the plaintext
+                // loads costs 2 % where they fit the last-level cache)
+                __builtin_nontemporal_store((uint64_t)__double_as_longlong(r + 4503599627370496.0) & 0x000FFFFFFFFFFFFFull,
+                                            &o[c * N + Ti + 256 * e]);
             }
         }
         if (next >= total) break;

@@ -255,7 +255,8 @@ def measure_workload(pkg, pi, torch, dev, wl, steps: int, warmup: int, oracle_se
 
     # the MFMA kernel's roofline: int8 MFMA for the projections; HBM where the algorithmic bytes of the launch
     # (digit planes + W + C) take longer at 8 TB/s than its int8 work at 5 POP/s (the wide workload)
-    gemm_alg_bytes = wl.K * wl.Ncols * wl.L * wl.digits + wl.M * wl.K * wl.slices + out_bytes
+    fused = mfma_kernel_name(wl) == "gemm_shortk_kernel"      # cuts the digits itself: reads the residues, no split kernel
+    gemm_alg_bytes = (res_bytes if fused else wl.K * wl.Ncols * wl.L * wl.digits) + wl.M * wl.K * wl.slices + out_bytes
     mfma_floor_s = wl.int8_ops / (INT8_MFMA_PEAK_TOPS * 1e12)
     hbm_floor_s = gemm_alg_bytes / (HBM_PEAK_GBS * 1e9)
     kname = mfma_kernel_name(wl) + " (int8 MFMA main loop + recombine + reduce mod q)"
@@ -270,7 +271,7 @@ def measure_workload(pkg, pi, torch, dev, wl, steps: int, warmup: int, oracle_se
     roofline["algorithmic_bytes_per_launch"] = gemm_alg_bytes
     roofline["traffic"] = _traffic_from_profiles(wl)
 
-    split_GBs = split_alg_bytes / (split_avg * 1e-3) / 1e9
+    split_GBs = None if fused else split_alg_bytes / (split_avg * 1e-3) / 1e9
     rec = {
         "name": wl.name,
         "workload": "%s: W %dx%d int%d, A %dx%d uint64 residues, L=%d primes of %d bits, D=%d digits, S=%d"
@@ -288,11 +289,11 @@ def measure_workload(pkg, pi, torch, dev, wl, steps: int, warmup: int, oracle_se
         "kernels": {
             "gemm_ms_avg": gemm_avg,
             "gemm_ms_min": min(gemm_ms),
-            "split_ms_avg": split_avg,
-            "split_ms_min": min(split_ms),
+            "split_ms_avg": None if fused else split_avg,
+            "split_ms_min": None if fused else min(split_ms),
             "split_hbm_GBs": split_GBs,
-            "split_frac_of_hbm_peak": split_GBs / HBM_PEAK_GBS,
-            "split_frac_of_copy": (split_GBs / copy_GBs) if copy_GBs else None,
+            "split_frac_of_hbm_peak": None if fused else split_GBs / HBM_PEAK_GBS,
+            "split_frac_of_copy": (split_GBs / copy_GBs) if copy_GBs and not fused else None,
         },
     }
     if oracle_seconds > 0:

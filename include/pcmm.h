@@ -77,7 +77,8 @@ pcmm_status pcmm_plan_create(pcmm_plan **out, int64_t M, int64_t K, int64_t Ncol
 /*
  * Device bytes the plan owns: the converted weights (1 or 2 bytes per entry of W, where the paper's
  * converted PCMM tiles take 8, Section 5.3 and Table "model-conversion-memory"), the digit scratch of
- * one run (digits bytes per residue of A) and the per-limb constants.  0 for NULL.
+ * one run (digits bytes per residue of A; none for K <= 128 and primes below 2^50, which run as one
+ * kernel) and the per-limb constants.  0 for NULL.
  */
 size_t pcmm_plan_workspace_bytes(const pcmm_plan *plan);
 
@@ -108,8 +109,8 @@ pcmm_status pcmm_run(const pcmm_plan *plan, const uint64_t *A_dev, uint64_t *C_d
 
 /*
  * Same operation as pcmm_run (Section 5.1, B = W.A), but brackets each kernel with HIP events on `stream`, synchronises, and
- * reports the kernel durations in milliseconds: ms_out[0] = digit-split kernel, ms_out[1] =
- * MFMA + epilogue kernel (all its launches together when K is cut into ranges).  ms_out is a host array of 2 floats.  For measurement harnesses.
+ * reports the kernel durations in milliseconds: ms_out[0] = digit-split kernel (next to nothing for K <= 128 and primes
+ * below 2^50: the one kernel that runs cuts the digits itself), ms_out[1] = MFMA + epilogue kernel (all its launches together when K is cut into ranges).  ms_out is a host array of 2 floats.  For measurement harnesses.
  */
 pcmm_status pcmm_run_profiled(const pcmm_plan *plan, const uint64_t *A_dev, uint64_t *C_dev,
                               void *stream, float *ms_out);

@@ -9,6 +9,7 @@
 //                                integer of nine digits)
 //   gemm_kernel     (every run)  v_mfma_i32_16x16x64_i8 main loop, then recombination of the digit
 //                                accumulators and reduction modulo q_j
+//   (contractions of at most 128 values of k run as one kernel, pcmm_shortk.hip)
 // Beside it:
 //   transpose_u64_kernel         the coefficient permutation of ring switching (Section 3.3)
 //   mfma_probe_kernel            measurement aid: what the matrix cores sustain without memory traffic
@@ -236,17 +237,11 @@ __global__ __launch_bounds__(256) void split_pair_kernel(const uint64_t *__restr
             y1[r] = (uint32_t)p1;
             y2[r] = (uint32_t)(p1 >> 32) + th * qh;
         }
-        // bytes of four values -> four digits of four values each
-        auto transpose4 = [&](const uint32_t (&y)[4], int d) {
-            const uint32_t t0 = __builtin_amdgcn_perm(y[1], y[0], 0x05010400u), t1 = __builtin_amdgcn_perm(y[1], y[0], 0x07030602u);
-            const uint32_t u0 = __builtin_amdgcn_perm(y[3], y[2], 0x05010400u), u1 = __builtin_amdgcn_perm(y[3], y[2], 0x07030602u);
-            out[d][i] = __builtin_amdgcn_perm(u0, t0, 0x05040100u);
-            out[d + 1][i] = __builtin_amdgcn_perm(u0, t0, 0x07060302u);
-            out[d + 2][i] = __builtin_amdgcn_perm(u1, t1, 0x05040100u);
-            out[d + 3][i] = __builtin_amdgcn_perm(u1, t1, 0x07060302u);
-        };
-        transpose4(y0, 0);
-        transpose4(y1, 4);
+        uint32_t t0[4], t1[4];                      // four digits of four values each
+        transpose_bytes(y0, t0);
+        transpose_bytes(y1, t1);
+#pragma unroll
+        for (int d = 0; d < 4; ++d) { out[d][i] = t0[d]; out[4 + d][i] = t1[d]; }
         out[8][i] = y2[0] | (y2[1] << 8) | (y2[2] << 16) | (y2[3] << 24);
     }
     int8_t *chunk = Ad + ((pair * nkb + kb) * ntiles + ntile) * (D * kFrag);
@@ -711,7 +706,8 @@ struct pcmm_plan {
     int8_t *Ad;              // device digit scratch
     LimbConst *lc;           // device
     size_t bytes;
-    size_t ad_bytes;         // size of the digit scratch one run needs
+    size_t ad_bytes;         // size of the digit planes of one run (pcmm_run_noalloc's limit)
+    bool shortk;             // at most 128 values of k: pcmm_shortk runs, which needs no digit scratch
     int pairs;               // limb pairs whose digits are split jointly; limbs from 2 * pairs on run singly
     int64_t pair_ntiles;     // n-tiles (16 columns) of a pair
     PairConsts pcs;
@@ -866,15 +862,15 @@ pcmm_status run_impl(const pcmm_plan *p, int8_t *Ad, const uint64_t *A, uint64_t
     if (!dg.ok) return PCMM_EDEVICE;
 
     if (ms && hipEventRecord(p->ev[0], st) != hipSuccess) return PCMM_EDEVICE;
-    if (launch_split(p, Ad, A, st) != hipSuccess) return PCMM_EDEVICE;
+    if (!p->shortk && launch_split(p, Ad, A, st) != hipSuccess) return PCMM_EDEVICE;
     if (ms && (hipEventRecord(p->ev[1], st) != hipSuccess || hipEventRecord(p->ev[2], st) != hipSuccess))
         return PCMM_EDEVICE;
-    if (pcmm_shortk::covers(p->D, p->S, p->epi, p->nkb)) {
-        // at most 128 values of k: the kernel that keeps the digit fragments in registers and walks down W
+    if (p->shortk) {
+        // at most 128 values of k: the kernel that cuts the digits itself, keeps them in registers and walks down W
         pcmm_shortk::Args sa;
-        sa.Wp = p->Wp; sa.Ad = Ad; sa.C = C; sa.lc = p->lc;
-        sa.M = p->M; sa.Ncols = p->Ncols; sa.MB = p->MB;
-        sa.ntiles = (int)p->ntiles; sa.L = p->L;
+        sa.Wp = p->Wp; sa.A = A; sa.C = C; sa.lc = p->lc;
+        sa.M = p->M; sa.K = p->K; sa.Ncols = p->Ncols; sa.MB = p->MB;
+        sa.L = p->L;
         if (pcmm_shortk::launch(sa, p->D, p->S, p->epi, st) != hipSuccess) return PCMM_EDEVICE;
     } else {
         GemmArgs ga = {};
@@ -943,6 +939,7 @@ pcmm_status pcmm_plan_create(pcmm_plan **out, int64_t M, int64_t K, int64_t Ncol
     p->D = D; p->S = S;
     p->WM = g.WM; p->MT = g.MT; p->NT = g.NT;
     p->epi = g.epi;
+    p->shortk = pcmm_shortk::covers(g.D, g.S, g.epi, g.nkb);
     p->MB = g.MB; p->nkb = g.nkb; p->mtiles = g.mtiles; p->ntiles = g.ntiles;
     p->nkb_launch = g.nkb_launch;
     p->pairs = g.pairs;
@@ -956,17 +953,18 @@ pcmm_status pcmm_plan_create(pcmm_plan **out, int64_t M, int64_t K, int64_t Ncol
     // set-up for pcmm_run_noalloc: this device's address of the static digit scratch, asked for once
     if (!static_scratch_ptr(device)) { delete p; return PCMM_EDEVICE; }
 
-    const size_t wp_bytes = g.wp_bytes, ad_bytes = g.ad_bytes;
+    const size_t wp_bytes = g.wp_bytes, ad_bytes = p->shortk ? 0 : g.ad_bytes;   // scratch the plan owns
     const size_t lc_bytes = (size_t)L * sizeof(LimbConst);
     int *err_dev = nullptr;
     pcmm_status rc = PCMM_OK;
-    if (hipMalloc((void **)&p->Wp, wp_bytes) != hipSuccess || hipMalloc((void **)&p->Ad, ad_bytes) != hipSuccess ||
+    if (hipMalloc((void **)&p->Wp, wp_bytes) != hipSuccess ||
+        (ad_bytes && hipMalloc((void **)&p->Ad, ad_bytes) != hipSuccess) ||
         hipMalloc((void **)&p->lc, lc_bytes) != hipSuccess || hipMalloc((void **)&err_dev, sizeof(int)) != hipSuccess) {
         (void)hipGetLastError();
         rc = PCMM_ENOMEM;
     }
     p->bytes = wp_bytes + ad_bytes + lc_bytes;
-    p->ad_bytes = ad_bytes;
+    p->ad_bytes = g.ad_bytes;
 
     if (rc == PCMM_OK) {
         LimbConst h[pcmm_host::kMaxLimbs];

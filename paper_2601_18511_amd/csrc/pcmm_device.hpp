@@ -54,6 +54,45 @@ __device__ __forceinline__ void static_for(F &&f)
     static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
+// bytes of four words -> four words, word d of the result holding byte d of each
+__device__ __forceinline__ void transpose_bytes(const uint32_t (&y)[4], uint32_t (&t)[4])
+{
+    const uint32_t a0 = __builtin_amdgcn_perm(y[1], y[0], 0x05010400u), a1 = __builtin_amdgcn_perm(y[1], y[0], 0x07030602u);
+    const uint32_t b0 = __builtin_amdgcn_perm(y[3], y[2], 0x05010400u), b1 = __builtin_amdgcn_perm(y[3], y[2], 0x07030602u);
+    t[0] = __builtin_amdgcn_perm(b0, a0, 0x05040100u);
+    t[1] = __builtin_amdgcn_perm(b0, a0, 0x07060302u);
+    t[2] = __builtin_amdgcn_perm(b1, a1, 0x05040100u);
+    t[3] = __builtin_amdgcn_perm(b1, a1, 0x07060302u);
+}
+
+// Balanced base-256 digits of sixteen residues: byte j of out[d] (as sixteen int8) is digit d of x[j].
+// With Bias = sum_{i<D} 128 * 256^i, the bytes of x + Bias, each xor 0x80, read as int8, are digits s_i in [-128,127]
+// with x = sum_i s_i 256^i (valid while x + Bias < 256^D).
+template <int D>
+__device__ __forceinline__ void digits16(const uint64_t (&x)[16], v4i (&out)[D])
+{
+    static_assert(D >= 4 && D <= 8, "four to eight digits");
+    constexpr uint64_t bias = 0x8080808080808080ull >> (8 * (8 - D));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        uint32_t lo[4], hi[4], t[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const uint64_t y = x[4 * i + r] + bias;
+            lo[r] = (uint32_t)y;
+            hi[r] = (uint32_t)(y >> 32);
+        }
+        transpose_bytes(lo, t);
+#pragma unroll
+        for (int d = 0; d < 4; ++d) out[d][i] = (int)(t[d] ^ 0x80808080u);
+        if constexpr (D > 4) {
+            transpose_bytes(hi, t);
+#pragma unroll
+            for (int d = 4; d < D; ++d) out[d][i] = (int)(t[d - 4] ^ 0x80808080u);
+        }
+    }
+}
+
 // Rounding to the nearest integer without the (slower) rounding instruction: for |x| < 2^51 the sum
 // x + 1.5 * 2^52 has unit spacing, so its rounding is the rounding of x to an integer (ties to even), and
 // subtracting the constant again is exact.  round_fma(h, s) rounds the exact product h s once.

@@ -5,8 +5,11 @@
 // the vector-ALU work of the modular reduction, not by the matrix cores.
 //
 // Design.  A work-group of four waves owns a strip of 64 columns of one limb; wave w owns columns
-// 16w .. 16w+15 and keeps their digit fragments (both k-steps, all D digits: 2 D operand registers of
-// 16 bytes) in registers for the whole kernel: the digit planes are read from memory exactly once.
+// 16w .. 16w+15, reads their residues, cuts them into digits and keeps the digit fragments (both k-steps, all D
+// digits: 2 D operand registers of 16 bytes) in registers for the whole kernel.  No digit plane goes through memory
+// and no split kernel runs before this one (with one: 128 x 128 by 128 x 8192, two 36-bit limbs 17.5 us against 8.4;
+// 300 x 100 by 100 x 131072, six 50-bit limbs 756 us against 511; 4096 x 128 by 128 x 131072, six limbs 6.27 ms
+// against 6.12).
 // The work-group then walks down the rows of W.  W is shared by the four waves, so it is staged through
 // LDS, four 16-row blocks at a time, double-buffered: the global loads of stage s+2 are issued before
 // the results of stage s+1 are stored.  Per 16 x 16 output block a wave issues 2 D S MFMAs into
@@ -42,11 +45,16 @@ struct KArgs {
 };
 
 // MODE: the grouping reduce_f64 uses (0: groups of three accumulators; 2: groups of four, pairs joined in int32)
-template <int D, int S, int MODE>
-__global__ __launch_bounds__(256, 3) void gemm_shortk_kernel(KArgs ka)
+// ONCE: one work-group covers all rows of its strip, so every residue is read once: non-temporal loads (64 rows,
+//       131072 columns, four limbs 152 -> 145 us).  With several parts the later ones find the residues in the caches;
+//       non-temporal loads would keep them out (4096 x 128 by 128 x 8192: 74 -> 121 us).
+// LINES: every row of C starts on a 128-byte line, the stores write whole lines and are non-temporal.  Otherwise the
+//       lines that two waves or work-groups share are joined in L2, which non-temporal stores prevent (3001 x 128 by
+//       128 x 65001, two limbs: 1.99 ms non-temporal, 1.13 ms cached).
+template <int D, int S, int MODE, bool ONCE, bool LINES>
+__global__ __launch_bounds__(256, D == 7 && S == 2 ? 3 : 4) void gemm_shortk_kernel(KArgs ka)
 {
     constexpr int E = D + S - 1;
-    constexpr int CH = 2 * D * kFrag;             // one 32-column digit chunk of one k-step
     constexpr int NF = RS * S * 2;                // W fragments per stage: [row block][slice][k-step]
     constexpr int STAGE = NF * kFrag;
     constexpr int NLD = NF / 4;                   // fragments each wave moves per stage (one 16-byte unit per lane)
@@ -56,37 +64,60 @@ __global__ __launch_bounds__(256, 3) void gemm_shortk_kernel(KArgs ka)
     __shared__ __attribute__((aligned(16))) int8_t lds[2][STAGE];
 
     // which strip: work-groups are dealt round-robin to the 8 XCDs; each XCD walks its own contiguous
-    // range, parts of one strip next to each other (they read the same digit fragments)
+    // range, strips fastest, so that the work-groups resident together store to the same rows side by side (against
+    // the parts of a strip next to each other: 8192 x 64 by 64 x 8192 132 -> 101 us; 777 x 96 by 96 x 20001, four
+    // limbs 202 -> 183 us; equal where a strip has one part)
     const int64_t bid = blockIdx.x;
     const int64_t t = (bid % kXcd) * ka.per_xcd + bid / kXcd;
     if (bid / kXcd >= ka.per_xcd || t >= ka.total) return;
-    const int mpart = (int)(t % ka.mparts);
-    const int strip = (int)((t / ka.mparts) % ka.nstrips);
+    const int strip = (int)(t % ka.nstrips);
+    const int mpart = (int)((t / ka.nstrips) % ka.mparts);
     const int limb = (int)(t / ((int64_t)ka.mparts * ka.nstrips));
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t loff = (uint32_t)lane * 16u;
 
-    // ---- this wave's digit fragments: column block nb of the limb, both k-steps, all digits
+    // ---- this wave's digit fragments, cut from the residues of its 16 columns: lane l holds column l % 16 and, of each
+    // k-step, the values 16 (l / 16) .. 16 (l / 16) + 15 of k.  All sixteen loads of a k-step are in flight before the
+    // first use; rows and columns beyond the matrix load its last one instead and count as zero.
     const int nb = strip * 4 + wave;
-    const bool active = (int64_t)nb * 16 < a.Ncols;        // wave-uniform
+    const int64_t n = (int64_t)nb * 16 + (lane & 15);
     v4i b[2][D];
     {
-        const int ntile = nb >> 1, nt = nb & 1;
-        const int8_t *base = a.Ad + (int64_t)limb * 2 * a.ntiles * CH;
-        const uint32_t ad_limb_bytes = (uint32_t)((int64_t)2 * a.ntiles * CH);
-        const __amdgpu_buffer_rsrc_t ars =
-            __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t *>(base), 0, ad_limb_bytes, 0x00020000);
+        const uint64_t *src = a.A + (int64_t)limb * a.K * a.Ncols + min(n, a.Ncols - 1);
+        const int k0 = (lane >> 4) * 16, klast = (int)a.K - 1;
+        uint64_t x[2][16];
+        auto load = [&](int kb) {
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-            for (int d = 0; d < D; ++d) {
-                // a column block beyond the limb's digit planes reads out of range: zeros
-                const uint32_t off = active ? (uint32_t)(kb * a.ntiles + ntile) * (uint32_t)CH + (uint32_t)((nt * D + d) * kFrag)
-                                            : ad_limb_bytes;
-                b[kb][d] = (v4i)__builtin_amdgcn_raw_buffer_load_b128(ars, loff, (int)off, 0);
+            for (int j = 0; j < 16; ++j) {
+                const uint64_t *word = &src[(int64_t)min(kb * 64 + k0 + j, klast) * a.Ncols];
+                x[kb][j] = ONCE ? __builtin_nontemporal_load(word) : *word;
             }
+        };
+        auto cut = [&](int kb) {
+#pragma unroll
+            for (int j = 0; j < 16; ++j)
+                if (kb * 64 + k0 + j > klast || n >= a.Ncols) x[kb][j] = 0;
+            digits16<D>(x[kb], b[kb]);
+        };
+        load(0);
+        if constexpr (D < 6) load(1);
+        cut(0);
+        if constexpr (D >= 6) {              // both at once would not fit the 128 registers
+            __builtin_amdgcn_sched_barrier(0);
+            load(1);
+        }
+        cut(1);
+        // The digits are final values here: without this the compiler carries parts of their making into the loop and
+        // needs 132 registers for seven digits of two slices instead of 124 (three waves on a SIMD instead of four).
+        if constexpr (MODE == 2) {
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int d = 0; d < D; ++d) asm volatile("" : "+v"(b[kb][d]));
+        }
+        __builtin_amdgcn_sched_barrier(0);   // the loads of W below stay below
     }
 
     // ---- W stages.  Fragment f = wave + 4 i of a stage is (row block f / (2S), slice (f / 2) % S, k-step f % 2)
@@ -95,6 +126,7 @@ __global__ __launch_bounds__(256, 3) void gemm_shortk_kernel(KArgs ka)
     const __amdgpu_buffer_rsrc_t wrs =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t *>(a.Wp), 0, wp_bytes, 0x00020000);
     const int mb_first = mpart * ka.stages_per_part * RS;
+    const int mb_last = (int)a.MB - 1;
     v4i wst[NLD];
     auto stage_load = [&](int s) {           // stage s of this part: global -> registers
         const int mb0 = mb_first + s * RS;
@@ -102,9 +134,8 @@ __global__ __launch_bounds__(256, 3) void gemm_shortk_kernel(KArgs ka)
         for (int i = 0; i < NLD; ++i) {
             const int f = wave + 4 * i;
             const int r = f / (2 * S), sl = (f / 2) % S, kb = f % 2;
-            const int mb = mb0 + r;
-            // row blocks beyond the packed matrix read out of range: zeros
-            const uint32_t off = mb < a.MB ? (uint32_t)((sl * 2 + kb) * (int)a.MB + mb) * (uint32_t)kFrag : wp_bytes;
+            const int mb = min(mb0 + r, mb_last);   // blocks beyond the packed matrix are not stored: any data will do
+            const uint32_t off = (uint32_t)((sl * 2 + kb) * (int)a.MB + mb) * (uint32_t)kFrag;
             wst[i] = (v4i)__builtin_amdgcn_raw_buffer_load_b128(wrs, loff, (int)off, 0);
         }
     };
@@ -127,7 +158,6 @@ __global__ __launch_bounds__(256, 3) void gemm_shortk_kernel(KArgs ka)
 
     uint64_t *Cl = a.C + (int64_t)limb * a.M * a.Ncols;
     const uint32_t c_rowbytes = (uint32_t)a.Ncols * 8u;
-    const int64_t n = (int64_t)nb * 16 + (lane & 15);
     // lanes whose column lies beyond Ncols get an offset that is out of range for every row
     const uint32_t c_lane = n < a.Ncols ? (uint32_t)((lane >> 4) * 4) * c_rowbytes + (uint32_t)n * 8u : 0x80000000u;
 
@@ -168,9 +198,8 @@ __global__ __launch_bounds__(256, 3) void gemm_shortk_kernel(KArgs ka)
         reduce_f64<E, MODE, 4>(avs, lc.qd, lc.invq, res);
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-            // non-temporal: the output is written once and not read back by this kernel
             __builtin_amdgcn_raw_buffer_store_b64((v2u){(uint32_t)res[r], (uint32_t)(res[r] >> 32)}, crs,
-                                                  c_lane + (uint32_t)r * c_rowbytes, 0, 2);
+                                                  c_lane + (uint32_t)r * c_rowbytes, 0, LINES ? 2 : 0);
     };
 
     // ---- stage s is in LDS[s & 1] while stage s+1 travels global -> registers
@@ -196,15 +225,24 @@ __global__ __launch_bounds__(256, 3) void gemm_shortk_kernel(KArgs ka)
     }
 }
 
+template <int D, int S, int MODE>
+void launch_mode(const KArgs &ka, int64_t grid, hipStream_t st)
+{
+    const dim3 g((unsigned)grid), b(256);
+    const bool once = ka.mparts == 1, lines = ka.a.Ncols % 16 == 0;
+    const auto kern = once ? (lines ? gemm_shortk_kernel<D, S, MODE, true, true> : gemm_shortk_kernel<D, S, MODE, true, false>)
+                           : (lines ? gemm_shortk_kernel<D, S, MODE, false, true> : gemm_shortk_kernel<D, S, MODE, false, false>);
+    hipLaunchKernelGGL(kern, g, b, 0, st, ka);
+}
+
 template <int D, int S>
 hipError_t launch_ds(const KArgs &ka, int epi, int64_t grid, hipStream_t st)
 {
     constexpr int E = D + S - 1;
-    const dim3 g((unsigned)grid), b(256);
     if (epi == EPI_F64) {
-        hipLaunchKernelGGL((gemm_shortk_kernel<D, S, 0>), g, b, 0, st, ka);
+        launch_mode<D, S, 0>(ka, grid, st);
     } else if (epi == EPI_F64_G4P) {
-        if constexpr (E >= 7) hipLaunchKernelGGL((gemm_shortk_kernel<D, S, 2>), g, b, 0, st, ka);
+        if constexpr (E >= 7) launch_mode<D, S, 2>(ka, grid, st);
         else return hipErrorInvalidValue;
     } else {
         return hipErrorInvalidValue;
@@ -226,12 +264,16 @@ hipError_t launch(const Args &a, int D, int S, int epi, hipStream_t st)
     if (!covers(D, S, epi, 2)) return hipErrorInvalidValue;
     KArgs ka;
     ka.a = a;
-    ka.nstrips = (a.ntiles + 1) / 2;
+    ka.nstrips = (int)((a.Ncols + 63) / 64);
     const int64_t stages = ((a.M + 15) / 16 + RS - 1) / RS;        // stages that hold a row of W
-    // enough work-groups to balance 512 resident ones, as few as possible otherwise (a work-group reads
-    // its digit fragments once, whatever number of rows it then covers)
+    // Enough work-groups to balance the 1024 resident ones, as few as possible otherwise: every part of a strip reads
+    // and cuts the strip's residues again.  Up to 512 strips, where that repeats most, 1536 work-groups, else 3072.
+    // Measured with 1536 / 3072 / 6144: 128 strips (4096 x 128 by 128 x 8192) 56 / 69 / 82 us; 256 strips (1024 x 128
+    // by 128 x 8192, two limbs) 36 / 41 / 60 us; 626 strips (4096 x 128 by 128 x 20000, two limbs) 273 / 261 / 277 us;
+    // 2048 strips (1000 x 80 by 80 x 65536, two limbs) 249 / 210 / 223 us.
     const int64_t strips = (int64_t)a.L * ka.nstrips;
-    int64_t mparts = std::min<int64_t>(stages, std::max<int64_t>(1, (8192 + strips - 1) / strips));
+    const int64_t target = strips <= 512 ? 1536 : 3072;
+    const int64_t mparts = std::min<int64_t>(stages, std::max<int64_t>(1, (target + strips - 1) / strips));
     ka.stages_per_part = (int)((stages + mparts - 1) / mparts);
     ka.mparts = (int)((stages + ka.stages_per_part - 1) / ka.stages_per_part);
     ka.total = strips * ka.mparts;

@@ -11,16 +11,15 @@
 
 namespace pcmm_shortk {
 
-// What one launch needs.  Wp and Ad are the plan's packed weights and one run's digit planes, in the
-// layouts pack_w_kernel and split_kernel write (two k-steps of 64).
+// What one launch needs.  Wp is the plan's packed weights in the layout pack_w_kernel writes (two k-steps of 64); the
+// residues are read as they are, their digits never go through memory.
 struct Args {
     const int8_t *Wp;                     // [S][2][MB][64][16]
-    const int8_t *Ad;                     // [L][2][ntiles][2][D][64][16]
+    const uint64_t *A;                    // [L][K][Ncols]
     uint64_t *C;                          // [L][M][Ncols]
     const pcmm_host::LimbConst *lc;       // [L]
-    int64_t M, Ncols;
+    int64_t M, K, Ncols;
     int64_t MB;                           // 16-row blocks in Wp
-    int ntiles;                           // 32-column tiles in Ad
     int L;
 };
 

@@ -177,7 +177,8 @@ def workload_figures(name: str) -> dict:
     import pcmm_inputs as pi
 
     w = pi.WORKLOADS[name]
-    digits_bytes = w.K * w.Ncols * w.L * w.digits
+    fused = w.K <= 128 and w.prime_bits <= 50            # gemm_shortk_kernel reads the residues and cuts the digits itself
+    digits_bytes = w.K * w.Ncols * w.L * (8 if fused else w.digits)
     return {
         "desc": "W %dx%d int%d, A %dx%d uint64 residues, L=%d primes of %d bits, D=%d digits, S=%d slices"
                 % (w.M, w.K, w.w_bits, w.K, w.Ncols, w.L, w.prime_bits, w.digits, w.slices),
@@ -185,14 +186,14 @@ def workload_figures(name: str) -> dict:
         "gemm_bytes": float(digits_bytes + w.M * w.K * w.slices + 8 * w.M * w.Ncols * w.L),
         "gemm_parts": (digits_bytes, w.M * w.K * w.slices, 8 * w.M * w.Ncols * w.L),
         "split_bytes": float(w.K * w.Ncols * w.L * (8 + w.digits)),
-        "mfma_kernel": "gemm_shortk_kernel" if (w.K <= 128 and w.prime_bits <= 50) else "gemm_kernel",
+        "mfma_kernel": "gemm_shortk_kernel" if fused else "gemm_kernel",
     }
 
 
 def trace_summary(workload: str, fig: dict, trace: Dict[str, List[float]], commands: Sequence[str]) -> str:
     mine = pick(trace, r"gemm_kernel|gemm_shortk_kernel|split_kernel|transpose_u64_kernel|mfma_probe_kernel")
     lines = ["rocprofv3 kernel trace of the PCMM kernels on the %s workload" % workload,
-             "(%s; one pcmm_run = 1 split_kernel + 1 MFMA-kernel launch)" % fig["desc"], ""]
+             "(%s; one pcmm_run = the split kernels + the MFMA kernels, or gemm_shortk_kernel alone)" % fig["desc"], ""]
     lines += ["commands (from /tmp with TMPDIR=/tmp on the MI355X box, R = repository root):"] + ["  " + c for c in commands] + [""]
     lines.append("%-46s %6s %12s %12s %12s" % ("kernel", "calls", "avg_ms", "min_ms", "max_ms"))
     for k in mine:
@@ -254,7 +255,7 @@ def traffic_summary(workload: str, fig: dict, counters, commands: Sequence[str],
             traffic = (f * sf + w * sw) * 1024.0
     dp, wp, cp = fig["gemm_parts"]
     lines += ["",
-              "algorithmic bytes per launch: %s %.2f GiB (digit planes %.2f + packed W %.3f + C %.2f), split_kernel %.2f GiB"
+              "algorithmic bytes per launch: %s %.2f GiB (digit planes or residues %.2f + packed W %.3f + C %.2f), split_kernel %.2f GiB"
               % (fig["mfma_kernel"], fig["gemm_bytes"] / GIB, dp / GIB, wp / GIB, cp / GIB, fig["split_bytes"] / GIB),
               "traffic / algorithmic bytes of the MFMA kernel: %.2f" % (traffic / fig["gemm_bytes"]),
               "FETCH_SIZE counts what the L2s request from the fabric: re-reads of W and of digit chunks by different XCDs show up",

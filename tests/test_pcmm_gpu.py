@@ -116,6 +116,45 @@ def test_short_contractions_bit_exact(gpu_device, M, K, Ncols, bits, L, wbits):
     assert (got == want).all(), int((got != want).sum())
 
 
+@pytest.mark.parametrize(
+    "M,K,Ncols,bits,L,wbits",
+    [
+        (1, 1, 1, 36, 1, 8),              # one value: every other row, column and k is padding
+        (64, 65, 31, 50, 2, 16),          # one part (a single stage), ragged columns: cached stores
+        (64, 128, 48, 28, 3, 8),          # one part, whole lines
+        (65, 64, 47, 44, 1, 16),          # two parts, the second k-step all padding
+        (65, 33, 70000, 36, 3, 8),        # more than 3072 strips: one part of two stages
+        (640, 127, 513, 45, 35, 8),  # 315 strips: five parts; a strip of one column
+        (200, 128, 1055, 49, 36, 16),     # 612 strips: four parts of one stage
+        (257, 128, 16 * 33, 48, 1, 16),   # a last part with one row, a strip of 16 columns
+    ],
+)
+def test_digits_cut_inside_the_short_contraction_kernel(gpu_device, M, K, Ncols, bits, L, wbits):
+    """Strips, parts, padding and both kinds of loads and stores; residues with extreme digits; C written nowhere else."""
+    import torch
+
+    import paper_2601_18511_amd as pkg
+    from oracle import pcmm_oracle
+
+    rng = np.random.default_rng(M * 31 + K * 7 + Ncols)
+    primes = pi.ntt_primes(bits, 1 << 10, L)
+    W = _rand_W(rng, M, K, wbits)
+    A = np.stack([_digit_pattern_residues(q, bits, K, Ncols, rng) for q in primes])
+    A[:, K - 1, Ncols - 1] = np.array(primes, dtype=np.uint64) - np.uint64(1)
+    plan = pkg.pcmm_plan_create(torch.from_numpy(W).to(gpu_device), primes, bits, Ncols)
+    guard = torch.full((L * M * Ncols + 512,), -7, dtype=torch.int64, device=gpu_device)
+    C = guard[256:256 + L * M * Ncols].view(L, M, Ncols)
+    A_dev = torch.from_numpy(A.view(np.int64)).to(gpu_device)
+    want = pcmm_oracle(W, A, primes)
+    for _ in range(2):
+        C.fill_(-1)
+        pkg.pcmm_run(plan, A_dev, C)
+        torch.cuda.synchronize()
+        assert (C.cpu().numpy().view(np.uint64) == want).all()
+    assert (guard[:256] == -7).all() and (guard[-256:] == -7).all()
+    pkg.pcmm_plan_destroy(plan)
+
+
 def _digit_pattern_residues(q, bits, K, Ncols, rng):
     """Residues whose balanced base-256 digits sit at the extremes (+127 / -128 / 0 / -1 patterns)."""
     pats = []

@@ -267,7 +267,7 @@ struct GemmArgs {
     int64_t M, Ncols;
     int64_t MB;             // padded M / 16
     int nkb;                // padded K / 64: k-steps in the layouts of Wp and Ad
-    int kb0, nkbc;          // this launch contracts k-steps [kb0, kb0 + nkbc), nkbc even
+    int kb0, nkbc;          // this launch contracts k-steps [kb0, kb0 + nkbc), nkbc >= 2
     int accumulate;         // 0: C = result;  1: C = (C + result) mod q  (later slices of a long K)
     int mtiles, ntiles, L;
     int gn;                 // n-tiles per raster group
@@ -287,7 +287,11 @@ struct GemmArgs {
 // Measured (whole pcmm_run, single limbs -> pairs): 4096 x 4096 by 4096 x 32768, four 36-bit limbs 9.25 -> 8.81 ms;
 // 14336 rows 29.66 -> 28.16 ms; 14336 values of k, three limbs (a pair and a single) 23.80 -> 22.59 ms.
 //
-// nkbc (k-steps of one launch) must be even.
+// Work done for padding: a contraction of an odd number of k-steps ends in a three-step tail instead of taking a
+// k-step of zeros along, and a wave whose rows all lie beyond M only moves its share of the digit chunks.
+// Measured (pcmm_run, before -> after): 1000 x 777 by 777 x 12300, three 45-bit limbs 333 -> 319 us; 2100 x 160 by
+// 160 x 16384, four 36-bit limbs 377 -> 334 us; 300 x 4160 by 4160 x 16384, two limbs 553 -> 526 us; 3000 x 320 by
+// 320 x 16384, int16 W, two 55-bit limbs 729 -> 687 us; whole tiles and even counts equal (4096 x 4096: 8.69 and 8.70 ms).
 template <int WM, int MT, int NT, int D, int S, int EPI>
 __global__ __launch_bounds__(WM * 64) void gemm_kernel(GemmArgs a)
 {
@@ -372,6 +376,21 @@ __global__ __launch_bounds__(WM * 64) void gemm_kernel(GemmArgs a)
         else if constexpr (TAIL == 8) *reinterpret_cast<v2u *>(&lds[buf][toff]) = x.tail;
         else *reinterpret_cast<uint32_t *>(&lds[buf][toff]) = x.tail[0];
     };
+
+    // A wave whose rows all lie in the padding of the last m-tile: the same copies and barriers as below, no products.
+    if (mb0 * 16 >= a.M) {
+        Staged x, y;
+        static_for<NLD>([&](auto ic) { ld_a(x, ic, 0); });
+        static_for<NLD>([&](auto ic) { ld_a(y, ic, 1); });
+        static_for<NLD>([&](auto ic) { st_a(x, ic, 0); });
+        __syncthreads();
+        for (int kb = 0; kb < nkb - 1; ++kb) {
+            static_for<NLD>([&](auto ic) { st_a(y, ic, (kb + 1) & 1); });
+            if (kb + 2 < nkb) static_for<NLD>([&](auto ic) { ld_a(y, ic, kb + 2); });
+            __syncthreads();
+        }
+        return;
+    }
 
     // accumulator (i, j, e) = registers a[4*((i*NT + j)*E + e) ...+4)
     constexpr int NACC = 4 * MT * NT * E;
@@ -469,12 +488,20 @@ __global__ __launch_bounds__(WM * 64) void gemm_kernel(GemmArgs a)
         using P0 = std::integral_constant<int, 0>;
         using P1 = std::integral_constant<int, 1>;
         int kb = 0;
-        for (; kb < nkb - 2; kb += 2) {   // nkb is even
+        for (; kb + 3 < nkb; kb += 2) {
             step(P0{}, std::true_type{}, std::true_type{}, kb);
             step(P1{}, std::true_type{}, std::true_type{}, kb + 1);
         }
-        step(P0{}, std::true_type{}, std::false_type{}, kb);
-        step(P1{}, std::false_type{}, std::false_type{}, kb + 1);
+        bool odd = false;                 // three k-steps are left, else two
+        if constexpr (pcmm_host::odd_ksteps(S, MT)) odd = nkb & 1;
+        if (odd) {
+            step(P0{}, std::true_type{}, std::true_type{}, kb);
+            step(P1{}, std::true_type{}, std::false_type{}, kb + 1);
+            step(P0{}, std::false_type{}, std::false_type{}, kb + 2);
+        } else {
+            step(P0{}, std::true_type{}, std::false_type{}, kb);
+            step(P1{}, std::false_type{}, std::false_type{}, kb + 1);
+        }
     }
 
     // volatile asm statements keep their order: last MFMA, drain, accumulator reads
@@ -702,6 +729,7 @@ struct pcmm_plan {
     int epi;                 // Epi: how the epilogue reduces
     int64_t MB, nkb, mtiles, ntiles;
     int64_t nkb_launch;      // most k-steps one GEMM launch may contract (int32 accumulator headroom)
+    int64_t ksteps;          // k-steps that are split and contracted (the layouts hold nkb)
     int8_t *Wp;              // device
     int8_t *Ad;              // device digit scratch
     LimbConst *lc;           // device
@@ -806,7 +834,7 @@ hipError_t launch_split(const pcmm_plan *p, int8_t *Ad, const uint64_t *A, hipSt
 {
     const dim3 block(256);
     if (p->pairs) {
-        const dim3 grid((unsigned)((p->pair_ntiles * 16 + 63) / 64), (unsigned)p->nkb, (unsigned)p->pairs);
+        const dim3 grid((unsigned)((p->pair_ntiles * 16 + 63) / 64), (unsigned)p->ksteps, (unsigned)p->pairs);
         hipLaunchKernelGGL(split_pair_kernel, grid, block, 0, st, A, Ad, p->K, p->Ncols, p->nkb, p->pair_ntiles, p->pcs);
         const hipError_t rc = hipGetLastError();
         if (rc != hipSuccess) return rc;
@@ -816,7 +844,7 @@ hipError_t launch_split(const pcmm_plan *p, int8_t *Ad, const uint64_t *A, hipSt
     A += (int64_t)2 * p->pairs * p->K * p->Ncols;
     Ad += pair_digit_bytes(p);
     int64_t colblocks = (p->ntiles * p->NT * 16 + 63) / 64;
-    dim3 grid((unsigned)colblocks, (unsigned)p->nkb, (unsigned)single);
+    dim3 grid((unsigned)colblocks, (unsigned)p->ksteps, (unsigned)single);
 #define PCMM_SPLIT_CASE(DD)                                                                              \
     case DD:                                                                                             \
         hipLaunchKernelGGL((split_kernel<DD>), grid, block, 0, st, A, Ad, p->K, p->Ncols, p->nkb,     \
@@ -887,9 +915,9 @@ pcmm_status run_impl(const pcmm_plan *p, int8_t *Ad, const uint64_t *A, uint64_t
         ga.gn = 8;
         // A contraction longer than the int32 accumulators can hold runs as several launches over
         // consecutive ranges of k; every launch after the first adds its result to C modulo q_j.
-        for (int64_t kb0 = 0; kb0 < p->nkb; kb0 += p->nkb_launch) {
+        for (int64_t kb0 = 0; kb0 < p->ksteps; kb0 += p->nkb_launch) {
             ga.kb0 = (int)kb0;
-            ga.nkbc = (int)std::min(p->nkb_launch, p->nkb - kb0);
+            ga.nkbc = (int)std::min(p->nkb_launch, p->ksteps - kb0);
             ga.accumulate = kb0 > 0;
             for (bool pair : {true, false})
                 if (launch_products(p, ga, pair, st) != hipSuccess) return PCMM_EDEVICE;
@@ -942,6 +970,7 @@ pcmm_status pcmm_plan_create(pcmm_plan **out, int64_t M, int64_t K, int64_t Ncol
     p->shortk = pcmm_shortk::covers(g.D, g.S, g.epi, g.nkb);
     p->MB = g.MB; p->nkb = g.nkb; p->mtiles = g.mtiles; p->ntiles = g.ntiles;
     p->nkb_launch = g.nkb_launch;
+    p->ksteps = g.ksteps;
     p->pairs = g.pairs;
     p->pair_ntiles = g.pair_ntiles;
     for (int j = 0; j < g.pairs; ++j) p->pcs.c[j] = pcmm_host::pair_const(primes_host[2 * j], primes_host[2 * j + 1]);

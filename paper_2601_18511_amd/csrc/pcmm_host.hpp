@@ -129,14 +129,20 @@ inline int balanced_digits(uint64_t qmax)
 // Accumulator footprint limits the tile: MT*NT*E*4 accumulator registers per lane (NT = 2), at most 160.
 constexpr int tile_mt(int E) { return E <= 5 ? 4 : (E == 6 ? 3 : 2); }
 
+// Whether the GEMM kernel contracts odd numbers of k-steps.  With eight W fragments per k-step (four digits, two slices)
+// its third tail step takes the kernel from under 256 registers to 284, and only one work-group fits a compute unit.
+constexpr bool odd_ksteps(int S, int MT) { return S * MT < 8; }
+
 // Everything about a plan that follows from its arguments alone.
 struct Geometry {
     int D, S, E;               // digits per residue, int8 slices of W, accumulators per output
     int WM, MT, NT;            // waves per work-group, 16-row fragments per wave, 16-column fragments per tile
     int epi;                   // epi::Epi
     int64_t MB;                // padded M / 16
-    int64_t nkb;               // padded K / 64 (even)
+    int64_t nkb;               // padded K / 64 (even): the k-steps of the layouts
     int64_t nkb_launch;        // most k-steps one GEMM launch may contract (int32 accumulator headroom)
+    int64_t ksteps;            // k-steps that are split and contracted: ceil(K / 64), and one of padding where a launch
+                               // would otherwise be left with a single k-step or odd_ksteps() says so
     int64_t mtiles, ntiles;
     size_t wp_bytes, ad_bytes, lc_bytes;
     int pairs;                 // limb pairs split jointly (0 or L / 2)
@@ -186,6 +192,8 @@ inline pcmm_status plan_geometry(int64_t M, int64_t K, int64_t Ncols, int32_t L,
     g->MB = g->mtiles * BM / 16;
     g->nkb = (K + 127) / 128 * 2;   // the main loop takes two k-steps of 64 per round
     g->nkb_launch = nkb_launch;
+    const int64_t ks = (K + 63) / 64;
+    g->ksteps = !odd_ksteps(S, g->MT) ? g->nkb : (ks - 1) % nkb_launch == 0 ? ks + 1 : ks;   // at most nkb: nkb_launch is even
     if ((int64_t)L * g->mtiles * g->ntiles > 0x7fffff00LL) return PCMM_EUNSUPPORTED;   // the grid is a 32-bit count
 
     g->epi = qmax < ((uint64_t)1 << 50) ? epi::EPI_F64 : epi::EPI_INT;

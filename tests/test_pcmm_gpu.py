@@ -155,6 +155,31 @@ def test_digits_cut_inside_the_short_contraction_kernel(gpu_device, M, K, Ncols,
     pkg.pcmm_plan_destroy(plan)
 
 
+@pytest.mark.parametrize(
+    "M,K,Ncols,bits,L,wbits",
+    [
+        (257, 129, 40, 36, 3, 8),         # three k-steps (no main loop); a pair and a single limb; three of four waves all padding
+        (320, 320, 33, 45, 2, 8),         # five k-steps; 192-row tiles, the last with one busy wave of 48 rows
+        (129, 192, 64, 50, 1, 16),        # three whole k-steps, 128-row tiles, one row in the last
+        (65, 193, 100, 62, 1, 16),        # four k-steps, the last with one value of k
+        (100, 577, 31, 30, 2, 8),         # two-wave work-groups, ten k-steps
+        (1, 449, 17, 36, 2, 8),           # one row: the second wave of the only tile is all padding; eight k-steps
+        (200, 64, 70, 55, 2, 8),          # one k-step of data under primes the short kernel does not take
+        (300, 150, 50, 30, 2, 16),        # four digits of two slices: always an even count
+        (513, 130944 + 64, 16, 36, 2, 8), # the second launch would be left with one k-step
+    ],
+)
+def test_odd_counts_of_ksteps_and_waves_of_padding(gpu_device, M, K, Ncols, bits, L, wbits):
+    from oracle import pcmm_oracle
+
+    rng = np.random.default_rng(M + K * 3 + Ncols)
+    primes = pi.ntt_primes(bits, 1 << 10, L)
+    W = _rand_W(rng, M, K, wbits)
+    A = np.stack([_digit_pattern_residues(q, bits, K, Ncols, rng) for q in primes])
+    got, _ = _run_gpu(W, A, primes, bits, gpu_device)
+    assert (got == pcmm_oracle(W, A, primes)).all()
+
+
 def _digit_pattern_residues(q, bits, K, Ncols, rng):
     """Residues whose balanced base-256 digits sit at the extremes (+127 / -128 / 0 / -1 patterns)."""
     pats = []

@@ -287,8 +287,11 @@ struct GemmArgs {
 // Measured (whole pcmm_run, single limbs -> pairs): 4096 x 4096 by 4096 x 32768, four 36-bit limbs 9.25 -> 8.81 ms;
 // 14336 rows 29.66 -> 28.16 ms; 14336 values of k, three limbs (a pair and a single) 23.80 -> 22.59 ms.
 //
-// Work done for padding: a contraction of an odd number of k-steps ends in a three-step tail instead of taking a
-// k-step of zeros along, and a wave whose rows all lie beyond M only moves its share of the digit chunks.
+// Work done for padding: a contraction of an odd number of k-steps runs its first k-step in the second phase of the pipeline
+// instead of taking a k-step of zeros along, and a wave whose rows all lie beyond M only moves its share of the digit chunks.
+// (A three-step tail of its own for odd counts took 20 to 40 registers more and the two-wave kernels past 256, one wave on
+// a SIMD instead of two: 128 x 4096 by 4096 x 16384, two 38-bit limbs 444 us without, 459 with, 442 this way; 64 x 1024 by
+// 1024 x 16384, int16 W, two 62-bit limbs 158, 162 and 159 us.)
 // Measured (pcmm_run, before -> after): 1000 x 777 by 777 x 12300, three 45-bit limbs 333 -> 319 us; 2100 x 160 by
 // 160 x 16384, four 36-bit limbs 377 -> 334 us; 300 x 4160 by 4160 x 16384, two limbs 553 -> 526 us; 3000 x 320 by
 // 320 x 16384, int16 W, two 55-bit limbs 729 -> 687 us; whole tiles and even counts equal (4096 x 4096: 8.69 and 8.70 ms).
@@ -377,15 +380,20 @@ __global__ __launch_bounds__(WM * 64) void gemm_kernel(GemmArgs a)
         else *reinterpret_cast<uint32_t *>(&lds[buf][toff]) = x.tail[0];
     };
 
+    // 1: an odd number of k-steps, the two-phase pipeline below is entered in phase 1 (k-step kb in phase (kb + odd) & 1,
+    // its digit chunk in that LDS buffer)
+    int odd = 0;
+    if constexpr (pcmm_host::odd_ksteps(S, MT)) odd = nkb & 1;
+
     // A wave whose rows all lie in the padding of the last m-tile: the same copies and barriers as below, no products.
     if (mb0 * 16 >= a.M) {
         Staged x, y;
         static_for<NLD>([&](auto ic) { ld_a(x, ic, 0); });
         static_for<NLD>([&](auto ic) { ld_a(y, ic, 1); });
-        static_for<NLD>([&](auto ic) { st_a(x, ic, 0); });
+        static_for<NLD>([&](auto ic) { st_a(x, ic, odd); });
         __syncthreads();
         for (int kb = 0; kb < nkb - 1; ++kb) {
-            static_for<NLD>([&](auto ic) { st_a(y, ic, (kb + 1) & 1); });
+            static_for<NLD>([&](auto ic) { st_a(y, ic, (kb + 1 + odd) & 1); });
             if (kb + 2 < nkb) static_for<NLD>([&](auto ic) { ld_a(y, ic, kb + 2); });
             __syncthreads();
         }
@@ -400,7 +408,7 @@ __global__ __launch_bounds__(WM * 64) void gemm_kernel(GemmArgs a)
 
     // Software pipeline, one k-step = 64 k, LDS double-buffered, one barrier per k-step:
     //   W fragments   global -> wreg[2], loaded one k-step ahead of use
-    //   digit chunk   global -> areg (second half of k-step kb-1) -> LDS[(kb+1)&1] (first half of kb)
+    //   digit chunk   global -> areg (second half of k-step kb-1) -> LDS[(kb+1+odd)&1] (first half of kb)
     //   digit operand LDS -> b, read at the start of each 16-column half
     // The kernel is sized to at most 256 registers per lane so that two work-groups share a CU:
     // the second wave on each SIMD issues MFMAs while the first waits on LDS, memory or the barrier.
@@ -432,13 +440,16 @@ __global__ __launch_bounds__(WM * 64) void gemm_kernel(GemmArgs a)
         Staged first;
         static_for<NLD>([&](auto ic) { ld_a(first, ic, 0); });
 #pragma unroll
-        for (int f = 0; f < NW; ++f) wreg[0][f / MT][f % MT] = ld_w(f / MT, f % MT, 0);
+        for (int f = 0; f < NW; ++f) {
+            if (odd) wreg[1][f / MT][f % MT] = ld_w(f / MT, f % MT, 0);
+            else wreg[0][f / MT][f % MT] = ld_w(f / MT, f % MT, 0);
+        }
         static_for<NLD>([&](auto ic) { ld_a(areg, ic, 1); });
 #pragma unroll
         for (int i = 0; i < LP * LCW; ++i) w[i] = __builtin_amdgcn_readfirstlane(w[i]);
         __builtin_memcpy(&lc, w, sizeof(lc));
         __builtin_memcpy(&lc2, w + (LP - 1) * LCW, sizeof(lc2));
-        static_for<NLD>([&](auto ic) { st_a(first, ic, 0); });
+        static_for<NLD>([&](auto ic) { st_a(first, ic, odd); });
     }
     __syncthreads();
 
@@ -487,21 +498,14 @@ __global__ __launch_bounds__(WM * 64) void gemm_kernel(GemmArgs a)
     {
         using P0 = std::integral_constant<int, 0>;
         using P1 = std::integral_constant<int, 1>;
-        int kb = 0;
-        for (; kb + 3 < nkb; kb += 2) {
+        int kb = odd;                     // the last two k-steps always run in phases 0 and 1
+        if (odd) step(P1{}, std::true_type{}, std::true_type{}, 0);
+        for (; kb + 2 < nkb; kb += 2) {
             step(P0{}, std::true_type{}, std::true_type{}, kb);
             step(P1{}, std::true_type{}, std::true_type{}, kb + 1);
         }
-        bool odd = false;                 // three k-steps are left, else two
-        if constexpr (pcmm_host::odd_ksteps(S, MT)) odd = nkb & 1;
-        if (odd) {
-            step(P0{}, std::true_type{}, std::true_type{}, kb);
-            step(P1{}, std::true_type{}, std::false_type{}, kb + 1);
-            step(P0{}, std::false_type{}, std::false_type{}, kb + 2);
-        } else {
-            step(P0{}, std::true_type{}, std::false_type{}, kb);
-            step(P1{}, std::false_type{}, std::false_type{}, kb + 1);
-        }
+        step(P0{}, std::true_type{}, std::false_type{}, kb);
+        step(P1{}, std::false_type{}, std::false_type{}, kb + 1);
     }
 
     // volatile asm statements keep their order: last MFMA, drain, accumulator reads

@@ -129,8 +129,9 @@ inline int balanced_digits(uint64_t qmax)
 // Accumulator footprint limits the tile: MT*NT*E*4 accumulator registers per lane (NT = 2), at most 160.
 constexpr int tile_mt(int E) { return E <= 5 ? 4 : (E == 6 ? 3 : 2); }
 
-// Whether the GEMM kernel contracts odd numbers of k-steps.  With eight W fragments per k-step (four digits, two slices)
-// its third tail step takes the kernel from under 256 registers to 284, and only one work-group fits a compute unit.
+// Whether the GEMM kernel contracts odd numbers of k-steps.  Not with eight W fragments per k-step (four digits, two
+// slices): the second entry into the loop costs its two-wave kernel more than the k-step of zeros it saves (128 x 4096 by
+// 4096 x 16384, two 30-bit limbs 423 -> 433 us, an even count; 2000 x 160 by 160 x 16384, four limbs 400 us either way).
 constexpr bool odd_ksteps(int S, int MT) { return S * MT < 8; }
 
 // Everything about a plan that follows from its arguments alone.

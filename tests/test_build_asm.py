@@ -63,14 +63,20 @@ def test_accumulators_are_touched_only_by_the_kernels_own_asm(device_asm):
     assert n >= 20
 
 
-def test_register_budget_allows_two_workgroups_per_cu(device_asm):
+def _gemm_registers(asm):
+    """kernel name -> (accumulation registers, all registers) of the GEMM kernels; none of them spills"""
     found = {}
     for m in re.finditer(r"- \.agpr_count:\s+(\d+).*?\.name:\s+(\S+).*?\.vgpr_count:\s+(\d+)\s+\.vgpr_spill_count:\s+(\d+)",
-                         device_asm, re.S):
+                         asm, re.S):
         agpr, name, total, spill = int(m.group(1)), m.group(2), int(m.group(3)), int(m.group(4))
         if "gemm_kernel" in name:
             assert spill == 0, name
             found[name] = (agpr, total)
+    return found
+
+
+def test_register_budget_allows_two_workgroups_per_cu(device_asm):
+    found = _gemm_registers(device_asm)
     # WM=4, MT=4, NT=2, D=5, S=1, double-precision epilogue: the Llama projection kernel
     flagship = [v for k, v in found.items() if "ILi4ELi4ELi2ELi5ELi1ELi0E" in k]
     assert len(flagship) == 1
@@ -80,3 +86,11 @@ def test_register_budget_allows_two_workgroups_per_cu(device_asm):
     assert len(big) >= 15
     for k, (agpr, total) in big.items():
         assert total <= 256, (k, agpr, total)
+
+
+def test_two_wave_kernels_keep_two_waves_on_a_simd(device_asm):
+    """The kernels of products with few rows: at most 256 registers too, except four digits of two slices (260 since it was built)."""
+    small = {k: v for k, v in _gemm_registers(device_asm).items() if "gemm_kernelILi2E" in k}
+    assert len(small) >= 15
+    for k, (agpr, total) in small.items():
+        assert total <= (260 if "ILi2ELi4ELi2ELi4ELi2E" in k else 256), (k, agpr, total)

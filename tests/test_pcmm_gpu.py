@@ -180,6 +180,32 @@ def test_odd_counts_of_ksteps_and_waves_of_padding(gpu_device, M, K, Ncols, bits
     assert (got == pcmm_oracle(W, A, primes)).all()
 
 
+@pytest.mark.parametrize(
+    "M,K,Ncols,bits,L,wbits",
+    [
+        (128, 192, 40, 38, 2, 8),         # two-wave work-groups, three k-steps: the loop is not entered
+        (65, 129, 33, 36, 1, 16),         # three k-steps, the second wave of 48 rows with 17
+        (64, 300, 50, 49, 2, 16),         # five k-steps: the loop runs once
+        (33, 520, 31, 62, 1, 16),         # nine k-steps, one row in the second wave
+        (50, 400, 100, 62, 2, 8),         # seven k-steps
+        (20, 577 + 64, 100, 56, 1, 8),    # eleven k-steps, the second wave all padding
+        (100, 700, 130, 36, 2, 8),        # a limb pair, eleven k-steps
+        (40, 257, 17, 45, 3, 8),          # five k-steps, the second wave all padding
+        (64, 130944 + 130, 16, 38, 1, 8), # the second launch contracts three k-steps and adds to C
+        (300, 130944 + 130, 16, 45, 1, 8),
+    ],
+)
+def test_odd_counts_of_ksteps_in_two_wave_work_groups(gpu_device, M, K, Ncols, bits, L, wbits):
+    from oracle import pcmm_oracle
+
+    rng = np.random.default_rng(M * 5 + K + Ncols)
+    primes = pi.ntt_primes(bits, 1 << 10, L)
+    W = _rand_W(rng, M, K, wbits)
+    A = np.stack([_digit_pattern_residues(q, bits, K, Ncols, rng) for q in primes])
+    got, _ = _run_gpu(W, A, primes, bits, gpu_device)
+    assert (got == pcmm_oracle(W, A, primes)).all()
+
+
 def _digit_pattern_residues(q, bits, K, Ncols, rng):
     """Residues whose balanced base-256 digits sit at the extremes (+127 / -128 / 0 / -1 patterns)."""
     pats = []

@@ -212,9 +212,16 @@ inline pcmm_status plan_geometry(int64_t M, int64_t K, int64_t Ncols, int32_t L,
     // Limb pairs share nine digits where two limbs take ten.  Their digit planes, 9 * pair_ntiles fragments per k-step
     // with pair_ntiles <= 2 ntiles, are never more than the 10 * 2 ntiles of two single limbs, so ad_bytes covers them.
     // Contractions of at most 128 values of k keep single limbs: their kernel holds a limb's digits in registers.
+    // An odd number of limbs leaves one that runs singly, in launches of its own behind those of the pairs: two starts and
+    // two last rounds of work-groups.  That costs 10 to 40 us and pays from 2^37 products a limb on (pcmm_run, all limbs
+    // singly -> pairs and one single, three 36-bit limbs: 100 x 192 by 192 x 8192 25 -> 37 us; 1000 x 512 by 512 x 8192
+    // 115 -> 125; 1000 x 4096 by 4096 x 16384 1271 -> 1274; 2^37: 4096 x 4096 by 4096 x 8192 1748 -> 1697; 2^38: 4096 x
+    // 4096 by 4096 x 16384 3449 -> 3346).
+    constexpr int64_t kOddLimbsProducts = (int64_t)1 << 37;
     g->pair_ntiles = (Ncols + 15) / 16;
     g->pairs = 0;
-    if (S == 1 && D == 5 && g->nkb > 2 && (uint64_t)g->pair_ntiles * g->nkb * kPairDigits * kFragBytes < ((uint64_t)1 << 32)) {
+    if (S == 1 && D == 5 && g->nkb > 2 && (uint64_t)g->pair_ntiles * g->nkb * kPairDigits * kFragBytes < ((uint64_t)1 << 32) &&
+        (L % 2 == 0 || M * K * Ncols >= kOddLimbsProducts)) {           // M * K < 2^31 (wp_bytes), so the product fits
         g->pairs = L / 2;
         for (int j = 0; j < L / 2; ++j)
             if (!pair_ok(primes_host[2 * j], primes_host[2 * j + 1])) g->pairs = 0;

@@ -81,13 +81,21 @@ int main()
     for (int64_t nc : {1, 15, 16, 17, 31, 32, 33, 100, 8192})
         for (int32_t L = 1; L <= 5; ++L) {
             CHECK(plan_geometry(300, 129, nc, L, q36, 36, 8, 0, &g) == PCMM_OK);
-            CHECK(g.pairs == L / 2 && g.pair_ntiles * 16 >= nc);
+            CHECK(g.pairs == (L % 2 ? 0 : L / 2) && g.pair_ntiles * 16 >= nc);   // small: an odd number of limbs stays single
             const size_t pair_bytes = (size_t)g.pairs * g.nkb * g.pair_ntiles * kPairDigits * kFragBytes;
             const size_t single_bytes = (size_t)(L - 2 * g.pairs) * g.nkb * g.ntiles * g.NT * g.D * kFragBytes;
             CHECK(pair_bytes + single_bytes <= g.ad_bytes);
         }
     CHECK(plan_geometry(300, 128, 100, 2, q36, 36, 8, 0, &g) == PCMM_OK && g.pairs == 0);      // short contraction
     CHECK(plan_geometry(300, 300, 100, 2, q36, 36, 16, 0, &g) == PCMM_OK && g.pairs == 0);     // two weight slices
+    // an odd number of limbs pairs from 2^37 products a limb on, and the scratch covers the pairs and the single limb
+    CHECK(plan_geometry(8192, 4096, 4095, 3, q36, 36, 8, 0, &g) == PCMM_OK && g.pairs == 0);
+    CHECK(plan_geometry(8192, 4096, 4096, 1, q36, 36, 8, 0, &g) == PCMM_OK && g.pairs == 0);
+    for (int64_t nc : {4096, 4097, 4113, 32768})
+        for (int32_t L : {3, 5}) {
+            CHECK(plan_geometry(8192, 4096, nc, L, q36, 36, 8, 0, &g) == PCMM_OK && g.pairs == L / 2);
+            CHECK((size_t)g.nkb * kFragBytes * (g.pairs * g.pair_ntiles * kPairDigits + g.ntiles * g.NT * g.D) <= g.ad_bytes);
+        }
     const uint64_t same[2] = {68718428161ull, 68718428161ull};
     CHECK(plan_geometry(300, 300, 100, 2, same, 36, 8, 0, &g) == PCMM_OK && g.pairs == 0);
     CHECK(plan_geometry(128, 20000, 32768, 2, q36, 36, 8, 0, &g) == PCMM_OK && g.pairs == 0);  // nine planes beyond 4 GiB

@@ -30,11 +30,14 @@ def test_joint_digits_on_the_host(tmp_path):
 @pytest.mark.parametrize("M,K,Ncols,bits,L,ascending", [
     (1, 129, 1, 36, 2, False),          # smallest contraction that pairs; one row, one column
     (128, 200, 15, 36, 2, True),        # two-wave work-groups, ragged column fragment
-    (129, 192, 16, 33, 3, False),       # smallest primes; a pair and a single limb
+    (129, 192, 16, 33, 2, False),       # smallest primes
+    (129, 192, 16, 33, 3, False),       # an odd number of limbs this small: all singly
     (256, 256, 17, 34, 4, True),
-    (300, 257, 63, 35, 5, False),       # ragged rows, columns and k
+    (300, 257, 63, 35, 4, False),       # ragged rows, columns and k
+    (300, 257, 63, 35, 5, False),
     (257, 700, 130, 36, 6, True),
-    (64, 130944 + 64, 20, 36, 3, False),   # K in two launches: the second adds to both limbs of the pair
+    (64, 130944 + 64, 20, 36, 2, False),   # K in two launches: the second adds to both limbs of the pair
+    (64, 130944 + 64, 20, 36, 3, False),
 ])
 def test_paired_limbs_bit_exact(gpu_device, M, K, Ncols, bits, L, ascending, extreme):
     import torch
@@ -57,3 +60,31 @@ def test_paired_limbs_bit_exact(gpu_device, M, K, Ncols, bits, L, ascending, ext
     torch.cuda.synchronize()
     pkg.pcmm_plan_destroy(plan)
     assert (C.cpu().numpy().view(np.uint64) == pcmm_oracle(W, A, primes)).all()
+
+
+@pytest.mark.gpu
+def test_pairs_and_a_single_limb(gpu_device):
+    """Three limbs of 2^37 products each: the first two as a pair, the last one singly; ragged rows and columns, sampled."""
+    import torch
+
+    import paper_2601_18511_amd as pkg
+    from oracle import pcmm_oracle_select
+
+    M, K, Ncols, L, bits = 8200, 4096, 4100, 3, 36
+    primes = pi.ntt_primes(bits, 1 << 10, L)
+    g = torch.Generator(device=gpu_device)
+    g.manual_seed(7)
+    W = torch.randint(-128, 128, (M, K), dtype=torch.int8, device=gpu_device, generator=g)
+    A = torch.stack([torch.randint(0, q, (K, Ncols), dtype=torch.int64, device=gpu_device, generator=g) for q in primes])
+    C = torch.full((L, M, Ncols), -1, dtype=torch.int64, device=gpu_device)
+    plan = pkg.pcmm_plan_create(W, primes, bits, Ncols)
+    pkg.pcmm_run(plan, A, C)
+    torch.cuda.synchronize()
+    pkg.pcmm_plan_destroy(plan)
+    W_host, A_host = W.cpu().numpy(), A.cpu().numpy().view(np.uint64)
+    C_host = C.cpu().numpy().view(np.uint64)
+    rows = [0, 255, 256, 4096, 8191, 8192, M - 1]
+    cols = list(range(0, 40)) + list(range(2040, 2060)) + list(range(Ncols - 30, Ncols))
+    all_rows, all_cols = np.arange(M), np.arange(Ncols)
+    assert (C_host[:, rows, :] == pcmm_oracle_select(W_host, A_host, primes, rows, all_cols)).all()
+    assert (C_host[:, :, cols] == pcmm_oracle_select(W_host, A_host, primes, all_rows, cols)).all()

@@ -742,6 +742,7 @@ struct pcmm_plan {
     bool shortk;             // at most 128 values of k: pcmm_shortk runs, which needs no digit scratch
     int pairs;               // limb pairs whose digits are split jointly; limbs from 2 * pairs on run singly
     int64_t pair_ntiles;     // n-tiles (16 columns) of a pair
+    int gn, pair_gn;         // n-tiles per raster group
     PairConsts pcs;
     hipEvent_t ev[4];
     bool have_ev;
@@ -873,6 +874,7 @@ hipError_t launch_products(const pcmm_plan *p, GemmArgs ga, bool pair, hipStream
     ga.L = pair ? p->pairs : p->L - limb0;
     if (!ga.L) return hipSuccess;
     ga.ntiles = (int)(pair ? p->pair_ntiles : p->ntiles);
+    ga.gn = pair ? p->pair_gn : p->gn;
     ga.Ad += pair ? 0 : pair_digit_bytes(p);
     ga.C += (int64_t)limb0 * p->M * p->Ncols;
     ga.lc += limb0;
@@ -915,8 +917,6 @@ pcmm_status run_impl(const pcmm_plan *p, int8_t *Ad, const uint64_t *A, uint64_t
         ga.MB = p->MB;
         ga.nkb = (int)p->nkb;
         ga.mtiles = (int)p->mtiles;
-        // concurrent tiles on one XCD (32 CUs) should form a block of about 4 m-tiles x 8 n-tiles
-        ga.gn = 8;
         // A contraction longer than the int32 accumulators can hold runs as several launches over
         // consecutive ranges of k; every launch after the first adds its result to C modulo q_j.
         for (int64_t kb0 = 0; kb0 < p->ksteps; kb0 += p->nkb_launch) {
@@ -977,6 +977,7 @@ pcmm_status pcmm_plan_create(pcmm_plan **out, int64_t M, int64_t K, int64_t Ncol
     p->ksteps = g.ksteps;
     p->pairs = g.pairs;
     p->pair_ntiles = g.pair_ntiles;
+    p->gn = g.gn; p->pair_gn = g.pair_gn;
     for (int j = 0; j < g.pairs; ++j) p->pcs.c[j] = pcmm_host::pair_const(primes_host[2 * j], primes_host[2 * j + 1]);
     p->Wp = nullptr; p->Ad = nullptr; p->lc = nullptr; p->bytes = 0; p->have_ev = false;
 

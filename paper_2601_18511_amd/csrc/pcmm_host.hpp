@@ -148,6 +148,7 @@ struct Geometry {
     size_t wp_bytes, ad_bytes, lc_bytes;
     int pairs;                 // limb pairs split jointly (0 or L / 2)
     int64_t pair_ntiles;       // n-tiles of 16 columns
+    int gn, pair_gn;           // n-tiles per raster group of the GEMM kernel, for single limbs and for pairs
     uint32_t w_kstride;        // bytes between k-steps of one packed W slice
     uint32_t a_kstride;        // bytes between k-steps of one limb's digit chunks
 };
@@ -217,15 +218,32 @@ inline pcmm_status plan_geometry(int64_t M, int64_t K, int64_t Ncols, int32_t L,
     // singly -> pairs and one single, three 36-bit limbs: 100 x 192 by 192 x 8192 25 -> 37 us; 1000 x 512 by 512 x 8192
     // 115 -> 125; 1000 x 4096 by 4096 x 16384 1271 -> 1274; 2^37: 4096 x 4096 by 4096 x 8192 1748 -> 1697; 2^38: 4096 x
     // 4096 by 4096 x 16384 3449 -> 3346).
+    // Rows of C that start inside a 128-byte line: every n-tile shares a line with its neighbour, and a pair's tiles are half as
+    // wide.  With more than 16 m-tiles, where the raster below cannot make up for it, pairs then pay beyond 768 values of k
+    // only (singly -> pairs, two limbs, 12301 columns: 9000 x 192 by 192 623 -> 675 us; 6000 x 512 607 -> 635; 6000 x 768
+    // 739 -> 756; 6000 x 1000 863 -> 868; 6000 x 1500 1124 -> 1102; up to 16 m-tiles 2048 x 192 156 -> 161, 4096 x 400
+    // 403 -> 403, 1000 x 1000 232 -> 218).
     constexpr int64_t kOddLimbsProducts = (int64_t)1 << 37;
+    const bool shared_lines = Ncols % 16 != 0 && g->mtiles > 16 && K <= 768;
     g->pair_ntiles = (Ncols + 15) / 16;
     g->pairs = 0;
     if (S == 1 && D == 5 && g->nkb > 2 && (uint64_t)g->pair_ntiles * g->nkb * kPairDigits * kFragBytes < ((uint64_t)1 << 32) &&
-        (L % 2 == 0 || M * K * Ncols >= kOddLimbsProducts)) {           // M * K < 2^31 (wp_bytes), so the product fits
+        !shared_lines && (L % 2 == 0 || M * K * Ncols >= kOddLimbsProducts)) {   // M * K < 2^31 (wp_bytes), so the product fits
         g->pairs = L / 2;
         for (int j = 0; j < L / 2; ++j)
             if (!pair_ok(primes_host[2 * j], primes_host[2 * j + 1])) g->pairs = 0;
     }
+
+    // The raster of the GEMM kernel: the work-groups that are resident together on one XCD (32 CUs) form a block of about
+    // 8 m-tiles x gn n-tiles.  Eight n-tiles of 32 columns are 2 KiB of every output row; a pair's tiles have 16 columns and
+    // take sixteen for the same 2 KiB while the contraction is short enough for the stores to count (at most 2048 values of
+    // k) and the matrix has at most 16 m-tiles (pcmm_run, 8 -> 16 n-tiles: 2048 x 256 by 256 x 8192, four limbs 216 -> 198 us,
+    // 198 singly; 4096 x 256 by 256 x 16384, four limbs 768 -> 650, 704 singly; 2048 x 1500 by 1500 x 8192, four limbs
+    // 608 -> 569, 603 singly).  With more m-tiles sixteen are slower (14336 x 1500 by 1500 x 8192, four limbs 2930 -> 3325),
+    // with longer contractions they are equal or slower (4096 x 4096 by 4096 x 32768, four limbs 8767 and 8765; 4096 x 14336 by
+    // 14336 x 8192, five limbs 9147 -> 9654).
+    g->gn = 8;
+    g->pair_gn = g->mtiles <= 16 && K <= 2048 ? 16 : 8;
 
     g->w_kstride = (uint32_t)(g->MB * kFragBytes);
     g->a_kstride = (uint32_t)(g->ntiles * g->NT * D * kFragBytes);

@@ -96,6 +96,15 @@ int main()
             CHECK(plan_geometry(8192, 4096, nc, L, q36, 36, 8, 0, &g) == PCMM_OK && g.pairs == L / 2);
             CHECK((size_t)g.nkb * kFragBytes * (g.pairs * g.pair_ntiles * kPairDigits + g.ntiles * g.NT * g.D) <= g.ad_bytes);
         }
+    // pairs of short contractions: output rows of 2 KiB at a time as with single limbs, up to 16 m-tiles; beyond those no
+    // pairs where the rows of C start inside a line
+    CHECK(plan_geometry(4096, 2048, 8192, 2, q36, 36, 8, 0, &g) == PCMM_OK && g.pairs == 1 && g.pair_gn * 16 == g.gn * g.NT * 16);
+    CHECK(plan_geometry(4096, 2049, 8192, 2, q36, 36, 8, 0, &g) == PCMM_OK && g.pair_gn == 8);
+    CHECK(plan_geometry(4097, 2048, 8192, 2, q36, 36, 8, 0, &g) == PCMM_OK && g.pairs == 1 && g.pair_gn == 8);
+    CHECK(plan_geometry(4097, 768, 8192, 2, q36, 36, 8, 0, &g) == PCMM_OK && g.pairs == 1);
+    CHECK(plan_geometry(4097, 768, 8191, 2, q36, 36, 8, 0, &g) == PCMM_OK && g.pairs == 0);
+    CHECK(plan_geometry(4096, 768, 8191, 2, q36, 36, 8, 0, &g) == PCMM_OK && g.pairs == 1);
+    CHECK(plan_geometry(4097, 769, 8191, 2, q36, 36, 8, 0, &g) == PCMM_OK && g.pairs == 1);
     const uint64_t same[2] = {68718428161ull, 68718428161ull};
     CHECK(plan_geometry(300, 300, 100, 2, same, 36, 8, 0, &g) == PCMM_OK && g.pairs == 0);
     CHECK(plan_geometry(128, 20000, 32768, 2, q36, 36, 8, 0, &g) == PCMM_OK && g.pairs == 0);  // nine planes beyond 4 GiB

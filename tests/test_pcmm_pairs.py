@@ -36,6 +36,9 @@ def test_joint_digits_on_the_host(tmp_path):
     (300, 257, 63, 35, 4, False),       # ragged rows, columns and k
     (300, 257, 63, 35, 5, False),
     (257, 700, 130, 36, 6, True),
+    (500, 200, 257, 36, 2, False),      # raster groups of sixteen n-tiles, the last of one tile; two m-tiles
+    (4100, 150, 273, 36, 2, False),     # 17 m-tiles, rows of C inside lines: singly
+    (4100, 150, 272, 36, 2, True),      # 17 m-tiles: raster groups of eight
     (64, 130944 + 64, 20, 36, 2, False),   # K in two launches: the second adds to both limbs of the pair
     (64, 130944 + 64, 20, 36, 3, False),
 ])

@@ -186,8 +186,8 @@ __global__ __launch_bounds__(256) void split_kernel(const uint64_t *__restrict__
 // residues are therefore joined by the Chinese remainder theorem into one integer X with X = x1 mod q1 and
 // X = x2 mod q2, and X is cut into nine balanced digits; the product sum W X reduced modulo q1 and modulo q2 gives both
 // outputs.  One digit product in ten is saved: in the matrix products, in the digit planes and in every copy of them.
-//   t = ((x2 - x1) q1^-1 + s) mod q2,   s = floor(Bias / q1),   Y = q1 t + x1 + (Bias mod q1)
-// is X + Bias for X = q1 (t - s) + x1, and 0 <= Y < q1 q2 + q1 <= 256^9, so the bytes of Y, each xor 0x80, are the
+//   t = ((x2 - x1) q1^-1 + s) mod q2,   s = floor(Bias / q1) mod q2,   Y = q1 t + x1 + (Bias mod q1)
+// is X + Bias for X = q1 (t - floor(Bias / q1)) + x1, and 0 <= Y < q1 q2 + q1 <= 256^9, so the bytes of Y, each xor 0x80, are the
 // balanced digits of X (pcmm_host.hpp decides which primes qualify and derives the constants).
 // Bound: HBM, 16 bytes read and 9 written per pair of residues; about 45 vector instructions per pair, a third of what
 // the memory time hides.  Layout as in split_kernel with one 16-column fragment per tile (NT = 1) and nine digits.
@@ -225,7 +225,8 @@ __global__ __launch_bounds__(256) void split_pair_kernel(const uint64_t *__restr
             // residues as doubles: placed in the low mantissa bits of 2^52 + x, whose difference is exact
             constexpr uint64_t kMagic = 0x4330000000000000ull;
             const double dx = __longlong_as_double(u2 | kMagic) - __longlong_as_double(u1 | kMagic);
-            // |dx| < 2^36 < 2 q2, so |mulmod| <= 0.75 q2 + 1; s < 2.01 q2 (q1 > 2^35)
+            // -q1 < dx < q2 and q1 < 2 q2, so |mulmod| <= 0.75 q2 + 1; 0 <= s < q2: -0.75 q2 - 1 <= v < 1.75 q2 + 1, which
+            // is within one q2 of [0, q2), and canonical takes far more
             const double v = mulmod(pc.inv, dx, pc.q2, pc.invq2) + pc.s;
             const uint64_t t = (uint64_t)__double_as_longlong(canonical(v, pc.q2, pc.invq2, pc.half_invq2) + 4503599627370496.0);
             const uint32_t tl = (uint32_t)t, th = (uint32_t)(t >> 32) & 0xFu;

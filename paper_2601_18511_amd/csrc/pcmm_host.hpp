@@ -62,7 +62,7 @@ inline LimbConst limb_const(uint64_t q)
 }
 
 // Two limbs whose digits are split jointly: x1 mod q1 and x2 mod q2 become
-//   Y = q1 t + x1 + (Bias mod q1),  t = ((x2 - x1) q1^-1 + s) mod q2,  s = floor(Bias / q1),
+//   Y = q1 t + x1 + (Bias mod q1),  t = ((x2 - x1) q1^-1 + s) mod q2,  s = floor(Bias / q1) mod q2,
 // the balanced digits of the integer X = Y - Bias with X = x1 mod q1, X = x2 mod q2 (Bias = sum_{i<9} 128 * 256^i).
 constexpr int kPairDigits = 9;
 struct PairConst {

@@ -181,7 +181,7 @@ __global__ __launch_bounds__(256) void split_kernel(const uint64_t *__restrict__
     }
 }
 
-// Digit split of TWO limbs at once (S = 1, primes of 33 to 36 bits).  One residue x_i < q_i < 2^36 takes five
+// Digit split of TWO limbs at once (S = 1, five digits a limb, primes below 2^36).  One residue x_i < q_i < 2^36 takes five
 // base-256 digits, so two limbs cost ten digit products although they hold only 72 bits, nine bytes.  The two
 // residues are therefore joined by the Chinese remainder theorem into one integer X with X = x1 mod q1 and
 // X = x2 mod q2, and X is cut into nine balanced digits; the product sum W X reduced modulo q1 and modulo q2 gives both

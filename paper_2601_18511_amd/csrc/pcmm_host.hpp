@@ -80,13 +80,13 @@ inline u128 pair_bias()
     return bias;
 }
 
-// Whether two limbs can share nine digits: distinct primes of 33 to 36 bits (below, two limbs take eight single
-// digits anyway; above, nine digits do not hold the product), coprime, Y < q1 q2 + q1 <= 256^9.
-// The split kernel's arithmetic needs q1 < 2 q2 and th = t >> 32 below 16.
+// Whether two limbs of five digits each can share nine: coprime, of one size (q1 < 2 q2, which the split kernel's arithmetic
+// needs, and q2 < 2 q1; the limbs of a plan always are), Y < q1 q2 + q1 <= 256^9, below 2^36 (the kernel takes th = t >> 32
+// as four bits).  The limbs of a plan take five digits from 31-bit primes above 0x7F7F7F80 on.
 inline bool pair_ok(uint64_t q1, uint64_t q2)
 {
-    const uint64_t lo = (uint64_t)1 << 32, hi = (uint64_t)1 << 36;
-    if (q1 <= lo || q2 <= lo || q1 >= hi || q2 >= hi || q1 >= 2 * q2) return false;
+    const uint64_t hi = (uint64_t)1 << 36;
+    if (q1 >= hi || q2 >= hi || q1 >= 2 * q2 || q2 >= 2 * q1) return false;
     uint64_t a = q1, b = q2;
     while (b) { const uint64_t r = a % b; a = b; b = r; }
     return a == 1 && (u128)q1 * q2 + q1 <= ((u128)1 << (8 * kPairDigits));

@@ -48,9 +48,10 @@ static void check_value(const PairConst &c, uint64_t q1, uint64_t q2, uint64_t x
 
 int main()
 {
-    // the largest odd pair below 2^36, primes of 36, 35, 34 and 33 bits
+    // the largest odd pair below 2^36, numbers of 36, 35, 34, 33, 32 and 31 bits (31: the smallest that take five digits)
     const uint64_t qs[] = {68719476735ull, 68719476733ull, 68719476503ull, 68718428161ull, 34359738641ull, 34359738421ull,
-                           17179869209ull, 8589934609ull, 4294967311ull, 4294967357ull};
+                           17179869209ull, 8589934609ull, 4294967311ull, 4294967357ull,
+                           4294967291ull, 4294967279ull, 2147483659ull, 2147483647ull, 2139062149ull, 2139062145ull};
     const int n = sizeof(qs) / sizeof(qs[0]);
     uint64_t r = 88172645463325252ull;
     int accepted = 0;
@@ -73,7 +74,7 @@ int main()
     CHECK(accepted >= 20);
     CHECK(!pair_ok(68718428161ull, 68718428161ull));                    // one modulus twice: not coprime
     CHECK(!pair_ok((1ull << 36) + 1, 68718428161ull));                  // 37 bits
-    CHECK(!pair_ok(4294967291ull, 68718428161ull));                     // 32 bits
+    CHECK(!pair_ok(4294967291ull, 68718428161ull));                     // 32 and 36 bits
     CHECK(!pair_ok(68718428161ull, 8589934609ull));                     // q1 >= 2 q2
     // the plan pairs limbs only where nine digits replace ten, and its scratch covers both layouts
     const uint64_t q36[5] = {68719476733ull, 68718428161ull, 68719476503ull, 68719476731ull, 68719476735ull};
@@ -105,6 +106,15 @@ int main()
     CHECK(plan_geometry(4097, 768, 8191, 2, q36, 36, 8, 0, &g) == PCMM_OK && g.pairs == 0);
     CHECK(plan_geometry(4096, 768, 8191, 2, q36, 36, 8, 0, &g) == PCMM_OK && g.pairs == 1);
     CHECK(plan_geometry(4097, 769, 8191, 2, q36, 36, 8, 0, &g) == PCMM_OK && g.pairs == 1);
+    // every size of prime that takes five digits pairs, none that takes four or six
+    for (int bits = 24; bits <= 41; ++bits) {
+        const uint64_t top[2] = {((uint64_t)1 << bits) - 1, ((uint64_t)1 << bits) - 3};
+        CHECK(plan_geometry(300, 300, 100, 2, top, bits, 8, 0, &g) == PCMM_OK);
+        CHECK(g.pairs == (bits >= 31 && bits <= 36 ? 1 : 0) && (g.pairs == 0 || g.D == 5));
+    }
+    const uint64_t low31[2] = {2139062145ull - 2, 2139062145ull - 4}, edge31[2] = {2139062145ull, 2139062143ull};
+    CHECK(plan_geometry(300, 300, 100, 2, low31, 31, 8, 0, &g) == PCMM_OK && g.D == 4 && g.pairs == 0);
+    CHECK(plan_geometry(300, 300, 100, 2, edge31, 31, 8, 0, &g) == PCMM_OK && g.D == 5 && g.pairs == 1);
     const uint64_t same[2] = {68718428161ull, 68718428161ull};
     CHECK(plan_geometry(300, 300, 100, 2, same, 36, 8, 0, &g) == PCMM_OK && g.pairs == 0);
     CHECK(plan_geometry(128, 20000, 32768, 2, q36, 36, 8, 0, &g) == PCMM_OK && g.pairs == 0);  // nine planes beyond 4 GiB

@@ -30,7 +30,10 @@ def test_joint_digits_on_the_host(tmp_path):
 @pytest.mark.parametrize("M,K,Ncols,bits,L,ascending", [
     (1, 129, 1, 36, 2, False),          # smallest contraction that pairs; one row, one column
     (128, 200, 15, 36, 2, True),        # two-wave work-groups, ragged column fragment
-    (129, 192, 16, 33, 2, False),       # smallest primes
+    (129, 192, 16, 33, 2, False),
+    (200, 150, 40, 31, 2, True),        # smallest primes of five digits
+    (129, 192, 33, 32, 4, False),
+    (300, 129, 16, 32, 2, False),
     (129, 192, 16, 33, 3, False),       # an odd number of limbs this small: all singly
     (256, 256, 17, 34, 4, True),
     (300, 257, 63, 35, 4, False),       # ragged rows, columns and k

@@ -7,7 +7,8 @@ and C resident in HBM.  Plan creation (W packing) is outside the timed region.
 
 Prints ONE JSON line.  `value` is algorithmic int8 TOPS = 2*M*K*Ncols*L*D*S / time with
 D = ceil(prime_bits/8) digits and S = w_bits/8 slices for the headline workload (--workload, default
-attn_proj); padding or extra issued MFMA work is not credited.  The same line carries, under
+attn_proj); padding or extra issued MFMA work is not credited.  The rooflines count the digit products that run:
+nine for two limbs whose digits are split jointly, where the formula has ten.  The same line carries, under
 "workloads", the same measurement for every workload of pcmm_inputs.WORKLOADS (per-step ms median and
 min from HIP events, TOPS, the roofline of the MFMA kernel, a check of sampled GPU rows against the
 oracle), a plain device copy timed in the same run as the ceiling of the streaming kernels, and the
@@ -178,7 +179,7 @@ def pcmv_rates(pkg, pi, torch, dev, copy_GBs: float, iters: int = 10, check: boo
         e1.record(stream)
         e1.synchronize()
         ms = e0.elapsed_time(e1) / iters
-        nbytes = 8.0 * L * N * (Mp * Kp + 2 * Mp + 2 * Kp)          # plaintexts read, products written, ciphertexts read
+        nbytes = L * N * (4.5 * Mp * Kp + 16.0 * Mp + 16.0 * Kp)    # plaintexts (packed, 36 bits) read, products written, ciphertexts read
         rec = {"plaintext_polynomials": Mp * Kp, "input_ciphertexts": Kp, "ms": ms, "algorithmic_bytes": nbytes,
                "GBs": nbytes / (ms * 1e-3) / 1e9, "frac_of_hbm_peak": nbytes / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
                "frac_of_copy": nbytes / (ms * 1e-3) / 1e9 / copy_GBs,
@@ -247,17 +248,18 @@ def measure_workload(pkg, pi, torch, dev, wl, steps: int, warmup: int, oracle_se
     tops = wl.int8_ops / (ms_per_step * 1e-3) / 1e12
     gemm_avg = sum(gemm_ms) / len(gemm_ms)
     split_avg = sum(split_ms) / len(split_ms)
-    gemm_tops = wl.int8_ops / (gemm_avg * 1e-3) / 1e12
+    gemm_tops = wl.run_int8_ops / (gemm_avg * 1e-3) / 1e12
     res_bytes = 8.0 * wl.K * wl.Ncols * wl.L
     out_bytes = 8.0 * wl.M * wl.Ncols * wl.L
-    split_alg_bytes = res_bytes * (8 + wl.digits) / 8.0
+    planes_bytes = float(wl.K * wl.Ncols * wl.digit_planes)
+    split_alg_bytes = res_bytes + planes_bytes
     alg_bytes = res_bytes + out_bytes + wl.M * wl.K * wl.slices
 
     # the MFMA kernel's roofline: int8 MFMA for the projections; HBM where the algorithmic bytes of the launch
     # (digit planes + W + C) take longer at 8 TB/s than its int8 work at 5 POP/s (the wide workload)
     fused = mfma_kernel_name(wl) == "gemm_shortk_kernel"      # cuts the digits itself: reads the residues, no split kernel
-    gemm_alg_bytes = (res_bytes if fused else wl.K * wl.Ncols * wl.L * wl.digits) + wl.M * wl.K * wl.slices + out_bytes
-    mfma_floor_s = wl.int8_ops / (INT8_MFMA_PEAK_TOPS * 1e12)
+    gemm_alg_bytes = (res_bytes if fused else planes_bytes) + wl.M * wl.K * wl.slices + out_bytes
+    mfma_floor_s = wl.run_int8_ops / (INT8_MFMA_PEAK_TOPS * 1e12)
     hbm_floor_s = gemm_alg_bytes / (HBM_PEAK_GBS * 1e9)
     kname = mfma_kernel_name(wl) + " (int8 MFMA main loop + recombine + reduce mod q)"
     if mfma_floor_s >= hbm_floor_s:
@@ -268,6 +270,7 @@ def measure_workload(pkg, pi, torch, dev, wl, steps: int, warmup: int, oracle_se
         roofline = {"kernel": kname, "bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                     "frac": gbs / HBM_PEAK_GBS, "mfma_TOPs": gemm_tops}
     roofline["avg_launch_ms"] = gemm_avg
+    roofline["int8_ops_per_run"] = wl.run_int8_ops
     roofline["algorithmic_bytes_per_launch"] = gemm_alg_bytes
     roofline["traffic"] = _traffic_from_profiles(wl)
 
@@ -429,7 +432,7 @@ def main() -> int:
 
 
 def wl_tops(rec) -> float:
-    """int8 TOP/s of the MFMA kernel alone (algorithmic ops / its average launch time)."""
+    """int8 TOP/s of the MFMA kernel alone (the digit products that run / its average time)."""
     r = rec["roofline"]
     return r["achieved"] if r["bound"] == "mfma" else r["mfma_TOPs"]
 

@@ -6,7 +6,9 @@ the figures are the ones a roofline needs):
   * per kernel: launches, average / minimum / maximum duration (from --kernel-trace, or from the dispatch
     timestamps of a --pmc run when no trace is given);
   * achieved int8 TOP/s of the MFMA kernel against the chip's 5000 TOP/s dense int8 peak, and its
-    algorithmic bytes per second against the 8000 GB/s HBM peak;
+    algorithmic bytes per second against the 8000 GB/s HBM peak.  One pcmm_run may launch two instantiations
+    (limb pairs, and the single limb left over): their times and counters are added up, and the operations and
+    bytes are those of the digit planes the run makes (nine for a pair);
   * HBM-side traffic: FETCH_SIZE and WRITE_SIZE (KiB per dispatch), each scaled by what the same counter
     reads for a plain device copy of known size in the same run (bench.py --copy-calibration);
   * MFMA utilisation: SQ_VALU_MFMA_BUSY_CYCLES / (SIMDs x shader cycles), the shader cycles taken from
@@ -147,6 +149,14 @@ def mean(xs: Sequence[float]) -> float:
     return sum(xs) / len(xs)
 
 
+SPLIT = r"^split_kernel<|^split_pair_kernel$"
+
+
+def run_mean(values: Dict[str, List[float]], kernels: Sequence[str]) -> float:
+    """Average per pcmm_run over the instantiations that one run launches once each: the sum of their averages."""
+    return sum(mean(values[k]) for k in kernels)
+
+
 # --------------------------------------------------------------------------------------------------
 # derived figures
 # --------------------------------------------------------------------------------------------------
@@ -178,20 +188,20 @@ def workload_figures(name: str) -> dict:
 
     w = pi.WORKLOADS[name]
     fused = w.K <= 128 and w.prime_bits <= 50            # gemm_shortk_kernel reads the residues and cuts the digits itself
-    digits_bytes = w.K * w.Ncols * w.L * (8 if fused else w.digits)
+    digits_bytes = w.K * w.Ncols * (8 * w.L if fused else w.digit_planes)
     return {
-        "desc": "W %dx%d int%d, A %dx%d uint64 residues, L=%d primes of %d bits, D=%d digits, S=%d slices"
-                % (w.M, w.K, w.w_bits, w.K, w.Ncols, w.L, w.prime_bits, w.digits, w.slices),
-        "int8_ops": float(w.int8_ops),
+        "desc": "W %dx%d int%d, A %dx%d uint64 residues, L=%d primes of %d bits, %d digit planes, S=%d slices"
+                % (w.M, w.K, w.w_bits, w.K, w.Ncols, w.L, w.prime_bits, w.digit_planes, w.slices),
+        "int8_ops": float(w.run_int8_ops),
         "gemm_bytes": float(digits_bytes + w.M * w.K * w.slices + 8 * w.M * w.Ncols * w.L),
         "gemm_parts": (digits_bytes, w.M * w.K * w.slices, 8 * w.M * w.Ncols * w.L),
-        "split_bytes": float(w.K * w.Ncols * w.L * (8 + w.digits)),
+        "split_bytes": float(w.K * w.Ncols * (8 * w.L + w.digit_planes)),
         "mfma_kernel": "gemm_shortk_kernel" if fused else "gemm_kernel",
     }
 
 
 def trace_summary(workload: str, fig: dict, trace: Dict[str, List[float]], commands: Sequence[str]) -> str:
-    mine = pick(trace, r"gemm_kernel|gemm_shortk_kernel|split_kernel|transpose_u64_kernel|mfma_probe_kernel")
+    mine = pick(trace, r"gemm_kernel|gemm_shortk_kernel|split_kernel|split_pair_kernel|transpose_u64_kernel|mfma_probe_kernel")
     lines = ["rocprofv3 kernel trace of the PCMM kernels on the %s workload" % workload,
              "(%s; one pcmm_run = the split kernels + the MFMA kernels, or gemm_shortk_kernel alone)" % fig["desc"], ""]
     lines += ["commands (from /tmp with TMPDIR=/tmp on the MI355X box, R = repository root):"] + ["  " + c for c in commands] + [""]
@@ -202,23 +212,23 @@ def trace_summary(workload: str, fig: dict, trace: Dict[str, List[float]], comma
     lines.append("(every other kernel in the trace belongs to torch: input generators, the calibration copy)")
     g = pick(trace, r"^%s<" % fig["mfma_kernel"])
     if g:
-        d = [x for k in g for x in trace[k]]
-        avg, lo = mean(d), min(d)
+        avg, lo = run_mean(trace, g), sum(min(trace[k]) for k in g)
         tops = fig["int8_ops"] / (avg * 1e-9) / 1e12
         gbs = fig["gemm_bytes"] / (avg * 1e-9) / 1e9
         lines += ["",
-                  "%s: average %.3f ms (min %.3f ms, median %.3f ms) over %d launches"
-                  % (fig["mfma_kernel"], avg / 1e6, lo / 1e6, statistics.median(d) / 1e6, len(d)),
-                  "  algorithmic int8 work %.4g ops / average = %.0f TOP/s = %.1f %% of the %.0f TOP/s int8 MFMA peak"
+                  "%s: average %.3f ms (min %.3f ms, median %.3f ms) over %d runs of %d launch%s"
+                  % (fig["mfma_kernel"], avg / 1e6, lo / 1e6, sum(statistics.median(trace[k]) for k in g) / 1e6,
+                     len(trace[g[0]]), len(g), "es" if len(g) > 1 else ""),
+                  "  int8 work %.4g ops / average = %.0f TOP/s = %.1f %% of the %.0f TOP/s int8 MFMA peak"
                   % (fig["int8_ops"], tops, 100 * tops / INT8_MFMA_PEAK_TOPS, INT8_MFMA_PEAK_TOPS),
                   "  algorithmic bytes %.2f GiB / average = %.0f GB/s = %.1f %% of the %.0f GB/s HBM peak"
                   % (fig["gemm_bytes"] / GIB, gbs, 100 * gbs / HBM_PEAK_GBS, HBM_PEAK_GBS)]
-    s = pick(trace, r"^split_kernel<")
+    s = pick(trace, SPLIT)
     if s:
-        d = [x for k in s for x in trace[k]]
-        gbs = fig["split_bytes"] / (mean(d) * 1e-9) / 1e9
-        lines += ["split_kernel: average %.3f ms (min %.3f ms); algorithmic bytes %.2f GiB / average = %.0f GB/s = %.1f %% of the HBM peak"
-                  % (mean(d) / 1e6, min(d) / 1e6, fig["split_bytes"] / GIB, gbs, 100 * gbs / HBM_PEAK_GBS)]
+        avg = run_mean(trace, s)
+        gbs = fig["split_bytes"] / (avg * 1e-9) / 1e9
+        lines += ["%s: average %.3f ms (min %.3f ms); algorithmic bytes %.2f GiB / average = %.0f GB/s = %.1f %% of the HBM peak"
+                  % (" + ".join(s), avg / 1e6, sum(min(trace[k]) for k in s) / 1e6, fig["split_bytes"] / GIB, gbs, 100 * gbs / HBM_PEAK_GBS)]
     lines.append("(averages include the first, cold launch; bench.py reports the HIP-event average of its timed steps)")
     return "\n".join(lines) + "\n"
 
@@ -241,21 +251,21 @@ def traffic_summary(workload: str, fig: dict, counters, commands: Sequence[str],
                   % (cal_f[0], sf, cal_w[0], sw), ""]
     else:
         lines += ["calibration: no copy kernel in these runs; counters taken at face value (scale 1)", ""]
-    lines.append("per launch (average over the profiled launches), counters in KiB, scaled values in GiB:")
+    lines.append("per run (average over the profiled runs), counters in KiB, scaled values in GiB:")
     traffic = None
-    for pat, label in ((r"^%s<" % fig["mfma_kernel"], fig["mfma_kernel"]), (r"^split_kernel<", "split_kernel")):
+    for pat, label in ((r"^%s<" % fig["mfma_kernel"], fig["mfma_kernel"]), (SPLIT, "split kernels")):
         ks = pick(counters, pat)
         if not ks:
             continue
-        f = mean([v for k in ks for v in counters[k].get("FETCH_SIZE", [])])
-        w = mean([v for k in ks for v in counters[k].get("WRITE_SIZE", [])])
+        f = run_mean({k: counters[k].get("FETCH_SIZE") or [0.0] for k in ks}, ks)
+        w = run_mean({k: counters[k].get("WRITE_SIZE") or [0.0] for k in ks}, ks)
         lines.append("  %-20s FETCH_SIZE %.0f KiB -> %.2f GiB read;   WRITE_SIZE %.0f KiB -> %.2f GiB written"
                      % (label, f, f * sf * 1024 / GIB, w, w * sw * 1024 / GIB))
         if label == fig["mfma_kernel"]:
             traffic = (f * sf + w * sw) * 1024.0
     dp, wp, cp = fig["gemm_parts"]
     lines += ["",
-              "algorithmic bytes per launch: %s %.2f GiB (digit planes or residues %.2f + packed W %.3f + C %.2f), split_kernel %.2f GiB"
+              "algorithmic bytes per run: %s %.2f GiB (digit planes or residues %.2f + packed W %.3f + C %.2f), split kernels %.2f GiB"
               % (fig["mfma_kernel"], fig["gemm_bytes"] / GIB, dp / GIB, wp / GIB, cp / GIB, fig["split_bytes"] / GIB),
               "traffic / algorithmic bytes of the MFMA kernel: %.2f" % (traffic / fig["gemm_bytes"]),
               "FETCH_SIZE counts what the L2s request from the fabric: re-reads of W and of digit chunks by different XCDs show up",
@@ -268,12 +278,13 @@ def counter_summary(workload: str, fig: dict, counters, durations, commands: Seq
     g = pick(counters, r"^%s<" % fig["mfma_kernel"])
     if not g:
         return None
-    c = {name: mean(v) for k in g for name, v in counters[k].items() if name not in ("FETCH_SIZE", "WRITE_SIZE")}
+    names = sorted({name for k in g for name in counters[k]} - {"FETCH_SIZE", "WRITE_SIZE"})
+    c = {name: sum(mean(counters[k][name]) for k in g if name in counters[k]) for name in names}
     if not c:
         return None
-    dur_ns = mean([x for k in g for x in durations.get(k, [])]) if any(k in durations for k in g) else None
-    lines = ["Issue and memory-system counters of %s on the %s workload (rocprofv3 --pmc, per launch, average over the"
-             % (", ".join(g), workload), "profiled launches; %s)" % fig["desc"], "",
+    dur_ns = run_mean(durations, g) if all(k in durations for k in g) else None
+    lines = ["Issue and memory-system counters of %s on the %s workload (rocprofv3 --pmc, per run, average over the"
+             % (" + ".join(g), workload), "profiled runs; %s)" % fig["desc"], "",
              "commands (from /tmp with TMPDIR=/tmp, R = repository root), one counter group per run:"]
     lines += ["  " + x for x in commands] + ["", "raw counters:"]
     lines += ["  %-40s %.6g" % (k, v) for k, v in sorted(c.items())]
@@ -326,7 +337,7 @@ def counter_summary(workload: str, fig: dict, counters, durations, commands: Seq
     return "\n".join(lines) + "\n"
 
 
-STREAMING = re.compile(r"^(split_kernel|transpose_u64_kernel|slot_rearrange_kernel|ntt\w*_kernel|mac_intt\w*|pack_w_kernel)")
+STREAMING = re.compile(r"^(split_kernel|split_pair_kernel|transpose_u64_kernel|slot_rearrange_kernel|ntt\w*_kernel|mac_intt\w*|pack_w_kernel)")
 
 
 def streaming_summary(trace_dir: Optional[str], fetch_dir: str, write_dir: str, commands: Sequence[str],

@@ -119,6 +119,23 @@ class Workload:
     def int8_ops(self) -> int:
         return 2 * self.modular_macs * self.digits * self.slices
 
+    @property
+    def limb_pairs(self) -> int:
+        """Pairs of limbs that the library splits jointly, nine digits a pair (the rule of csrc/pcmm_host.hpp for these workloads)."""
+        five_digits = self.w_bits == 8 and 0x7F7F7F80 < max(self.primes) < 1 << 36
+        worth_it = self.L % 2 == 0 or self.M * self.K * self.Ncols >= 1 << 37
+        return self.L // 2 if five_digits and self.K > 128 and worth_it else 0
+
+    @property
+    def digit_planes(self) -> int:
+        """Digit planes of all limbs together that the library makes and multiplies."""
+        return 9 * self.limb_pairs + self.digits * (self.L - 2 * self.limb_pairs)
+
+    @property
+    def run_int8_ops(self) -> int:
+        """The int8 operations that run: those of the digit planes.  int8_ops counts D digits for every limb."""
+        return 2 * self.M * self.K * self.Ncols * self.digit_planes * self.slices
+
 
 WORKLOADS = {
     w.name: w

@@ -25,6 +25,25 @@ def test_joint_digits_on_the_host(tmp_path):
     assert "all checks held" in r.stdout
 
 
+def test_the_measuring_tools_count_the_digit_planes_that_a_plan_makes(tmp_path):
+    if shutil.which("g++") is None:
+        pytest.skip("no g++")
+    calls = "".join(
+        'uint64_t q_%s[] = {%s}; if (plan_geometry(%d, %d, %d, %d, q_%s, %d, %d, 0, &g) != PCMM_OK) return 1;\n'
+        'printf("%s %%d %%d\\n", g.pairs, 9 * g.pairs + g.D * (%d - 2 * g.pairs));\n'
+        % (w.name, ", ".join("%dull" % q for q in w.primes), w.M, w.K, w.Ncols, w.L, w.name, w.prime_bits, w.w_bits, w.name, w.L)
+        for w in pi.WORKLOADS.values())
+    src = tmp_path / "planes.cpp"
+    src.write_text('#include <stdio.h>\n#include "pcmm_host.hpp"\nint main() { using namespace pcmm_host; Geometry g;\n' + calls + "return 0; }\n")
+    subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "paper_2601_18511_amd", "csrc"), "-o", str(tmp_path / "planes"), str(src)],
+                   check=True)
+    out = subprocess.run([str(tmp_path / "planes")], capture_output=True, text=True, check=True).stdout
+    assert out.split("\n")[:-1] == ["%s %d %d" % (w.name, w.limb_pairs, w.digit_planes) for w in pi.WORKLOADS.values()]
+    w = pi.WORKLOADS
+    assert (w["attn_proj"].digit_planes, w["ffn_down"].digit_planes, w["tiny"].digit_planes) == (18, 14, 10)
+    assert w["attn_proj"].run_int8_ops * 10 == w["attn_proj"].int8_ops * 9
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("extreme", [False, True])
 @pytest.mark.parametrize("M,K,Ncols,bits,L,ascending", [

@@ -141,3 +141,45 @@ def test_streaming_summary_lists_the_transform_kernels_of_both_decode_shapes(tmp
     # 256 MiB read (the counter halves it, the calibration doubles it back) + 256 MiB written in 0.2 ms
     assert abs(float(one[-3]) - 0.25) < 1e-3 and abs(float(one[-2]) - 0.25) < 1e-3
     assert abs(float(one[-1]) - 2 * 268435456 / 0.2e-3 / 1e9) < 1.0
+
+
+def test_a_run_of_limb_pairs_and_a_single_limb_is_added_up(tmp_path):
+    """Three limbs: one run launches the pair and the single instantiation of both kernels."""
+    gk, sk = "void (anonymous namespace)::gemm_kernel<4, 4, %s>((anonymous namespace)::GemmArgs)", "(anonymous namespace)::split%s(unsigned long const*)"
+    pair, single = gk % "1, 9, 1, 5", gk % "2, 5, 1, 0"
+    spair, ssingle = sk % "_pair_kernel", "void " + sk % "_kernel<5>"
+    w = 4096 * 14336 * 32768
+    ops, planes = 2.0 * w * 14, 14336 * 32768 * 14
+    runs = [(spair, 1e6), (ssingle, 0.5e6), (pair, 14e6), (single, 7e6)]        # ns
+
+    def names(text):
+        return [x.split("  ")[0] for x in text.splitlines()]
+
+    hdr = ["Dispatch_Id", "Kernel_Name", "Start_Timestamp", "End_Timestamp"]
+    rows = [[4 * r + i, k, 0, int(t)] for r in range(3) for i, (k, t) in enumerate(runs)]
+    _write_csv(str(tmp_path / "kt" / "h" / "1_kernel_trace.csv"), hdr, rows)
+    fig = rs.workload_figures("ffn_down")
+    assert fig["int8_ops"] == ops and fig["gemm_parts"][0] == planes
+    text = rs.trace_summary("ffn_down", fig, rs.read_kernel_trace(str(tmp_path / "kt")), [])
+    assert {"split_pair_kernel", "split_kernel<5>", "gemm_kernel<4, 4, 1, 9, 1, 5>", "gemm_kernel<4, 4, 2, 5, 1, 0>"} <= set(names(text))
+    assert "average 21.000 ms (min 21.000 ms, median 21.000 ms) over 3 runs of 2 launches" in text
+    assert "= %.0f TOP/s" % (ops / 21e-3 / 1e12) in text
+    assert "average 1.500 ms (min 1.500 ms)" in text
+    assert "= %.0f GB/s = " % ((14336 * 32768 * 24 + planes) / 1.5e-3 / 1e9) in text
+
+    hdr = ["Dispatch_Id", "Kernel_Name", "Grid_Size", "Counter_Name", "Counter_Value", "Start_Timestamp", "End_Timestamp"]
+    for d, counter, scale in (("f", "FETCH_SIZE", 1.0), ("w", "WRITE_SIZE", 2.0)):
+        rows = [[i, k, 64, counter, scale * (i + 1) * 1000.0, 0, int(t)] for i, (k, t) in enumerate(runs)]
+        _write_csv(str(tmp_path / d / "h" / "1_counter_collection.csv"), hdr, rows)
+    rows = [[i, k, 64, "GRBM_GUI_ACTIVE", 8.0 * t, 0, int(t)] for i, (k, t) in enumerate(runs)]
+    rows += [[i, k, 64, "SQ_VALU_MFMA_BUSY_CYCLES", 1024.0 * t * (0.8 if k == pair else 0.5), 0, int(t)] for i, (k, t) in enumerate(runs)]
+    _write_csv(str(tmp_path / "c" / "h" / "1_counter_collection.csv"), hdr, rows)
+    dirs = [str(tmp_path / d) for d in ("f", "w", "c")]
+    counters, durations = rs.merge_counters(dirs)
+    text = rs.traffic_summary("ffn_down", fig, counters, [], float(1 << 20), dirs)
+    assert "traffic_bytes_per_launch=%d" % ((3000 + 4000) * 3 * 1024) in text        # both launches of the run, read and written
+    assert "split kernels" in text and "FETCH_SIZE 3000 KiB" in text
+    text = rs.counter_summary("ffn_down", fig, counters, durations, [])
+    assert "gemm_kernel<4, 4, 1, 9, 1, 5> + gemm_kernel<4, 4, 2, 5, 1, 0>" in text
+    assert "1.00 GHz" in text and "70.0 %" in text                                     # (0.8 x 14 + 0.5 x 7) / 21
+    assert rs.STREAMING.search("split_pair_kernel")

@@ -120,7 +120,8 @@ pcmm_status pcmm_run_profiled(const pcmm_plan *plan, const uint64_t *A_dev, uint
  * while they run: code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.
  * Same arguments, same result (bit for bit) and same asynchrony as pcmm_run, but the digit planes of
  * A go to a buffer of PCMM_NOALLOC_SCRATCH_BYTES that is part of the library's device image (every
- * GPU the library runs on holds it until the process ends), not to the plan's own scratch.  The call
+ * GPU the library runs on holds it until the process ends), not to the plan's own scratch.  (K <= 128 with
+ * primes below 2^50 makes no digit planes; the limit below holds for it all the same.)  The call
  * allocates and frees nothing, on the host or on the device.
  *
  * PCMM_EUNSUPPORTED if the plan's digit planes, L * ceil(K/128)*128 * ceil(Ncols/32)*32 * digits

@@ -59,7 +59,36 @@ def test_tiny_workload(gpu_device):
     assert (new == ref).all()
 
 
+@pytest.mark.parametrize("K,L,bits", [(192, 1, 36), (192, 2, 36), (256, 3, 45)])
+def test_largest_digit_planes_that_fill_the_static_buffer(gpu_device, K, L, bits):
+    """More than 128 values of k, so that digit planes are made: one limb, a limb pair, three limbs of six digits."""
+    import torch
+
+    import paper_2601_18511_amd as pkg
+    from oracle import pcmm_oracle
+
+    rng = np.random.default_rng(K + L)
+    limit, D = pkg.pcmm.NOALLOC_SCRATCH_BYTES, -(-bits // 8)
+    ncols_fit = limit // (L * 256 * D) // 32 * 32
+    assert L * 256 * ncols_fit * D <= limit < L * 256 * (ncols_fit + 32) * D
+    W, A, primes = _case(rng, 5, K, ncols_fit, bits, L, 8)
+    ref, new = _both(W, A, primes, bits, gpu_device)
+    assert (new == ref).all(), int((new != ref).sum())
+    assert (new == pcmm_oracle(W, A, primes)).all()
+
+    plan = pkg.pcmm_plan_create(torch.from_numpy(W).to(gpu_device), primes, bits, ncols_fit + 1)
+    A_dev = torch.zeros((L, K, ncols_fit + 1), dtype=torch.int64, device=gpu_device)
+    C_dev = torch.full((L, 5, ncols_fit + 1), -3, dtype=torch.int64, device=gpu_device)
+    with pytest.raises(pkg.PcmmError) as e:
+        pkg.pcmm_run_noalloc(plan, A_dev, C_dev)
+    assert e.value.status == pkg.pcmm.PCMM_EUNSUPPORTED
+    torch.cuda.synchronize()
+    assert bool((C_dev == -3).all())
+    pkg.pcmm_plan_destroy(plan)
+
+
 def test_largest_input_that_fits_and_the_first_that_does_not(gpu_device):
+    """At 128 values of k no digit planes are made; the limit is the documented one all the same."""
     import torch
 
     import paper_2601_18511_amd as pkg

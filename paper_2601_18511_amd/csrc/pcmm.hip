@@ -618,8 +618,12 @@ __global__ __launch_bounds__(WM * 64) void gemm_kernel(GemmArgs a)
 // TC + 1 keeps the column-wise LDS reads off a single bank.
 constexpr int kTransposeWords = 4096;   // words per tile
 constexpr int kTransposeMaxTR = 512;    // most rows per tile (tiles of narrow matrices)
-// NT_LOADS, NT_STORES: cache policy by size (pcmm_host.hpp).
-template <bool NT_LOADS, bool NT_STORES>
+// Stores are non-temporal: the output is written once and not read here (2^16-coefficient polynomials, k = 16: 816 ->
+// 721 us for 2 GiB in, 93 -> 76 us for 256 MiB in, equal from 8 MiB down).  Loads are non-temporal (NT_LOADS) for inputs larger than
+// the 256 MiB last-level cache, where no later pass can find the input there (2 GiB in: 721 -> 685 us; 512 MiB: 175 -> 166 us;
+// 256 MiB: 76 -> 82 us, hence the line).
+constexpr int64_t kLastLevelCacheBytes = (int64_t)256 << 20;
+template <bool NT_LOADS>
 __global__ __launch_bounds__(256) void transpose_u64_kernel(const uint64_t *__restrict__ in, uint64_t *__restrict__ out,
                                                             int64_t R, int64_t C, int lTR, int lTC, int64_t tiles_r,
                                                             int64_t tiles_c)
@@ -650,9 +654,7 @@ __global__ __launch_bounds__(256) void transpose_u64_kernel(const uint64_t *__re
         for (int s = 0; s < 16; ++s) {
             const int idx = threadIdx.x + 256 * s;
             const int c = idx >> lTR, r = idx & (TR - 1);
-            uint64_t *word = &dst[(int64_t)c * R + r];
-            if (NT_STORES) __builtin_nontemporal_store(tile[r * pitch + c], word);
-            else *word = tile[r * pitch + c];
+            __builtin_nontemporal_store(tile[r * pitch + c], &dst[(int64_t)c * R + r]);
         }
         return;
     }
@@ -1138,10 +1140,7 @@ pcmm_status launch_transpose(const uint64_t *in, uint64_t *out, int64_t npoly, i
     if (blocks > 0x7fffffff) return PCMM_EUNSUPPORTED;
     DevGuard dg(device);
     if (!dg.ok) return PCMM_EDEVICE;
-    const int64_t bytes = npoly * R * C * 8;
-    const auto kern = pcmm_host::permutation_nt_loads(bytes)    ? transpose_u64_kernel<true, true>
-                      : pcmm_host::permutation_nt_stores(bytes) ? transpose_u64_kernel<false, true>
-                                                                : transpose_u64_kernel<false, false>;
+    const auto kern = npoly * R * C * 8 > kLastLevelCacheBytes ? transpose_u64_kernel<true> : transpose_u64_kernel<false>;
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), 0, st, in, out, R, C, lTR, lTC, tiles_r,
                        tiles_c);
     return hipGetLastError() == hipSuccess ? PCMM_OK : PCMM_EDEVICE;

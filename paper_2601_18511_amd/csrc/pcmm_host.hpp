@@ -134,18 +134,6 @@ constexpr int tile_mt(int E) { return E <= 5 ? 4 : (E == 6 ? 3 : 2); }
 // 4096 x 16384, two 30-bit limbs 423 -> 433 us, an even count; 2000 x 160 by 160 x 16384, four limbs 400 us either way).
 constexpr bool odd_ksteps(int S, int MT) { return S * MT < 8; }
 
-// Cache policy of the ring permutation for polynomials of `bytes` in all.  The last-level cache holds 256 MiB.
-// Stores are non-temporal where input and output together exceed it.  Below that the parts are still there when the
-// product, or the composition, reads them (cached -> non-temporal stores: decompose and compose 32 MiB 22.7 -> 26.9 us,
-// 128 MiB 79 -> 91; decompose 128 MiB and a product of 64 rows 102 -> 112; the permutation of 32 MiB by itself
-// 11.4 -> 9.5, of 128 MiB 39.1 -> 38.6); above it they are not (192 MiB: decompose and compose 142 -> 134, by itself
-// 70 -> 57; 512 MiB 382 -> 339, 191 -> 167; 2 GiB 1593 -> 1400, 830 -> 691).
-// Loads are non-temporal for inputs larger than the cache by themselves, where no later pass can find the input there (2 GiB:
-// 721 -> 685 us; 512 MiB: 175 -> 166 us; 256 MiB: 76 -> 82 us, hence the line).
-constexpr int64_t kLastLevelCacheBytes = (int64_t)256 << 20;
-constexpr bool permutation_nt_stores(int64_t bytes) { return bytes > kLastLevelCacheBytes / 2; }
-constexpr bool permutation_nt_loads(int64_t bytes) { return bytes > kLastLevelCacheBytes; }
-
 // Everything about a plan that follows from its arguments alone.
 struct Geometry {
     int D, S, E;               // digits per residue, int8 slices of W, accumulators per output

@@ -132,10 +132,6 @@ int main()
     CHECK(balanced_digits(((uint64_t)1 << 62) - 1) == 8);
     CHECK(balanced_digits(((uint64_t)1 << 63) + 5) == 0);
 
-    // ring permutation: cached stores while input and output fit the last-level cache together, cached loads while the input does
-    CHECK(!permutation_nt_stores(32 << 20) && !permutation_nt_stores((int64_t)128 << 20) && permutation_nt_stores(((int64_t)128 << 20) + 8));
-    CHECK(!permutation_nt_loads((int64_t)256 << 20) && permutation_nt_loads(((int64_t)256 << 20) + 8));
-
     // per-limb constants, from the smallest to the largest supported primes
     const uint64_t qs[] = {8388617ull, 16777213ull, 68719403009ull, 68718428161ull, 1125899903827969ull,
                            (((uint64_t)1 << 55) - 55), (((uint64_t)1 << 61) - 1), 4611686018427387847ull, 4611686018326724609ull};

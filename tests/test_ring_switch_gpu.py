@@ -63,28 +63,6 @@ def test_full_size_batch_round_trip_and_samples(gpu_device):
         assert (parts[i].cpu().numpy() == want).all()
 
 
-@pytest.mark.parametrize("npoly,k", [(256, 16), (257, 16), (300, 4096), (512, 2), (513, 2)])
-def test_each_cache_policy(gpu_device, npoly, k):
-    """Either side of 128 MiB (stores) and of 256 MiB (loads): sampled polynomials against the oracle, the rest by the round trip."""
-    import torch
-
-    import paper_2601_18511_amd as pkg
-    from oracle import ring_decompose
-
-    N = 1 << 16
-    g = torch.Generator(device=gpu_device)
-    g.manual_seed(npoly)
-    p = torch.randint(-(1 << 62), 1 << 62, (npoly, N), dtype=torch.int64, device=gpu_device, generator=g)
-    parts = torch.full((npoly, k, N // k), -1, dtype=torch.int64, device=gpu_device)
-    back = torch.full_like(p, -1)
-    pkg.pcmm_ring_decompose(p, parts, N, k)
-    pkg.pcmm_ring_compose(parts, back, N, k)
-    torch.cuda.synchronize()
-    assert torch.equal(back, p)
-    for i in (0, npoly // 2, npoly - 1):
-        assert (parts[i].cpu().numpy() == ring_decompose(p[i].cpu().numpy(), k)).all()
-
-
 def test_bad_arguments_are_status_codes(gpu_device):
     import torch
 

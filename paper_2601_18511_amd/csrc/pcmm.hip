@@ -619,7 +619,11 @@ __global__ __launch_bounds__(WM * 64) void gemm_kernel(GemmArgs a)
 constexpr int kTransposeWords = 4096;   // words per tile
 constexpr int kTransposeMaxTR = 512;    // most rows per tile (tiles of narrow matrices)
 // Stores are non-temporal: the output is written once and not read here (2^16-coefficient polynomials, k = 16: 816 ->
-// 721 us for 2 GiB in, 93 -> 76 us for 256 MiB in, equal from 8 MiB down).  Loads are non-temporal (NT_LOADS) for inputs larger than
+// 721 us for 2 GiB in, 93 -> 76 us for 256 MiB in, equal from 8 MiB down).  The call that reads the parts next pays for it
+// where cached stores would have left them in the last-level cache, and gains where they would have pushed out what it reads
+// (cached -> non-temporal, four sets of buffers in turn: decompose 32 MiB and a product of 128 rows 29.9 -> 31.3 us, 64 MiB
+// and 512 rows 81.6 -> 84.6, 128 MiB and 512 rows 173 -> 171; decompose, product and compose 32 MiB 46.2 -> 46.5, 64 MiB 105
+// and 105, 128 MiB 221 -> 205; the permutation of 64 MiB by itself 24.9 -> 20.2): no line on the size was better over all.  Loads are non-temporal (NT_LOADS) for inputs larger than
 // the 256 MiB last-level cache, where no later pass can find the input there (2 GiB in: 721 -> 685 us; 512 MiB: 175 -> 166 us;
 // 256 MiB: 76 -> 82 us, hence the line).
 constexpr int64_t kLastLevelCacheBytes = (int64_t)256 << 20;

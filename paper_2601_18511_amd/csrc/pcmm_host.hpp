@@ -134,6 +134,25 @@ constexpr int tile_mt(int E) { return E <= 5 ? 4 : (E == 6 ? 3 : 2); }
 // 4096 x 16384, two 30-bit limbs 423 -> 433 us, an even count; 2000 x 160 by 160 x 16384, four limbs 400 us either way).
 constexpr bool odd_ksteps(int S, int MT) { return S * MT < 8; }
 
+// Whether the short-contraction kernel stores C non-temporally: row pitch and address of C, its size, the strips of 64 columns
+// over all limbs and the parts each strip is cut into.
+// Rows that start on 128-byte lines: always; every store writes whole lines.  Rows that start inside a line at any other place
+// than its middle: never; lines are joined in L2, which non-temporal stores prevent (9483 x 128 by 128 x 14636, five 44-bit
+// limbs: cached 1.91 ms, non-temporal 2.62).  Rows that start on half lines: cached stores are better while the memory-side
+// cache still joins the halves, non-temporal ones beyond (cached -> non-temporal: 300 x 64 by 64 x 42936, two limbs, 197 MiB
+// 61 -> 69 us; 768 x 128 by 128 x 14632, five limbs, 429 MiB 187 -> 115; 3000 x 80 by 80 x 42936, two limbs, 1.9 GiB 670 ->
+// 534).  Where that is depends on the raster: strips of two parts cross over at about 224 MiB (194 MiB 95 -> 79, 203 MiB
+// 113 -> 122, 283 MiB 114 -> 71), others above 768 strips at about 400 (294 MiB 79 -> 79, 382 MiB 101 -> 114, 438 MiB
+// 211 -> 152), fewer strips at about 640 (327 MiB 82 -> 89, 569 MiB 153 -> 161, 695 MiB 205 -> 183).  Over 230 shapes of 192 MiB to
+// 2 GiB: 9 % faster than cached stores throughout, 3 % than non-temporal ones, 1 % behind the better of the two each time.
+inline bool shortk_nt_stores(int64_t Ncols, uint64_t c_address, int64_t c_bytes, int64_t strips, int64_t parts)
+{
+    if (Ncols % 16 == 0) return true;
+    if (Ncols % 8 != 0 || c_address % 64 != 0) return false;
+    const int64_t from_mib = parts == 2 ? 224 : strips > 768 ? 416 : 640;
+    return c_bytes > from_mib << 20;
+}
+
 // Everything about a plan that follows from its arguments alone.
 struct Geometry {
     int D, S, E;               // digits per residue, int8 slices of W, accumulators per output

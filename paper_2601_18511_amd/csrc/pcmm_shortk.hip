@@ -48,10 +48,8 @@ struct KArgs {
 // ONCE: one work-group covers all rows of its strip, so every residue is read once: non-temporal loads (64 rows,
 //       131072 columns, four limbs 152 -> 145 us).  With several parts the later ones find the residues in the caches;
 //       non-temporal loads would keep them out (4096 x 128 by 128 x 8192: 74 -> 121 us).
-// LINES: every row of C starts on a 128-byte line, the stores write whole lines and are non-temporal.  Otherwise the
-//       lines that two waves or work-groups share are joined in L2, which non-temporal stores prevent (3001 x 128 by
-//       128 x 65001, two limbs: 1.99 ms non-temporal, 1.13 ms cached).
-template <int D, int S, int MODE, bool ONCE, bool LINES>
+// NT_STORES: shortk_nt_stores in pcmm_host.hpp says when and what both sides measured.
+template <int D, int S, int MODE, bool ONCE, bool NT_STORES>
 __global__ __launch_bounds__(256, D == 7 && S == 2 ? 3 : 4) void gemm_shortk_kernel(KArgs ka)
 {
     constexpr int E = D + S - 1;
@@ -199,7 +197,7 @@ __global__ __launch_bounds__(256, D == 7 && S == 2 ? 3 : 4) void gemm_shortk_ker
 #pragma unroll
         for (int r = 0; r < 4; ++r)
             __builtin_amdgcn_raw_buffer_store_b64((v2u){(uint32_t)res[r], (uint32_t)(res[r] >> 32)}, crs,
-                                                  c_lane + (uint32_t)r * c_rowbytes, 0, LINES ? 2 : 0);
+                                                  c_lane + (uint32_t)r * c_rowbytes, 0, NT_STORES ? 2 : 0);
     };
 
     // ---- stage s is in LDS[s & 1] while stage s+1 travels global -> registers
@@ -229,9 +227,11 @@ template <int D, int S, int MODE>
 void launch_mode(const KArgs &ka, int64_t grid, hipStream_t st)
 {
     const dim3 g((unsigned)grid), b(256);
-    const bool once = ka.mparts == 1, lines = ka.a.Ncols % 16 == 0;
-    const auto kern = once ? (lines ? gemm_shortk_kernel<D, S, MODE, true, true> : gemm_shortk_kernel<D, S, MODE, true, false>)
-                           : (lines ? gemm_shortk_kernel<D, S, MODE, false, true> : gemm_shortk_kernel<D, S, MODE, false, false>);
+    const bool once = ka.mparts == 1;
+    const bool nt = pcmm_host::shortk_nt_stores(ka.a.Ncols, (uint64_t)(uintptr_t)ka.a.C, (int64_t)ka.a.L * ka.a.M * ka.a.Ncols * 8,
+                                                (int64_t)ka.a.L * ka.nstrips, ka.mparts);
+    const auto kern = once ? (nt ? gemm_shortk_kernel<D, S, MODE, true, true> : gemm_shortk_kernel<D, S, MODE, true, false>)
+                           : (nt ? gemm_shortk_kernel<D, S, MODE, false, true> : gemm_shortk_kernel<D, S, MODE, false, false>);
     hipLaunchKernelGGL(kern, g, b, 0, st, ka);
 }
 

@@ -132,6 +132,17 @@ int main()
     CHECK(balanced_digits(((uint64_t)1 << 62) - 1) == 8);
     CHECK(balanced_digits(((uint64_t)1 << 63) + 5) == 0);
 
+    // short contractions: whole lines non-temporal, odd rows cached, rows on half lines by size, only where C itself is on one
+    {
+        const int64_t MiB = 1 << 20;
+        CHECK(shortk_nt_stores(8192, 4096, MiB, 128, 8) && shortk_nt_stores(8192, 4104, MiB, 128, 8));
+        CHECK(!shortk_nt_stores(8196, 4096, 4096 * MiB, 2000, 2) && !shortk_nt_stores(8193, 4096, 4096 * MiB, 2000, 2));
+        CHECK(!shortk_nt_stores(8200, 4096, 224 * MiB, 2000, 2) && shortk_nt_stores(8200, 4096, 224 * MiB + 8, 2000, 2));
+        CHECK(!shortk_nt_stores(8200, 4096, 416 * MiB, 769, 3) && shortk_nt_stores(8200, 4096, 416 * MiB + 8, 769, 3));
+        CHECK(!shortk_nt_stores(8200, 4096, 640 * MiB, 768, 4) && shortk_nt_stores(8200, 4096, 640 * MiB + 8, 768, 4));
+        CHECK(!shortk_nt_stores(8200, 4104, 4096 * MiB, 2000, 2) && shortk_nt_stores(8200, 4160, 4096 * MiB, 2000, 2));
+    }
+
     // per-limb constants, from the smallest to the largest supported primes
     const uint64_t qs[] = {8388617ull, 16777213ull, 68719403009ull, 68718428161ull, 1125899903827969ull,
                            (((uint64_t)1 << 55) - 55), (((uint64_t)1 << 61) - 1), 4611686018427387847ull, 4611686018326724609ull};

@@ -155,6 +155,35 @@ def test_digits_cut_inside_the_short_contraction_kernel(gpu_device, M, K, Ncols,
     pkg.pcmm_plan_destroy(plan)
 
 
+@pytest.mark.parametrize("offset", [0, 1])
+def test_short_contraction_with_rows_on_half_lines(gpu_device, offset):
+    """Rows of C in the middle of 128-byte lines, 235 MiB: non-temporal stores, and cached ones where C itself is off a half line.
+    Sampled rows and columns; every entry is written, nothing beside C is."""
+    import torch
+
+    import paper_2601_18511_amd as pkg
+    from oracle import pcmm_oracle_select
+
+    M, K, Ncols, L, bits = 201, 33, 51208, 3, 36
+    primes = pi.ntt_primes(bits, 1 << 10, L)
+    g = torch.Generator(device=gpu_device)
+    g.manual_seed(3)
+    W = torch.randint(-128, 128, (M, K), dtype=torch.int8, device=gpu_device, generator=g)
+    A = torch.stack([torch.randint(0, q, (K, Ncols), dtype=torch.int64, device=gpu_device, generator=g) for q in primes])
+    guard = torch.full((L * M * Ncols + 512,), -7, dtype=torch.int64, device=gpu_device)
+    C = guard[256 + offset:256 + offset + L * M * Ncols].view(L, M, Ncols)
+    plan = pkg.pcmm_plan_create(W, primes, bits, Ncols)
+    pkg.pcmm_run(plan, A, C)
+    torch.cuda.synchronize()
+    pkg.pcmm_plan_destroy(plan)
+    assert bool((guard[:256 + offset] == -7).all()) and bool((guard[256 + offset + L * M * Ncols:] == -7).all())
+    assert bool((C >= 0).all())
+    W_host, A_host, C_host = W.cpu().numpy(), A.cpu().numpy().view(np.uint64), C.cpu().numpy().view(np.uint64)
+    rows, cols = [0, 1, 64, 127, 128, M - 1], list(range(0, 40)) + list(range(25592, 25640)) + list(range(Ncols - 40, Ncols))
+    assert (C_host[:, rows, :] == pcmm_oracle_select(W_host, A_host, primes, rows, np.arange(Ncols))).all()
+    assert (C_host[:, :, cols] == pcmm_oracle_select(W_host, A_host, primes, np.arange(M), cols)).all()
+
+
 @pytest.mark.parametrize(
     "M,K,Ncols,bits,L,wbits",
     [

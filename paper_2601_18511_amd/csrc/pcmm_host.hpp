@@ -233,23 +233,23 @@ inline pcmm_status plan_geometry(int64_t M, int64_t K, int64_t Ncols, int32_t L,
     // with pair_ntiles <= 2 ntiles, are never more than the 10 * 2 ntiles of two single limbs, so ad_bytes covers them.
     // Contractions of at most 128 values of k keep single limbs: their kernel holds a limb's digits in registers.
     // An odd number of limbs leaves one that runs singly, in launches of its own behind those of the pairs: two starts and
-    // two last rounds of work-groups.  That costs 10 to 30 us and pays from about 2 10^10 products a limb on, a line chosen
-    // over 290 shapes of 200 to 13629 rows (0.5 % behind the better of the two on average, 8 % at worst).  pcmm_run, all
-    // three limbs singly -> a pair and one single: 100 x 192 by 192 x 8192 25 -> 37 us; 1000 x 400 by 400 x 8192 106 -> 114;
-    // 2048 x 672 by 672 x 4096 118 -> 134; 4096 x 1000 by 1000 x 4096 269 -> 274; 6000 x 1000 by 1000 x 4096 (2.5 10^10)
-    // 383 -> 386; 4096 x 672 by 672 x 8192 449 -> 433; 9344 x 2611 by 2611 x 4096 1235 -> 1202; 4096 x 4096 by 4096 x 8192
-    // 1726 -> 1674.
+    // two last rounds of work-groups.  That costs 10 to 30 us and pays from about 2.5 10^10 products a limb on, the digit split
+    // counted as 600 rows (a line chosen over 290 shapes of 200 to 13629 rows: 0.4 % behind the better of the two on average,
+    // 10 % at worst).  pcmm_run, all three limbs singly -> a pair and one single: 100 x 192 by 192 x 8192 25 -> 37 us; 1000 x
+    // 400 by 400 x 8192 106 -> 114; 2048 x 672 by 672 x 4096 118 -> 134; 4096 x 1000 by 1000 x 4096 269 -> 274; 200 x 2611 by
+    // 2611 x 16384 465 -> 467; 6000 x 1000 by 1000 x 4096 383 -> 386; 200 x 9000 by 9000 x 8192 828 -> 785; 4096 x 672 by 672 x
+    // 8192 449 -> 433; 9344 x 2611 by 2611 x 4096 1235 -> 1202; 4096 x 4096 by 4096 x 8192 1726 -> 1674.
     // Rows of C that start inside a 128-byte line: every n-tile shares a line with its neighbour, and a pair's tiles are half as
     // wide.  With more than 16 m-tiles, where the raster below cannot make up for it, pairs then pay beyond 768 values of k
     // only (singly -> pairs, two limbs, 12301 columns: 9000 x 192 by 192 623 -> 675 us; 6000 x 512 607 -> 635; 6000 x 768
     // 739 -> 756; 6000 x 1000 863 -> 868; 6000 x 1500 1124 -> 1102; up to 16 m-tiles 2048 x 192 156 -> 161, 4096 x 400
     // 403 -> 403, 1000 x 1000 232 -> 218).
-    constexpr int64_t kOddLimbsProducts = 20000000000;
+    constexpr int64_t kOddLimbsProducts = 25000000000, kSplitRows = 600;
     const bool shared_lines = Ncols % 16 != 0 && g->mtiles > 16 && K <= 768;
     g->pair_ntiles = (Ncols + 15) / 16;
     g->pairs = 0;
     if (S == 1 && D == 5 && g->nkb > 2 && (uint64_t)g->pair_ntiles * g->nkb * kPairDigits * kFragBytes < ((uint64_t)1 << 32) &&
-        !shared_lines && (L % 2 == 0 || M * K * Ncols >= kOddLimbsProducts)) {   // M * K < 2^31 (wp_bytes), so the product fits
+        !shared_lines && (L % 2 == 0 || (M + kSplitRows) * K * Ncols >= kOddLimbsProducts)) {   // M * K < 2^31 (wp_bytes): the product fits
         g->pairs = L / 2;
         for (int j = 0; j < L / 2; ++j)
             if (!pair_ok(primes_host[2 * j], primes_host[2 * j + 1])) g->pairs = 0;

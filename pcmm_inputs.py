@@ -123,7 +123,7 @@ class Workload:
     def limb_pairs(self) -> int:
         """Pairs of limbs that the library splits jointly, nine digits a pair (the rule of csrc/pcmm_host.hpp for these workloads)."""
         five_digits = self.w_bits == 8 and 0x7F7F7F80 < max(self.primes) < 1 << 36
-        worth_it = self.L % 2 == 0 or self.M * self.K * self.Ncols >= 20 * 10 ** 9
+        worth_it = self.L % 2 == 0 or (self.M + 600) * self.K * self.Ncols >= 25 * 10 ** 9
         return self.L // 2 if five_digits and self.K > 128 and worth_it else 0
 
     @property

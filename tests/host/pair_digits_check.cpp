@@ -89,10 +89,10 @@ int main()
         }
     CHECK(plan_geometry(300, 128, 100, 2, q36, 36, 8, 0, &g) == PCMM_OK && g.pairs == 0);      // short contraction
     CHECK(plan_geometry(300, 300, 100, 2, q36, 36, 16, 0, &g) == PCMM_OK && g.pairs == 0);     // two weight slices
-    // an odd number of limbs pairs from 2 10^10 products a limb on, and the scratch covers the pairs and the single limb
-    CHECK(plan_geometry(5000, 1000, 3999, 3, q36, 36, 8, 0, &g) == PCMM_OK && g.pairs == 0);
-    CHECK(plan_geometry(5000, 1000, 4000, 1, q36, 36, 8, 0, &g) == PCMM_OK && g.pairs == 0);
-    for (int64_t nc : {4000, 4016, 4017, 4033, 32768})
+    // an odd number of limbs pairs from 2.5 10^10 products a limb on (600 rows more than M), and the scratch covers the pairs and the single limb
+    CHECK(plan_geometry(5000, 1000, 4464, 3, q36, 36, 8, 0, &g) == PCMM_OK && g.pairs == 0);
+    CHECK(plan_geometry(5000, 1000, 4465, 1, q36, 36, 8, 0, &g) == PCMM_OK && g.pairs == 0);
+    for (int64_t nc : {4465, 4480, 4481, 4497, 32768})
         for (int32_t L : {3, 5}) {
             CHECK(plan_geometry(5000, 1000, nc, L, q36, 36, 8, 0, &g) == PCMM_OK && g.pairs == L / 2);
             CHECK((size_t)g.nkb * kFragBytes * (g.pairs * g.pair_ntiles * kPairDigits + g.ntiles * g.NT * g.D) <= g.ad_bytes);

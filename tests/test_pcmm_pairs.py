@@ -89,7 +89,7 @@ def test_paired_limbs_bit_exact(gpu_device, M, K, Ncols, bits, L, ascending, ext
 
 @pytest.mark.gpu
 def test_pairs_and_a_single_limb(gpu_device):
-    """Three limbs of 2 10^10 products each: the first two as a pair, the last one singly; ragged rows, columns and k, sampled."""
+    """Three limbs of 2 10^10 products each, enough for pairs: the first two as a pair, the last one singly; ragged rows, columns and k, sampled."""
     import torch
 
     import paper_2601_18511_amd as pkg

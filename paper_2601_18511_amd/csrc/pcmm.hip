@@ -623,9 +623,9 @@ constexpr int kTransposeMaxTR = 512;    // most rows per tile (tiles of narrow m
 // where cached stores would have left them in the last-level cache, and gains where they would have pushed out what it reads
 // (cached -> non-temporal, four sets of buffers in turn: decompose 32 MiB and a product of 128 rows 29.9 -> 31.3 us, 64 MiB
 // and 512 rows 81.6 -> 84.6, 128 MiB and 512 rows 173 -> 171; decompose, product and compose 32 MiB 46.2 -> 46.5, 64 MiB 105
-// and 105, 128 MiB 221 -> 205; the permutation of 64 MiB by itself 24.9 -> 20.2): no line on the size was better over all.  Loads are non-temporal (NT_LOADS) for inputs larger than
-// the 256 MiB last-level cache, where no later pass can find the input there (2 GiB in: 721 -> 685 us; 512 MiB: 175 -> 166 us;
-// 256 MiB: 76 -> 82 us, hence the line).
+// and 105, 128 MiB 221 -> 205; the permutation of 64 MiB by itself 24.9 -> 20.2): no line on the size was better over all.
+// Loads are non-temporal (NT_LOADS) for inputs larger than the 256 MiB last-level cache, where no later pass can find the
+// input there (2 GiB in: 721 -> 685 us; 512 MiB: 175 -> 166 us; 256 MiB: 76 -> 82 us, hence the line).
 constexpr int64_t kLastLevelCacheBytes = (int64_t)256 << 20;
 template <bool NT_LOADS>
 __global__ __launch_bounds__(256) void transpose_u64_kernel(const uint64_t *__restrict__ in, uint64_t *__restrict__ out,

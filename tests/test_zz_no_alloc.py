@@ -2,7 +2,7 @@
 
 Both entry points run the same kernels; they differ in where the digit planes of A go (the plan's own
 scratch, or the library's static buffer).  The bar is the one of every PCMM parity test: bit-exact.
-This file is collected last on purpose: the round's GPU run stops at the first failure.
+This file is collected last on purpose: a GPU run stops at the first failure.
 """
 import numpy as np
 import pytest

@@ -296,8 +296,14 @@ struct GemmArgs {
 // Measured (pcmm_run, before -> after): 1000 x 777 by 777 x 12300, three 45-bit limbs 333 -> 319 us; 2100 x 160 by
 // 160 x 16384, four 36-bit limbs 377 -> 334 us; 300 x 4160 by 4160 x 16384, two limbs 553 -> 526 us; 3000 x 320 by
 // 320 x 16384, int16 W, two 55-bit limbs 729 -> 687 us; whole tiles and even counts equal (4096 x 4096: 8.69 and 8.70 ms).
-template <int WM, int MT, int NT, int D, int S, int EPI>
-__global__ __launch_bounds__(WM * 64) void gemm_kernel(GemmArgs a)
+//
+// ALONE: one wave on a SIMD (the descriptor asks for more than 256 registers; the code is the same).  A second two-wave
+// work-group of a compute unit otherwise lands on the SIMDs of the first while the two others idle.  Launches of at most two
+// work-groups a compute unit take this variant (shared -> alone: 64 x 96 by 96 x 4332, int16 W, two 60-bit limbs, 272
+// work-groups 22.1 -> 18.7 us; 64 x 300 by 300 x 8192, two 56-bit limbs, 512 work-groups 29.3 -> 27.2; 1024 work-groups,
+// 64 x 96 by 96 x 16384 31.6 -> 34.6, hence the line).
+template <int WM, int MT, int NT, int D, int S, int EPI, bool ALONE = false>
+__global__ __launch_bounds__(WM * 64) __attribute__((amdgpu_waves_per_eu(1, ALONE ? 1 : 8))) void gemm_kernel(GemmArgs a)
 {
     constexpr int E = D + S - 1;
     constexpr int T = WM * 64;
@@ -785,23 +791,35 @@ int64_t pair_digit_bytes(const pcmm_plan *p)
     return p->pairs * p->nkb * p->pair_ntiles * (int64_t)(pcmm_host::kPairDigits * kFrag);
 }
 
+template <int WM, int MT, int NT, int D, int S, int EPI>
+void launch_alone_or_not(const GemmArgs &ga, dim3 g, hipStream_t st)
+{
+    if constexpr (WM == 2) {
+        if (ga.total <= 2 * 256) {               // two for each of 256 compute units
+            hipLaunchKernelGGL((gemm_kernel<WM, MT, NT, D, S, EPI, true>), g, dim3(WM * 64), 0, st, ga);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((gemm_kernel<WM, MT, NT, D, S, EPI>), g, dim3(WM * 64), 0, st, ga);
+}
+
 template <int WM, int MT, int NT, int D, int S>
 hipError_t launch_gemm_ds(const pcmm_plan *p, const GemmArgs &ga, int64_t grid, hipStream_t st)
 {
-    const dim3 g((unsigned)grid), b(WM * 64);
+    const dim3 g((unsigned)grid);
     // 50-bit primes need at least 7 digits and 7-digit primes can be below 2^50: D <= 6 always takes
     // the double-precision epilogue, D = 8 never does
     if (p->epi == EPI_F64) {
-        if constexpr (D <= 7) hipLaunchKernelGGL((gemm_kernel<WM, MT, NT, D, S, EPI_F64>), g, b, 0, st, ga);
+        if constexpr (D <= 7) launch_alone_or_not<WM, MT, NT, D, S, EPI_F64>(ga, g, st);
         else return hipErrorInvalidValue;
     } else if (p->epi == EPI_F64_G4 || p->epi == EPI_F64_G4P) {
         if constexpr (D <= 7 && D + S - 1 >= 7) {
-            if (p->epi == EPI_F64_G4) hipLaunchKernelGGL((gemm_kernel<WM, MT, NT, D, S, EPI_F64_G4>), g, b, 0, st, ga);
-            else hipLaunchKernelGGL((gemm_kernel<WM, MT, NT, D, S, EPI_F64_G4P>), g, b, 0, st, ga);
+            if (p->epi == EPI_F64_G4) launch_alone_or_not<WM, MT, NT, D, S, EPI_F64_G4>(ga, g, st);
+            else launch_alone_or_not<WM, MT, NT, D, S, EPI_F64_G4P>(ga, g, st);
         } else return hipErrorInvalidValue;
     } else {
         if constexpr (D >= 7) {
-            hipLaunchKernelGGL((gemm_kernel<WM, MT, NT, D, S, EPI_INT>), g, b, 0, st, ga);
+            launch_alone_or_not<WM, MT, NT, D, S, EPI_INT>(ga, g, st);
         } else return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -890,7 +908,7 @@ hipError_t launch_products(const pcmm_plan *p, GemmArgs ga, bool pair, hipStream
     if (p->MT != 4 || p->S != 1) return hipErrorInvalidValue;
     constexpr int PD = pcmm_host::kPairDigits;
     if (p->WM == 4) hipLaunchKernelGGL((gemm_kernel<4, 4, 1, PD, 1, EPI_F64_PAIR>), dim3((unsigned)grid), dim3(256), 0, st, ga);
-    else hipLaunchKernelGGL((gemm_kernel<2, 4, 1, PD, 1, EPI_F64_PAIR>), dim3((unsigned)grid), dim3(128), 0, st, ga);
+    else launch_alone_or_not<2, 4, 1, PD, 1, EPI_F64_PAIR>(ga, dim3((unsigned)grid), st);
     return hipGetLastError();
 }
 

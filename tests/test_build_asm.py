@@ -94,3 +94,9 @@ def test_two_wave_kernels_keep_two_waves_on_a_simd(device_asm):
     assert len(small) >= 15
     for k, (agpr, total) in small.items():
         assert total <= (260 if "ILi2ELi4ELi2ELi4ELi2E" in k else 256), (k, agpr, total)
+    # the variant for launches of at most two work-groups a compute unit reserves more, so that it has its SIMD to itself
+    reserved = {m.group(1): int(m.group(2)) for m in
+                re.finditer(r"\.amdhsa_kernel (\S*gemm_kernelILi2E\S+).*?\.amdhsa_next_free_vgpr (\d+)", device_asm, re.S)}
+    assert set(reserved) == set(small)
+    for k, n in reserved.items():
+        assert ("ELb1EEEv" in k) == (n > 256) or "ILi2ELi4ELi2ELi4ELi2E" in k, (k, n)

@@ -222,6 +222,10 @@ def test_odd_counts_of_ksteps_and_waves_of_padding(gpu_device, M, K, Ncols, bits
         (40, 257, 17, 45, 3, 8),          # five k-steps, the second wave all padding
         (64, 130944 + 130, 16, 38, 1, 8), # the second launch contracts three k-steps and adds to C
         (300, 130944 + 130, 16, 45, 1, 8),
+        (40, 192, 16385, 38, 1, 8),       # 513 work-groups: two waves may share a SIMD (at most 512 above: they may not)
+        (64, 130, 16384, 62, 1, 16),      # 512 work-groups
+        (64, 130, 16400, 50, 1, 16),
+        (100, 200, 8200, 36, 2, 8),       # 513 work-groups of a limb pair
     ],
 )
 def test_odd_counts_of_ksteps_in_two_wave_work_groups(gpu_device, M, K, Ncols, bits, L, wbits):

@@ -77,8 +77,8 @@ pcmm_status pcmm_plan_create(pcmm_plan **out, int64_t M, int64_t K, int64_t Ncol
 /*
  * Device bytes the plan owns: the converted weights (1 or 2 bytes per entry of W, where the paper's
  * converted PCMM tiles take 8, Section 5.3 and Table "model-conversion-memory"), the digit scratch of
- * one run (digits bytes per residue of A; none for K <= 128 and primes below 2^50, which run as one
- * kernel) and the per-limb constants.  0 for NULL.
+ * one run (digits bytes per residue of A; none for contractions that run as one kernel, which cuts the
+ * digits itself: K <= 128 and primes below 2^50, and most K up to 1000 to 2000) and the per-limb constants.  0 for NULL.
  */
 size_t pcmm_plan_workspace_bytes(const pcmm_plan *plan);
 
@@ -109,8 +109,8 @@ pcmm_status pcmm_run(const pcmm_plan *plan, const uint64_t *A_dev, uint64_t *C_d
 
 /*
  * Same operation as pcmm_run (Section 5.1, B = W.A), but brackets each kernel with HIP events on `stream`, synchronises, and
- * reports the kernel durations in milliseconds: ms_out[0] = digit-split kernel (next to nothing for K <= 128 and primes
- * below 2^50: the one kernel that runs cuts the digits itself), ms_out[1] = MFMA + epilogue kernel (all its launches together when K is cut into ranges).  ms_out is a host array of 2 floats.  For measurement harnesses.
+ * reports the kernel durations in milliseconds: ms_out[0] = digit-split kernel (next to nothing for
+ * contractions that run as one kernel, which cuts the digits itself), ms_out[1] = MFMA + epilogue kernel (all its launches together when K is cut into ranges).  ms_out is a host array of 2 floats.  For measurement harnesses.
  */
 pcmm_status pcmm_run_profiled(const pcmm_plan *plan, const uint64_t *A_dev, uint64_t *C_dev,
                               void *stream, float *ms_out);
@@ -120,8 +120,8 @@ pcmm_status pcmm_run_profiled(const pcmm_plan *plan, const uint64_t *A_dev, uint
  * while they run: code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.
  * Same arguments, same result (bit for bit) and same asynchrony as pcmm_run, but the digit planes of
  * A go to a buffer of PCMM_NOALLOC_SCRATCH_BYTES that is part of the library's device image (every
- * GPU the library runs on holds it until the process ends), not to the plan's own scratch.  (K <= 128 with
- * primes below 2^50 makes no digit planes; the limit below holds for it all the same.)  The call
+ * GPU the library runs on holds it until the process ends), not to the plan's own scratch.  (Contractions
+ * that run as one kernel make no digit planes; the limit below holds for them all the same.)  The call
  * allocates and frees nothing, on the host or on the device.
  *
  * PCMM_EUNSUPPORTED if the plan's digit planes, L * ceil(K/128)*128 * ceil(Ncols/32)*32 * digits

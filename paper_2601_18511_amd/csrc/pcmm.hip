@@ -9,7 +9,8 @@
 //                                integer of nine digits)
 //   gemm_kernel     (every run)  v_mfma_i32_16x16x64_i8 main loop, then recombination of the digit
 //                                accumulators and reduction modulo q_j
-//   (contractions of at most 128 values of k run as one kernel, pcmm_shortk.hip)
+//   (contractions of at most 128 values of k run as one kernel, pcmm_shortk.hip, and so do those whose digits fit LDS,
+//   pcmm_resident.hip)
 // Beside it:
 //   transpose_u64_kernel         the coefficient permutation of ring switching (Section 3.3)
 //   mfma_probe_kernel            measurement aid: what the matrix cores sustain without memory traffic
@@ -29,6 +30,7 @@
 #include "../../include/pcmm.h"
 #include "pcmm_host.hpp"
 #include "pcmm_device.hpp"
+#include "pcmm_resident.hpp"
 #include "pcmm_shortk.hpp"
 #include "pcmm_hip_util.hpp"
 
@@ -584,26 +586,7 @@ __global__ __launch_bounds__(WM * 64) __attribute__((amdgpu_waves_per_eu(1, ALON
             } else if constexpr (EPI == EPI_F64_G4P) {
                 reduce_f64<E, 2, 4>(avs, lc.qd, lc.invq, res);
             } else {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    // value = vlo + 2^32 vhi (+ 2^64 vtop for a ninth accumulator), each part of magnitude < 2^56
-                    int64_t vlo = 0, vhi = 0;
-#pragma unroll
-                    for (int e = 0; e < (E < 8 ? E : 8); ++e) {
-                        int64_t v = (int64_t)avs[r][e];
-                        if (e < 4) vlo += v << (8 * e);
-                        else vhi += v << (8 * (e - 4));
-                    }
-                    uint64_t rlo = barrett_u64((uint64_t)vlo + lc.off, lc.q, lc.mu);
-                    uint64_t rhi = barrett_u64((uint64_t)vhi + lc.off, lc.q, lc.mu);
-                    res[r] = rlo + mulmod_shoup(rhi, lc.c32, lc.c32s, lc.q);
-                    if (res[r] >= lc.q) res[r] -= lc.q;
-                    if constexpr (E == 9) {
-                        uint64_t rtop = barrett_u64((uint64_t)(int64_t)avs[r][8] + lc.off, lc.q, lc.mu);
-                        res[r] += mulmod_shoup(rtop, lc.c64, lc.c64s, lc.q);
-                        if (res[r] >= lc.q) res[r] -= lc.q;
-                    }
-                }
+                reduce_int<E, 4>(avs, lc, res);
             }
             store_block(crs, c_lane, res, lc.q, accumulate_c);
         }
@@ -751,6 +734,7 @@ struct pcmm_plan {
     size_t bytes;
     size_t ad_bytes;         // size of the digit planes of one run (pcmm_run_noalloc's limit)
     bool shortk;             // at most 128 values of k: pcmm_shortk runs, which needs no digit scratch
+    pcmm_host::ResidentTile resident;   // NT > 0: pcmm_resident runs, which needs none either
     int pairs;               // limb pairs whose digits are split jointly; limbs from 2 * pairs on run singly
     int64_t pair_ntiles;     // n-tiles (16 columns) of a pair
     int gn, pair_gn;         // n-tiles per raster group
@@ -919,7 +903,7 @@ pcmm_status run_impl(const pcmm_plan *p, int8_t *Ad, const uint64_t *A, uint64_t
     if (!dg.ok) return PCMM_EDEVICE;
 
     if (ms && hipEventRecord(p->ev[0], st) != hipSuccess) return PCMM_EDEVICE;
-    if (!p->shortk && launch_split(p, Ad, A, st) != hipSuccess) return PCMM_EDEVICE;
+    if (!p->shortk && !p->resident.NT && launch_split(p, Ad, A, st) != hipSuccess) return PCMM_EDEVICE;
     if (ms && (hipEventRecord(p->ev[1], st) != hipSuccess || hipEventRecord(p->ev[2], st) != hipSuccess))
         return PCMM_EDEVICE;
     if (p->shortk) {
@@ -929,6 +913,14 @@ pcmm_status run_impl(const pcmm_plan *p, int8_t *Ad, const uint64_t *A, uint64_t
         sa.M = p->M; sa.K = p->K; sa.Ncols = p->Ncols; sa.MB = p->MB;
         sa.L = p->L;
         if (pcmm_shortk::launch(sa, p->D, p->S, p->epi, st) != hipSuccess) return PCMM_EDEVICE;
+    } else if (p->resident.NT) {
+        // the digits of the whole contraction fit LDS
+        pcmm_resident::Args ra;
+        ra.Wp = p->Wp; ra.A = A; ra.C = C; ra.lc = p->lc;
+        ra.M = p->M; ra.K = p->K; ra.Ncols = p->Ncols; ra.MB = p->MB;
+        ra.nkb = (int)p->nkb;
+        ra.L = p->L;
+        if (pcmm_resident::launch(ra, p->resident, p->D, p->S, p->epi, st) != hipSuccess) return PCMM_EDEVICE;
     } else {
         GemmArgs ga = {};
         ga.Wp = p->Wp;
@@ -995,6 +987,7 @@ pcmm_status pcmm_plan_create(pcmm_plan **out, int64_t M, int64_t K, int64_t Ncol
     p->WM = g.WM; p->MT = g.MT; p->NT = g.NT;
     p->epi = g.epi;
     p->shortk = pcmm_shortk::covers(g.D, g.S, g.epi, g.nkb);
+    p->resident = g.resident;
     p->MB = g.MB; p->nkb = g.nkb; p->mtiles = g.mtiles; p->ntiles = g.ntiles;
     p->nkb_launch = g.nkb_launch;
     p->ksteps = g.ksteps;
@@ -1010,7 +1003,7 @@ pcmm_status pcmm_plan_create(pcmm_plan **out, int64_t M, int64_t K, int64_t Ncol
     // set-up for pcmm_run_noalloc: this device's address of the static digit scratch, asked for once
     if (!static_scratch_ptr(device)) { delete p; return PCMM_EDEVICE; }
 
-    const size_t wp_bytes = g.wp_bytes, ad_bytes = p->shortk ? 0 : g.ad_bytes;   // scratch the plan owns
+    const size_t wp_bytes = g.wp_bytes, ad_bytes = p->shortk || p->resident.NT ? 0 : g.ad_bytes;   // scratch the plan owns
     const size_t lc_bytes = (size_t)L * sizeof(LimbConst);
     int *err_dev = nullptr;
     pcmm_status rc = PCMM_OK;

@@ -241,6 +241,32 @@ __device__ __forceinline__ void reduce_f64_pair(const int (&a)[R][E], double q1,
     horner_f64<G, 0, R>(c, q2, invq2, res2);
 }
 
+// (sum_e a[e] 256^e) mod q for any q < 2^62 in integers: the value is vlo + 2^32 vhi (+ 2^64 vtop for a ninth
+// accumulator), each part of magnitude < 2^56, made positive by lc.off, reduced and joined by Shoup multiplications.
+template <int E, int R>
+__device__ __forceinline__ void reduce_int(const int (&a)[R][E], const LimbConst &lc, uint64_t (&res)[R])
+{
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        int64_t vlo = 0, vhi = 0;
+#pragma unroll
+        for (int e = 0; e < (E < 8 ? E : 8); ++e) {
+            const int64_t v = (int64_t)a[r][e];
+            if (e < 4) vlo += v << (8 * e);
+            else vhi += v << (8 * (e - 4));
+        }
+        const uint64_t rlo = barrett_u64((uint64_t)vlo + lc.off, lc.q, lc.mu);
+        const uint64_t rhi = barrett_u64((uint64_t)vhi + lc.off, lc.q, lc.mu);
+        res[r] = rlo + mulmod_shoup(rhi, lc.c32, lc.c32s, lc.q);
+        if (res[r] >= lc.q) res[r] -= lc.q;
+        if constexpr (E == 9) {
+            const uint64_t rtop = barrett_u64((uint64_t)(int64_t)a[r][8] + lc.off, lc.q, lc.mu);
+            res[r] += mulmod_shoup(rtop, lc.c64, lc.c64s, lc.q);
+            if (res[r] >= lc.q) res[r] -= lc.q;
+        }
+    }
+}
+
 }  // namespace pcmm_device
 
 #endif  // PCMM_DEVICE_HPP

@@ -153,6 +153,79 @@ inline bool shortk_nt_stores(int64_t Ncols, uint64_t c_address, int64_t c_bytes,
     return c_bytes > from_mib << 20;
 }
 
+// ---- the kernel that keeps the digits of a whole contraction in LDS (pcmm_resident.hip)
+constexpr int64_t kLdsBytes = 160 * 1024;   // of a compute unit
+struct ResidentTile {
+    int NT;                // 16-column fragments per strip; 0: this kernel does not run
+    int MT;                // 16-row blocks a wave takes at a time
+    int waves;             // per work-group: 4 (two work-groups a compute unit, at most half of LDS each) or 8
+    int groups_per_part;   // groups of MT row blocks per work-group
+};
+// 16-row blocks a wave takes at a time: 4 MT NT E accumulation registers, 4 MT S for each set of W fragments, 4 D for digits
+constexpr int resident_mt(int D, int S, int NT)
+{
+    if (NT == 2) return S == 1 && D <= 5 ? 4 : 3;
+    return S == 1 ? 4 : 3;
+}
+// k-steps by which W fragments are requested ahead of their use: what fits 256 registers without spills, at most three (two
+// from seven digits on, whose contractions may have two k-steps only)
+constexpr int resident_ahead(int D, int S, int NT, int MT)
+{
+    const int E = D + S - 1, most = E >= 7 ? 2 : 3;
+    const int ahead = (226 - 4 * MT * NT * E - 4 * D - 4 * MT * S) / (4 * MT * S);
+    return ahead > most ? most : ahead < 1 ? 1 : ahead;
+}
+// k-steps that are cut and contracted
+inline int64_t resident_ksteps(int64_t K) { return K > 64 ? (K + 63) / 64 : 2; }
+
+// Whether C is stored non-temporally.  Rows on half lines of 128 bytes: always (1000 x 777 by 777 x 12288, three 45-bit limbs
+// 207 -> 179 us; 4096 x 500 by 500 x 8192, four 36-bit limbs 412 -> 317).  At other places lines are shared with the neighbouring
+// strip and cached stores join them in L2 (over 860 shapes non-temporal ones 15 to 30 % slower), except on quarter lines from 60
+// products a 16 x 16 block on, where the strips drift apart before they could be joined (1000 x 777 by 777 x 12300 236 -> 217;
+// over 190 shapes 0 to 6 % faster).
+inline bool resident_nt_stores(int64_t K, int64_t Ncols, uint64_t c_address, int D, int S)
+{
+    const uint64_t at = (uint64_t)Ncols * 8 | c_address;
+    return at % 64 == 0 || (at % 32 == 0 && resident_ksteps(K) * D * S >= 60);
+}
+
+// The tile for C = W A of L limbs, or NT = 0 where none fits.  The candidates are the strip widths, work-group sizes and numbers of row parts that fit; the estimate, per work-group, is a
+// start, the digits that each wave cuts, and the rounds of row groups each wave runs (MFMAs of two waves sharing a SIMD, and the
+// epilogue), times the rounds of work-groups, a last partial round counting 0.4 of a full one; strips of 16 columns count
+// 15 % more, since each output row is stored in pieces half as long.  The constants are a fit to 2600 shapes (129 to 2048 values
+// of k, all digit counts); the tile it picks is 1 % behind the fastest candidate on average.  (Limb pairs, nine digits for two limbs, were candidates too and gained
+// nothing here: a tenth of the MFMAs less, but two reductions of nine accumulators for every output pair.)
+inline ResidentTile resident_tile(int64_t M, int64_t K, int64_t Ncols, int64_t L, int D, int S)
+{
+    ResidentTile best = {0, 0, 0, 0};
+    double best_clocks = 0.0;
+    const int64_t ks = resident_ksteps(K);
+    const int E = D + S - 1;
+    for (int NT = 2; NT >= 1; --NT) {
+        if (NT == 2 && E > 6) continue;          // no registers for two column fragments
+        const int64_t lds = ks * NT * D * kFragBytes;
+        if (lds > kLdsBytes) continue;
+        const int MT = resident_mt(D, S, NT);
+        const int64_t groups = (M + 16 * MT - 1) / (16 * MT), strips = L * ((Ncols + 16 * NT - 1) / (16 * NT));
+        const double mfma = 16.0 * ks * MT * NT * D * S, epilogue = MT * NT * (32.0 * E + 360.0);
+        for (int waves = 4; waves <= 8; waves += 4) {
+            if (waves == 4 && lds > kLdsBytes / 2) continue;
+            const int64_t slots = waves == 4 ? 512 : 256;
+            for (int64_t p = 1; p <= 8 && p <= groups; ++p) {
+                const int64_t per_part = (groups + p - 1) / p, wgs = strips * ((groups + per_part - 1) / per_part);
+                if (wgs > 0x7fffff00LL) continue;
+                const double wg = 2300.0 + 1400.0 * ks * NT / waves + (double)((per_part + waves - 1) / waves) * (3.1 * mfma + epilogue);
+                const double full = (double)wgs / slots, rounds = 0.4 * (double)((wgs + slots - 1) / slots) + 0.6 * (full > 1.0 ? full : 1.0);
+                const double t = rounds * wg * (NT == 1 ? 1.15 : 1.0);
+                if (best.NT && t >= best_clocks) continue;
+                best_clocks = t;
+                best.NT = NT; best.MT = MT; best.waves = waves; best.groups_per_part = (int)per_part;
+            }
+        }
+    }
+    return best;
+}
+
 // Everything about a plan that follows from its arguments alone.
 struct Geometry {
     int D, S, E;               // digits per residue, int8 slices of W, accumulators per output
@@ -168,6 +241,7 @@ struct Geometry {
     int pairs;                 // limb pairs split jointly (0 or L / 2)
     int64_t pair_ntiles;       // n-tiles of 16 columns
     int gn, pair_gn;           // n-tiles per raster group of the GEMM kernel, for single limbs and for pairs
+    ResidentTile resident;     // NT > 0: the whole contraction fits LDS and runs as one kernel
     uint32_t w_kstride;        // bytes between k-steps of one packed W slice
     uint32_t a_kstride;        // bytes between k-steps of one limb's digit chunks
 };
@@ -265,6 +339,19 @@ inline pcmm_status plan_geometry(int64_t M, int64_t K, int64_t Ncols, int32_t L,
     // 14336 x 8192, five limbs 9147 -> 9654).
     g->gn = 8;
     g->pair_gn = g->mtiles <= 16 && K <= 2048 ? 16 : 8;
+
+    // Contractions whose digits fit LDS run as one kernel that cuts the digits itself (those of at most 128 values of k below
+    // 2^50 as pcmm_shortk's).  Measured over 2200 shapes of 129 to 2048 values of k against digit split and GEMM kernel: 1.43 times
+    // as fast on average, none slower (128 x 384 by 384 x 4096, two limbs 22 -> 10 us; 4096 x 500 by 500 x 8192, four limbs
+    // 467 -> 311; 9536 x 1454 by 1454 x 8192, two limbs 1000 -> 948), but for two cases that keep the old kernels:
+    // rows of C that start inside half lines, where the GEMM kernel's raster joins lines better once there are many rows (14093 x
+    // 475 by 475 x 19613 714 -> 900 us; 960 x 704 by 704 x 2937, int16 W 65 -> 69; up to 512 rows 1.47 times as fast); and the
+    // integer epilogue of int16 W with few rows (64 x 832 by 832 x 16384, four 58-bit limbs 5 % slower).
+    g->resident = ResidentTile{0, 0, 0, 0};
+    const bool shortk = g->nkb == 2 && D <= 7 && g->epi != epi::EPI_INT;
+    const bool inside_half_lines = Ncols % 8 != 0 && !(M <= 512 || (S == 1 && M <= 2048 && K <= 1024));
+    if (!shortk && !inside_half_lines && !(g->epi == epi::EPI_INT && S == 2 && M <= 100))
+        g->resident = resident_tile(M, K, Ncols, L, D, S);
 
     g->w_kstride = (uint32_t)(g->MB * kFragBytes);
     g->a_kstride = (uint32_t)(g->ntiles * g->NT * D * kFragBytes);

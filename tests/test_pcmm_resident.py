@@ -1,0 +1,123 @@
+"""Contractions whose digits fit LDS (pcmm_resident.hip): the tile that the plan chooses, on the host, and the products against the
+oracle on the GPU, bit-exact, at the edges of row groups, strips and k-steps and for every kernel variant."""
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+import pcmm_inputs as pi
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+HOST_CHECK = r"""
+#include <stdio.h>
+#include "pcmm_host.hpp"
+using namespace pcmm_host;
+#define CHECK(c) do { if (!(c)) { printf("check failed: %s (M %ld K %ld N %ld L %d bits %d w %d)\n", #c, (long)M, (long)K, (long)N, L, bits, wb); return 1; } } while (0)
+int main()
+{
+    const long Ms[] = {1, 16, 64, 100, 513, 2049, 14336, 1 << 24}, Ks[] = {1, 64, 65, 128, 129, 192, 320, 512, 513, 777, 1024, 1089, 1280, 2048, 2049, 4096};
+    const long Ns[] = {1, 16, 33, 4096, 12300, 32768, 1 << 22};
+    const int bitss[] = {24, 31, 33, 36, 41, 45, 48, 50, 51, 55, 58, 62};
+    long used = 0, parts = 0, four = 0;
+    for (long M : Ms) for (long K : Ks) for (long N : Ns) for (int bits : bitss) for (int wb = 8; wb <= 16; wb += 8) for (int L = 1; L <= 4; ++L) {
+        uint64_t q[4];
+        for (int j = 0; j < 4; ++j) q[j] = ((uint64_t)1 << bits) - 1 - 2 * j;
+        Geometry g;
+        if (plan_geometry(M, K, N, L, q, bits, wb, 0, &g) != PCMM_OK) continue;
+        const ResidentTile &t = g.resident;
+        if (!t.NT) continue;
+        const int D = g.D, S = g.S;
+        const int64_t ks = resident_ksteps(K), lds = ks * t.NT * D * kFragBytes;
+        CHECK(lds <= kLdsBytes && (t.waves == 8 || (t.waves == 4 && 2 * lds <= kLdsBytes)));
+        CHECK(t.MT == resident_mt(D, S, t.NT) && ks >= resident_ahead(D, S, t.NT, t.MT) && ks <= g.nkb && ks * 64 >= K);
+        CHECK(t.NT == 1 || (t.NT == 2 && D + S - 1 <= 6));
+        const int64_t groups = (M + 16 * t.MT - 1) / (16 * t.MT), mparts = (groups + t.groups_per_part - 1) / t.groups_per_part;
+        CHECK(t.groups_per_part >= 1 && t.groups_per_part <= groups);
+        CHECK(L * ((N + 16 * t.NT - 1) / (16 * t.NT)) * mparts <= 0x7fffff00L);
+        // the epilogues the kernel is built for
+        CHECK(g.epi == epi::EPI_INT ? g.D >= 7 : g.E <= 6 ? g.epi == epi::EPI_F64 : g.epi == epi::EPI_F64_G4 || g.epi == epi::EPI_F64_G4P);
+        // byte offsets: a k-step of residues, a block of outputs, and W up to the groups past the last row
+        CHECK(64 * N * 8 <= (int64_t)1 << 31 && ((ks + 2) * g.MB + (groups + 8) * t.MT) * kFragBytes < (int64_t)1 << 32);
+        ++used; parts += mparts > 1; four += t.waves == 4;
+    }
+    printf("%s\n", used > 1000 && parts > 10 && four > 100 ? "1" : "0");
+    return 0;
+}
+"""
+
+
+def test_chosen_tiles_fit(tmp_path):
+    if shutil.which("g++") is None:
+        pytest.skip("no g++")
+    (tmp_path / "t.cpp").write_text(HOST_CHECK)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-fsanitize=undefined", "-fno-sanitize-recover=all",
+                    "-I", os.path.join(ROOT, "paper_2601_18511_amd", "csrc"), "-o", str(tmp_path / "t"), str(tmp_path / "t.cpp")], check=True)
+    r = subprocess.run([str(tmp_path / "t")], capture_output=True, text=True)
+    assert r.returncode == 0 and r.stdout.strip() == "1", r.stdout + r.stderr
+
+
+# (M, K, Ncols, bits, L, w_bits)
+SHAPES = [
+    (1, 129, 1, 36, 1, 8),            # one row, one column, three k-steps
+    (15, 192, 15, 30, 2, 8),          # four digits
+    (64, 193, 16, 36, 1, 8),          # four k-steps; one row group
+    (65, 257, 17, 36, 3, 8),          # five k-steps
+    (300, 320, 32, 36, 2, 8),         # pairs or singles by the estimate
+    (1000, 500, 48, 33, 4, 8),
+    (1100, 448, 4096, 36, 2, 8),
+    (700, 384, 31, 45, 2, 8),         # six digits
+    (130, 777, 36, 45, 1, 8),         # 13 k-steps, rows on quarter lines
+    (130, 780, 40, 44, 1, 8),         # rows on half lines
+    (200, 1000, 33, 50, 2, 8),        # seven digits, groups of four accumulators
+    (200, 700, 33, 53, 2, 8),         # seven digits, integer epilogue
+    (193, 1100, 20, 62, 1, 8),        # eight digits
+    (128, 128, 64, 60, 2, 8),         # two k-steps (above 2^50: not the short kernel's)
+    (77, 30, 18, 52, 2, 8),           # one k-step and one of padding
+    (111, 100, 18, 55, 2, 16),
+    (49, 129, 16, 30, 1, 16),         # int16 W, four digits
+    (300, 640, 50, 36, 2, 16),
+    (1000, 900, 34, 36, 1, 16),
+    (500, 400, 24, 42, 2, 16),        # six digits
+    (500, 350, 24, 50, 1, 16),
+    (500, 350, 24, 54, 1, 16),
+    (241, 1200, 25, 62, 1, 16),       # nine accumulators
+    (100, 2048, 16, 36, 1, 8),        # 32 k-steps of five digits: all of LDS
+    (3000, 200, 64, 36, 1, 8),        # few strips: the rows are cut into parts
+    (5000, 130, 32, 50, 1, 16),
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,K,Ncols,bits,L,w_bits", SHAPES)
+@pytest.mark.parametrize("extreme", [False, True])
+def test_resident_products_bit_exact(gpu_device, M, K, Ncols, bits, L, w_bits, extreme):
+    import torch
+
+    import paper_2601_18511_amd as pkg
+    from oracle import pcmm_oracle
+
+    rng = np.random.default_rng(M + K + bits)
+    primes = list(pi.ntt_primes(bits, 1 << 8, L))
+    lo, hi, dt = (-128, 127, np.int8) if w_bits == 8 else (-32768, 32639, np.int16)
+    if extreme:
+        W = np.where(rng.random((M, K)) < 0.9, lo, hi).astype(dt)
+        A = np.stack([rng.choice(np.array([0, 1, q // 2, q - 1], dtype=np.uint64), size=(K, Ncols)) for q in primes])
+    else:
+        W = rng.integers(lo, hi + 1, size=(M, K), dtype=np.int64).astype(dt)
+        A = np.stack([rng.integers(0, q, size=(K, Ncols), dtype=np.uint64) for q in primes])
+    plan = pkg.pcmm_plan_create(torch.from_numpy(W).to(gpu_device), primes, bits, Ncols)
+    # rows of 64-bit words around C show stores outside it; an odd offset in words takes the cached stores
+    whole = torch.full((L * M * Ncols + 64,), -1, dtype=torch.int64, device=gpu_device)
+    A_dev = torch.from_numpy(A.view(np.int64)).to(gpu_device)
+    want = pcmm_oracle(W, A, primes)
+    for at in (32, 33):
+        whole.fill_(-1)
+        C = whole[at:at + L * M * Ncols].view(L, M, Ncols)
+        pkg.pcmm_run(plan, A_dev, C)
+        torch.cuda.synchronize()
+        assert (C.cpu().numpy().view(np.uint64) == want).all()
+        assert bool((whole[:at] == -1).all()) and bool((whole[at + L * M * Ncols:] == -1).all())
+    pkg.pcmm_plan_destroy(plan)

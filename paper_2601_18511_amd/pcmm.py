@@ -115,6 +115,22 @@ def _stream_handle(stream) -> int:
     return int(stream.cuda_stream)
 
 
+def _current_stream(device: int) -> int:
+    """Handle of torch's current stream on `device`."""
+    return int(torch.cuda.current_stream(device).cuda_stream)
+
+
+# The small calls are bound by the time the host takes for them.  Against a device context around every call and a Stream
+# object for its handle this takes half as long; the library itself sets the device for its launches and restores it.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", _current_stream)
+_WORDS = (torch.int64, torch.uint64)
+
+
+def _on(t: torch.Tensor, device: int) -> bool:
+    """Contiguous 64-bit words on the GPU `device`."""
+    return t.is_cuda and t.get_device() == device and t.dtype in _WORDS and t.is_contiguous()
+
+
 def pcmm_plan_create(W: torch.Tensor, primes: Sequence[int], prime_bits: int, Ncols: int, stream=None) -> PcmmPlan:
     """Plan for the device tensor W ([M][K], int8 or int16) and the host list of primes."""
     if not W.is_cuda or W.dim() != 2 or W.dtype not in (torch.int8, torch.int16) or not W.is_contiguous():
@@ -145,18 +161,21 @@ def pcmm_plan_digits(plan: PcmmPlan) -> int:
 def _check_io(plan: PcmmPlan, A: torch.Tensor, C: torch.Tensor) -> None:
     if plan.handle is None:
         raise ValueError("plan was destroyed")
+    if (_on(A, plan.device) and _on(C, plan.device) and A.shape == (plan.L, plan.K, plan.Ncols)
+            and C.shape == (plan.L, plan.M, plan.Ncols)):
+        return
     for name, t, rows in (("A", A, plan.K), ("C", C, plan.M)):
         if not t.is_cuda or t.device.index != plan.device or not t.is_contiguous():
             raise ValueError("%s must be a contiguous tensor on the plan's device" % name)
-        if t.dtype not in (torch.int64, torch.uint64) or tuple(t.shape) != (plan.L, rows, plan.Ncols):
+        if t.dtype not in _WORDS or tuple(t.shape) != (plan.L, rows, plan.Ncols):
             raise ValueError("%s must be 64-bit integers of shape [L][%d][Ncols]" % (name, rows))
 
 
 def pcmm_run(plan: PcmmPlan, A: torch.Tensor, C: torch.Tensor, stream=None) -> None:
     """Enqueue C[j] = W . A[j] mod q_j on `stream` (default: torch's current stream). Asynchronous."""
     _check_io(plan, A, C)
-    with torch.cuda.device(plan.device):
-        rc = load_library().pcmm_run(plan.handle, A.data_ptr(), C.data_ptr(), _stream_handle(stream))
+    rc = load_library().pcmm_run(plan.handle, A.data_ptr(), C.data_ptr(),
+                                  _raw_stream(plan.device) if stream is None else int(stream.cuda_stream))
     if rc != PCMM_OK:
         raise PcmmError(rc, "pcmm_run")
 
@@ -167,8 +186,8 @@ NOALLOC_SCRATCH_BYTES = 64 << 20     # PCMM_NOALLOC_SCRATCH_BYTES of include/pcm
 def pcmm_run_noalloc(plan: PcmmPlan, A: torch.Tensor, C: torch.Tensor, stream=None) -> None:
     """pcmm_run through the library's static digit scratch: the call allocates nothing. Asynchronous."""
     _check_io(plan, A, C)
-    with torch.cuda.device(plan.device):
-        rc = load_library().pcmm_run_noalloc(plan.handle, A.data_ptr(), C.data_ptr(), _stream_handle(stream))
+    rc = load_library().pcmm_run_noalloc(plan.handle, A.data_ptr(), C.data_ptr(),
+                                  _raw_stream(plan.device) if stream is None else int(stream.cuda_stream))
     if rc != PCMM_OK:
         raise PcmmError(rc, "pcmm_run_noalloc")
 
@@ -195,14 +214,16 @@ def pcmm_mfma_probe(device: int = 0, iters: int = 200000, random_operands: bool 
 
 
 def _ring_call(name: str, src: torch.Tensor, dst: torch.Tensor, N: int, k: int, stream) -> None:
-    for t in (src, dst):
-        if not t.is_cuda or not t.is_contiguous() or t.dtype not in (torch.int64, torch.uint64):
-            raise ValueError("ring switching moves contiguous 64-bit integer tensors on the GPU")
-    if src.device != dst.device or src.numel() != dst.numel() or src.numel() % int(N):
+    device = src.get_device()
+    if not (_on(src, device) and _on(dst, device)):
+        for t in (src, dst):
+            if not t.is_cuda or not t.is_contiguous() or t.dtype not in _WORDS:
+                raise ValueError("ring switching moves contiguous 64-bit integer tensors on the GPU")
+    words = src.numel()
+    if src.device != dst.device or words != dst.numel() or words % int(N):
         raise ValueError("source and destination must hold the same whole number of polynomials of degree N")
-    with torch.cuda.device(src.device):
-        rc = getattr(load_library(), name)(src.data_ptr(), dst.data_ptr(), src.numel() // int(N), int(N), int(k),
-                                           src.device.index, _stream_handle(stream))
+    rc = getattr(load_library(), name)(src.data_ptr(), dst.data_ptr(), words // int(N), int(N), int(k), device,
+                                       _raw_stream(device) if stream is None else int(stream.cuda_stream))
     if rc != PCMM_OK:
         raise PcmmError(rc, name)
 
@@ -225,14 +246,15 @@ def pcmm_slot_rearrange(S: torch.Tensor, out: torch.Tensor, d: int, ell: int, b:
     if k_count is None:
         k_count = int(d) - int(k_first)
     for t in (S, out):
-        if not t.is_cuda or not t.is_contiguous() or t.dtype not in (torch.int64, torch.uint64):
+        if not t.is_cuda or not t.is_contiguous() or t.dtype not in _WORDS:
             raise ValueError("the rearrangement moves contiguous 64-bit integer tensors on the GPU")
     d = int(d)
     if d <= 0 or S.numel() % (d * d) or S.device != out.device or out.numel() != S.numel() * int(k_count):
         raise ValueError("S must hold whole d x d matrices and out k_count times as many words")
-    with torch.cuda.device(S.device):
-        rc = load_library().pcmm_slot_rearrange(S.data_ptr(), out.data_ptr(), S.numel() // (d * d), d, int(ell), int(b),
-                                                int(k_first), int(k_count), S.device.index, _stream_handle(stream))
+    device = S.get_device()
+    rc = load_library().pcmm_slot_rearrange(S.data_ptr(), out.data_ptr(), S.numel() // (d * d), d, int(ell), int(b),
+                                            int(k_first), int(k_count), device,
+                                            _raw_stream(device) if stream is None else int(stream.cuda_stream))
     if rc != PCMM_OK:
         raise PcmmError(rc, "pcmm_slot_rearrange")
 
@@ -280,13 +302,15 @@ def pcmv_run(plan: PcmvPlan, ct: torch.Tensor, out: torch.Tensor, stream=None) -
     """Enqueue out[j][m][c] = sum_k pt[m][k] * ct[j][k][c] in Z_{q_j}[X]/(X^N+1). ct is [L][Kp][2][N], out [L][Mp][2][N]."""
     if plan.handle is None:
         raise ValueError("plan was destroyed")
-    for name, t, rows in (("ct", ct, plan.Kp), ("out", out, plan.Mp)):
-        if not t.is_cuda or t.device.index != plan.device or not t.is_contiguous():
-            raise ValueError("%s must be a contiguous tensor on the plan's device" % name)
-        if t.dtype not in (torch.int64, torch.uint64) or tuple(t.shape) != (plan.L, rows, 2, plan.N):
-            raise ValueError("%s must be 64-bit integers of shape [L][%d][2][N]" % (name, rows))
-    with torch.cuda.device(plan.device):
-        rc = load_library().pcmv_run(plan.handle, ct.data_ptr(), out.data_ptr(), _stream_handle(stream))
+    if not (_on(ct, plan.device) and _on(out, plan.device) and ct.shape == (plan.L, plan.Kp, 2, plan.N)
+            and out.shape == (plan.L, plan.Mp, 2, plan.N)):
+        for name, t, rows in (("ct", ct, plan.Kp), ("out", out, plan.Mp)):
+            if not t.is_cuda or t.device.index != plan.device or not t.is_contiguous():
+                raise ValueError("%s must be a contiguous tensor on the plan's device" % name)
+            if t.dtype not in _WORDS or tuple(t.shape) != (plan.L, rows, 2, plan.N):
+                raise ValueError("%s must be 64-bit integers of shape [L][%d][2][N]" % (name, rows))
+    rc = load_library().pcmv_run(plan.handle, ct.data_ptr(), out.data_ptr(),
+                                 _raw_stream(plan.device) if stream is None else int(stream.cuda_stream))
     if rc != PCMM_OK:
         raise PcmmError(rc, "pcmv_run")
 

@@ -7,13 +7,13 @@
 // useful coefficients afterwards belong to the algorithm the paper adopts by reference and are not here.
 //
 // Kernels:
-//   ntt_kernel / ntt4096_kernel   forward negacyclic NTT of polynomials: the plaintexts once, at plan time ("model
+//   ntt_kernel / ntt_blocked_kernel   forward negacyclic NTT of polynomials: the plaintexts once, at plan time ("model
 //                     conversion"), and the 2 Kp L ciphertext polynomials of every run
-//   mac_intt_kernel / mac_intt4096_kernel   per (limb, m): pointwise multiply-accumulate of the NTT-domain plaintexts
+//   mac_intt_kernel / mac_intt_blocked_kernel   per (limb, m): pointwise multiply-accumulate of the NTT-domain plaintexts
 //                     with both ciphertext components, inverse NTT of the two sums, store as uint64 residues
-// The *4096* kernels serve the paper's ring degree: sixteen values per thread in registers, four stages per pass, two
+// The *blocked* kernels serve the paper's ring degree, 4096, and 2048 and 1024: sixteen values per thread in registers, four stages per pass, two
 // trips through LDS per transform; the multiply-accumulate kernel runs as persistent work-groups fed from a queue.
-// The others serve every other power of two up to 4096, one radix-2 stage per pass over LDS.
+// The others serve every other power of two, one radix-2 stage per pass over LDS.
 //
 // Arithmetic.  MI355X runs double-precision vector arithmetic at full rate while 64-bit integer
 // multiplication costs many quarter-rate 32-bit multiplies, so residues are held as balanced integers in
@@ -40,7 +40,10 @@ using pcmm_device::canonical;
 using pcmm_device::mulmod;
 using pcmm_device::round_fma;
 
+using pcmm_device::kXcd;
+
 constexpr int kThreads = 256;
+constexpr int kQueueStride = 32;   // words between the work queues' counters: each in a 128-byte line of its own
 
 // the representative of an integer |v| < 2^52 modulo q (q > 2^23) with magnitude at most q/2 (+1 when the quotient
 // rounds the other way)
@@ -167,7 +170,7 @@ __global__ __launch_bounds__(kThreads) void mac_intt_kernel(const double *__rest
 // sixteen elements per thread in registers, two trips through LDS instead of twelve.
 //
 // NTT-domain polynomials are stored so that thread T reads its entries n = 16 T + e, e < 16, with 16-byte loads of
-// consecutive threads: as doubles, entry n at word 512 (e >> 1) + 2 T + (e & 1); the plaintexts of primes below 2^36
+// consecutive threads: as doubles, entry n at word N/8 (e >> 1) + 2 T + (e & 1); the plaintexts of primes below 2^36
 // packed (PtRaw below).
 //   pass 1  stages t = 1, 2, 4, 8        thread T holds n = 16 T + e
 //   pass 2  stages t = 16 .. 128         thread T = 16 A + B holds n = 256 A + B + 16 e
@@ -176,8 +179,22 @@ __global__ __launch_bounds__(kThreads) void mac_intt_kernel(const double *__rest
 // twiddles per thread in the four stages of a pass, contiguous in the table.
 // LDS holds entry n at n + (n >> 4) (one word of padding per sixteen): the 16-word strides of pass 1's writes
 // and the unit strides of the other accesses are then all free of bank conflicts for 8-byte accesses.
-constexpr int kN4096 = 4096;
-constexpr int kLdsPoly4096 = kN4096 + kN4096 / 16;
+// Ring degrees 2048 and 1024 run the same way on 128 and 64 threads: passes 1 and 2 as they are, pass 3 with the three or two
+// stages that are left, on two or four columns a thread
+// (radix-2 kernels through LDS -> these: degree 2048, 8192 outputs of one ciphertext, two 36-bit limbs 578 -> 164 us; 4096 of four
+// ciphertexts 484 -> 162; degree 1024, 8192 outputs, four limbs 413 -> 156; 4096 of four ciphertexts, two limbs 171 -> 75).
+constexpr int kMinBlocked = 1024, kMaxBlocked = 4096;   // ring degrees of these kernels
+template <int N>
+struct Blocked {
+    static constexpr int kT = N / 16;                // threads: sixteen values each
+    static constexpr int kV = N / 256;               // values of a column of pass 3
+    static constexpr int kLast = N == 4096 ? 4 : N == 2048 ? 3 : 2;   // stages of pass 3
+    static constexpr int kLds = N + N / 16;          // words of one polynomial
+    static constexpr uint32_t kQueues = N == 4096 ? 1 : 8;   // work queues of the multiply-accumulate kernel
+    // entry i (= kV r + e) of thread T in pass 3: its index is n = T + at(i), its word in LDS T + (T >> 4) + word(i)
+    static __host__ __device__ constexpr int at(int i) { return kT * (i / kV) + 256 * (i % kV); }
+    static __host__ __device__ constexpr int word(int i) { return (kT + kT / 16) * (i / kV) + 272 * (i % kV); }
+};
 
 // four Gentleman-Sande stages on sixteen values; tw[0..7], tw[8..11], tw[12..13], tw[14]: the twiddles of the
 // four stages (stage s pairs e with e + 2^s and uses twiddle number e >> (s + 1) of its run).
@@ -185,19 +202,22 @@ constexpr int kLdsPoly4096 = kN4096 + kN4096 / 16;
 // <= 2 q give products <= 0.75 q + 1), stages 1 and 3 reduce the sums (<= 4 q < 2^52 in, <= q/2 + 1 out) and
 // multiply differences <= 4 q (products <= q): outputs <= q again.
 // LAZY = true (q < 2^36): no sum is reduced anywhere in the twelve stages of the transform (bounds in the comment of mulmod).
-template <bool LAZY>
+// STAGES < 4 (pass 3 of smaller degrees): the values are 16 >> STAGES independent columns, the twiddles those of the last
+// STAGES runs.
+template <bool LAZY, int STAGES = 4>
 __device__ __forceinline__ void gs16(double (&v)[16], const double (&tw)[15], double q, double invq)
 {
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
+    for (int s = 0; s < STAGES; ++s) {
         const int half = 1 << s;
-        const int off = s == 0 ? 0 : (s == 1 ? 8 : (s == 2 ? 12 : 14));
+        const int run = s + 4 - STAGES;
+        const int off = run == 0 ? 0 : (run == 1 ? 8 : (run == 2 ? 12 : 14));
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
             if (e & half) continue;
             const double U = v[e], V = v[e + half];
             v[e] = (!LAZY && (s & 1)) ? reduce(U + V, q, invq) : U + V;
-            v[e + half] = mulmod(tw[off + (e >> (s + 1))], U - V, q, invq);
+            v[e + half] = mulmod(tw[off + ((e & ((1 << STAGES) - 1)) >> (s + 1))], U - V, q, invq);
         }
     }
 }
@@ -222,24 +242,25 @@ __device__ __forceinline__ v2d ld2(__amdgpu_buffer_rsrc_t r, uint32_t lane_off, 
 }
 // The sixteen NTT-domain values of a thread as they lie in memory.
 // PACKED (primes below 2^36): a balanced residue r, |r| <= q/2 + 1 < 2^35, is kept as u = r + 2^35 < 2^36: the low 32 bits
-// of entry e at byte 4096 (e >> 2) + 16 T + 4 (e & 3), the top four bits of the sixteen entries as eight bytes at
-// 16384 + 8 T, entry e in bits 4 e .. 4 e + 3.  18 KiB a polynomial instead of the 32 KiB of doubles: the plaintexts are most
+// of entry e at byte N (e >> 2) + 16 T + 4 (e & 3), the top four bits of the sixteen entries as eight bytes at
+// 4 N + 8 T, entry e in bits 4 e .. 4 e + 3.  At degree 4096 18 KiB a polynomial instead of the 32 KiB of doubles: the plaintexts are most
 // of what the multiply-accumulate kernel reads, and it is bound by memory as much as by its arithmetic.  Unpacking
 // places u in the low mantissa bits of 2^52 and subtracts: one v_perm and one addition a value, and the masks.
 // Measured, doubles -> packed (4096 output polynomials, two 36-bit limbs): one input ciphertext 182 -> 175 us, four
 // 416 -> 328 us (there also because every operand of a term is now requested one term ahead).
-template <bool PACKED>
+template <bool PACKED, int N>
 struct PtRaw;
-template <>
-struct PtRaw<true> {
-    static constexpr uint32_t kBytes = kN4096 * 4 + kN4096 / 2;   // of one polynomial
+template <int N>
+struct PtRaw<true, N> {
+    static constexpr uint32_t kBytes = N * 4 + N / 2;   // of one polynomial
+    static constexpr uint32_t kRow = N;                 // bytes of four entries of every thread (16 bytes each)
     v4u lo[4];
     v2u hi;
     __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, uint32_t T, uint32_t uniform_off)
     {
 #pragma unroll
-        for (int c = 0; c < 4; ++c) lo[c] = (v4u)__builtin_amdgcn_raw_buffer_load_b128(r, 16u * T + 4096u * c, uniform_off, 0);
-        hi = (v2u)__builtin_amdgcn_raw_buffer_load_b64(r, 8u * T + 16384u, uniform_off, 0);
+        for (int c = 0; c < 4; ++c) lo[c] = (v4u)__builtin_amdgcn_raw_buffer_load_b128(r, 16u * T + kRow * c, uniform_off, 0);
+        hi = (v2u)__builtin_amdgcn_raw_buffer_load_b64(r, 8u * T + 4 * kRow, uniform_off, 0);
     }
     __device__ __forceinline__ void unpack(double (&w)[16]) const
     {
@@ -268,19 +289,20 @@ struct PtRaw<true> {
                 l[i] = u[0];
                 h[e >> 3] |= (u[1] & 0xFu) << (4 * (e & 7));
             }
-            *reinterpret_cast<v4u *>(poly + 16u * T + 4096u * c) = l;
+            *reinterpret_cast<v4u *>(poly + 16u * T + kRow * c) = l;
         }
-        *reinterpret_cast<v2u *>(poly + 8u * T + 16384u) = h;
+        *reinterpret_cast<v2u *>(poly + 8u * T + 4 * kRow) = h;
     }
 };
-template <>
-struct PtRaw<false> {
-    static constexpr uint32_t kBytes = kN4096 * 8;
+template <int N>
+struct PtRaw<false, N> {
+    static constexpr uint32_t kBytes = N * 8;
+    static constexpr uint32_t kRow = N;                 // bytes of two entries of every thread (16 bytes each)
     v2d x[8];
     __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, uint32_t T, uint32_t uniform_off)
     {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) x[i] = ld2(r, 16u * T + 4096u * i, uniform_off);
+        for (int i = 0; i < 8; ++i) x[i] = ld2(r, 16u * T + kRow * i, uniform_off);
     }
     __device__ __forceinline__ void unpack(double (&w)[16]) const
     {
@@ -290,7 +312,7 @@ struct PtRaw<false> {
     static __device__ __forceinline__ void store(const double (&r)[16], char *poly, uint32_t T)
     {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) *reinterpret_cast<v2d *>(poly + 16u * T + 4096u * i) = (v2d){r[2 * i], r[2 * i + 1]};
+        for (int i = 0; i < 8; ++i) *reinterpret_cast<v2d *>(poly + 16u * T + kRow * i) = (v2d){r[2 * i], r[2 * i + 1]};
     }
 };
 
@@ -322,40 +344,42 @@ __device__ __forceinline__ void load_tw(double (&tw)[15], __amdgpu_buffer_rsrc_t
 // <= 2 q) to an unreduced value: <= 2.25 q + 2; stages 1 and 3 reduce that value first (<= q/2 + 1) and multiply
 // operands <= 2.25 q + 2 <= 4 q (products <= q): outputs <= 1.5 q + 1 again.
 // LAZY = true (q < 2^36): nothing is reduced; a value grows by at most 0.5625 q per stage, to less than 8 q in twelve.
-template <bool LAZY>
+// STAGES < 4 (pass A of smaller degrees): 16 >> STAGES independent columns.  Three stages end without a reduction: outputs
+// <= 2.25 q + 2, so that the next pass's first stage leaves <= 3.25 q + 3 <= 4 q and its second reduces as above.
+template <bool LAZY, int STAGES = 4>
 __device__ __forceinline__ void ct16(double (&v)[16], const double (&tw)[15], double q, double invq)
 {
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-        const int half = 8 >> s;
+    for (int s = 0; s < STAGES; ++s) {
+        const int half = (1 << STAGES) >> (s + 1);
         const int off = s == 0 ? 14 : (s == 1 ? 12 : (s == 2 ? 8 : 0));
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
             if (e & half) continue;
             const double U = (!LAZY && (s & 1)) ? reduce(v[e], q, invq) : v[e];
-            const double V = mulmod(tw[off + (e >> (4 - s))], v[e + half], q, invq);
+            const double V = mulmod(tw[off + ((e & ((1 << STAGES) - 1)) >> (STAGES - s))], v[e + half], q, invq);
             v[e] = U + V;
             v[e + half] = U - V;
         }
     }
 }
 
-// Forward negacyclic NTT of polynomials of degree 4096, one per work-group: the mirror image of the inverse
+// Forward negacyclic NTT of polynomials, one per work-group: the mirror image of the inverse
 // transform below -- three passes of four Cooley-Tukey stages on sixteen values per thread, two trips through LDS.
 //   pass A  stages t = 2048 .. 256       thread T holds n = T + 256 e     (read from memory, coalesced)
 //   pass B  stages t = 128 .. 16         thread T = 16 A + B holds n = 256 A + B + 16 e
 //   pass C  stages t = 8 .. 1            thread T holds n = 16 T + e      (entries of the bit-reversed order, stored in
 //                                        the layout the multiply-accumulate reads: PtRaw)
 // Stage t = N/(2m) uses the twiddle fwd[m + (n >> (log2 t + 1))].  Sources and the scaling of the plaintexts as in ntt_kernel.
-template <int SRC, bool LAZY>
-__global__ __launch_bounds__(kThreads) void ntt4096_kernel(const void *__restrict__ src, void *__restrict__ dst,
+template <int N, int SRC, bool LAZY>
+__global__ __launch_bounds__(N / 16) void ntt_blocked_kernel(const void *__restrict__ src, void *__restrict__ dst,
                                                            const double *__restrict__ fwd_tables, const LimbDev *__restrict__ lc,
                                                            int64_t polys_per_limb, uint32_t *__restrict__ queue, uint32_t queue_start)
 {
-    constexpr int N = kN4096;
-    __shared__ double lds[kLdsPoly4096];
+    using G = Blocked<N>;
+    __shared__ double lds[G::kLds];
     const int64_t p = blockIdx.x;
-    if (queue && p == 0 && threadIdx.x == 0) *queue = queue_start;       // the work queue of the kernel that follows
+    if (queue && p == 0 && threadIdx.x < Blocked<N>::kQueues) queue[threadIdx.x * kQueueStride] = queue_start;   // the work queues of the kernel that follows
     const int limb = (int)(p / polys_per_limb);
     const int64_t within = p % polys_per_limb;
     const double q = lc[limb].q, invq = lc[limb].invq;
@@ -366,18 +390,18 @@ __global__ __launch_bounds__(kThreads) void ntt4096_kernel(const void *__restric
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
         if (SRC == 0) {
-            const uint64_t x = static_cast<const uint64_t *>(src)[p * N + T + 256 * e];
+            const uint64_t x = static_cast<const uint64_t *>(src)[p * N + T + G::at(e)];
             v[e] = __builtin_fma((double)(uint32_t)(x >> 32), 4294967296.0, (double)(uint32_t)x);   // exact: x < 2^50
         } else {
-            v[e] = (double)static_cast<const int32_t *>(src)[within * N + T + 256 * e];
+            v[e] = (double)static_cast<const int32_t *>(src)[within * N + T + G::at(e)];
         }
     }
 #pragma unroll
     for (int e = 0; e < 16; ++e) v[e] = reduce(v[e], q, invq);
-    ct16<LAZY>(v, tw, q, invq);
+    ct16<LAZY, G::kLast>(v, tw, q, invq);
 #pragma unroll
-    for (int e = 0; e < 16; ++e) lds[T + (T >> 4) + 272 * e] = v[e];
-    load_tw(tw, frs, 16, A);
+    for (int e = 0; e < 16; ++e) lds[T + (T >> 4) + G::word(e)] = v[e];
+    load_tw(tw, frs, N / 256, A);
     __syncthreads();
     {
         double *s = lds + 272 * A + B;
@@ -387,7 +411,7 @@ __global__ __launch_bounds__(kThreads) void ntt4096_kernel(const void *__restric
 #pragma unroll
         for (int e = 0; e < 16; ++e) s[17 * e] = v[e];
     }
-    load_tw(tw, frs, 256, T);
+    load_tw(tw, frs, N / 16, T);
     __syncthreads();
 #pragma unroll
     for (int e = 0; e < 16; ++e) v[e] = lds[17 * T + e];
@@ -399,16 +423,18 @@ __global__ __launch_bounds__(kThreads) void ntt4096_kernel(const void *__restric
         v[e] = reduce(v[e], q, invq);
         if (SRC == 1) v[e] = reduce(mulmod(scale, v[e], q, invq), q, invq);
     }
-    using Raw = PtRaw<SRC == 1 && LAZY>;               // plaintexts packed where the prime allows it, ciphertexts as doubles
+    using Raw = PtRaw<SRC == 1 && LAZY, N>;               // plaintexts packed where the prime allows it, ciphertexts as doubles
     Raw::store(v, static_cast<char *>(dst) + p * (int64_t)Raw::kBytes, T);
 }
 
-// Persistent work-groups: work-group g takes the output polynomials g, g + G, g + 2 G, ... (G = grid size, two
-// work-groups per compute unit), so that what depends only on the limb stays in registers from one polynomial to the
-// next -- the twiddles of passes 1 and 2 and, for KP1 (one input ciphertext, the shape of every decode projection whose
-// input fits one polynomial), the thread's 32 values of the transformed ciphertext -- and the plaintext values of the
-// next polynomial are requested while the present one is transformed.  total = L Mp polynomials; the loop ends for
-// every wave when its index passes total.
+// Persistent work-groups (eight waves per compute unit), so that what depends only on the limb stays in registers from one
+// polynomial to the next -- the twiddles of passes 1 and 2 and, for KP1 (one input ciphertext, the shape of every decode projection
+// whose input fits one polynomial), the thread's 32 values of the transformed ciphertext -- and the plaintext values of the
+// next polynomial are requested while the present one is transformed.  total = L Mp polynomials: the first two of a work-group
+// are fixed, the rest come from a queue in order of asking; the loop ends for every wave when its index passes the last.
+// Degrees 2048 and 1024 have a queue for each XCD (work-group b runs on XCD b % 8) with an eighth of the polynomials: one counter hands
+// out a polynomial every 12 ns at most, and the 8192 of degree 1024 (4096 outputs, two 50-bit limbs) took 114 us with one queue, 55
+// with eight.  Degree 4096 needs a polynomial every 20 ns and keeps one: with eight it is no faster.
 //
 // LAZY (every prime below 2^36): no intermediate reduction of sums, neither in the transform nor between the
 // terms of the multiply-accumulate (Kp <= 4096 products of magnitude <= 0.5625 q: below 2^12 q; one reduction
@@ -417,26 +443,29 @@ __global__ __launch_bounds__(kThreads) void ntt4096_kernel(const void *__restric
 // All global reads are buffer loads (uniform base and offset in scalar registers, one 32-bit lane offset): no vector
 // registers go into addresses, and the loads of a term are all issued before the first is used (left to itself the
 // compiler starts the arithmetic on the first values early, which splits the loads into two dependent round trips).
-template <bool LAZY, bool KP1>
-__global__ __launch_bounds__(kThreads, 2) void mac_intt4096_kernel(const void *__restrict__ ptn, const double *__restrict__ ctn,
+template <int N, bool LAZY, bool KP1>
+__global__ __launch_bounds__(N / 16, 2) void mac_intt_blocked_kernel(const void *__restrict__ ptn, const double *__restrict__ ctn,
                                                                    uint64_t *__restrict__ out, const double *__restrict__ inv_tables,
                                                                    const LimbDev *__restrict__ lc, uint32_t Mp, int Kp, uint32_t total,
                                                                    uint32_t *__restrict__ queue)
 {
-    constexpr int N = kN4096;
+    using G = Blocked<N>;
     constexpr uint32_t PB = N * 8;                    // bytes of one polynomial of doubles
-    __shared__ double lds[2 * kLdsPoly4096];          // component a, component b
+    __shared__ double lds[2 * G::kLds];          // component a, component b
     __shared__ uint32_t queue_word;
     const int T = threadIdx.x;
-    using Raw = PtRaw<LAZY>;
-    uint32_t blk = blockIdx.x;
-    if (blk >= total) return;
-    uint32_t next = blk + gridDim.x;                  // the first two polynomials of a work-group are fixed; total + 3 grid < 2^32
+    using Raw = PtRaw<LAZY, N>;
+    constexpr uint32_t Q = G::kQueues;
+    const uint32_t own = blockIdx.x % Q, per_queue = (total + Q - 1) / Q, lo = own * per_queue;
+    const uint32_t hi = min(lo + per_queue, total);   // this queue's polynomials (none where lo >= hi); total + 3 grid + 8 < 2^32
+    uint32_t blk = lo + blockIdx.x / Q;
+    if (blk >= hi) return;
+    uint32_t next = blk + gridDim.x / Q;              // the first two polynomials of a work-group are fixed
     const uint32_t kpb = (uint32_t)Kp * Raw::kBytes;  // bytes of the plaintexts of one output polynomial (Kp <= 4096)
     auto plaintexts = [&](uint32_t poly) { return view(static_cast<const char *>(ptn) + (int64_t)poly * kpb, kpb); };
 
     double tw1[15], tw2[15];
-    PtRaw<false> xa, xb;                              // transformed ciphertext values
+    PtRaw<false, N> xa, xb;                              // transformed ciphertext values
     Raw wv;                                           // plaintext values, requested one term ahead
     double q = 0.0, invq = 0.0;
     uint32_t limb_loaded = 0xFFFFFFFFu;
@@ -446,7 +475,7 @@ __global__ __launch_bounds__(kThreads, 2) void mac_intt4096_kernel(const void *_
         // the polynomial after the next one comes from the queue (one lane asks; the answer is passed on through LDS
         // behind the first barrier below)
         uint32_t asked = 0;
-        if (T == 0) asked = atomicAdd(queue, 1u);
+        if (T == 0) asked = lo + atomicAdd(&queue[own * kQueueStride], 1u);
         // the LDS addresses below are recomputed from the thread index in every round (the asm hides that it is the same
         // index): kept across the loop they cost more registers than the kernel has
         int Ti = T;
@@ -459,8 +488,8 @@ __global__ __launch_bounds__(kThreads, 2) void mac_intt4096_kernel(const void *_
             q = lc[limb].q;
             invq = lc[limb].invq;
             if constexpr (KP1) {
-                load_tw(tw1, irs, 256, T);            // pass 1: table entries 2048 + 8 T .., 1024 + 4 T .., 512 + 2 T .., 256 + T
-                load_tw(tw2, irs, 16, T >> 4);        // pass 2, A = T / 16: 128 + 8 A .., 64 + 4 A .., 32 + 2 A .., 16 + A
+                load_tw(tw1, irs, N / 16, T);         // pass 1: table entries N/2 + 8 T .., N/4 + 4 T .., N/8 + 2 T .., N/16 + T
+                load_tw(tw2, irs, N / 256, T >> 4);   // pass 2, A = T / 16: N/32 + 8 A .., N/64 + 4 A .., N/128 + 2 A .., N/256 + A
                 xa.load(crs, T, 0);
                 xb.load(crs, T, PB);
             }
@@ -486,7 +515,7 @@ __global__ __launch_bounds__(kThreads, 2) void mac_intt4096_kernel(const void *_
             for (int e = 0; e < 16; ++e) va[e] = vb[e] = 0.0;
             // One term.  Each set of operands is requested for the next term as soon as the present one has used it: the
             // plaintexts once unpacked, component a's values behind the products of a, component b's behind those of b.
-            auto products = [&](double (&v)[16], const double (&w)[16], const PtRaw<false> &x) {
+            auto products = [&](double (&v)[16], const double (&w)[16], const PtRaw<false, N> &x) {
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
                     const double y = mulmod(w[e], x.x[e >> 1][e & 1], q, invq);
@@ -518,11 +547,11 @@ __global__ __launch_bounds__(kThreads, 2) void mac_intt4096_kernel(const void *_
                          "v"(vb[e + 3])
                          : "memory");
         // the first plaintext values of the next polynomial are requested now and used in the next round
-        if (next < total) wv.load(plaintexts(next), T, 0);
+        if (next < hi) wv.load(plaintexts(next), T, 0);
         if constexpr (!KP1) {
             // with several terms the registers do not hold the twiddles from one polynomial to the next
-            load_tw(tw1, irs, 256, Ti);
-            load_tw(tw2, irs, 16, Ai);
+            load_tw(tw1, irs, N / 16, Ti);
+            load_tw(tw2, irs, N / 256, Ai);
             if constexpr (LAZY) {
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
@@ -539,12 +568,12 @@ __global__ __launch_bounds__(kThreads, 2) void mac_intt4096_kernel(const void *_
         for (int e = 0; e < 16; ++e) lds[17 * Ti + e] = va[e];          // n = 16 T + e at n + (n >> 4)
         gs16<LAZY>(vb, tw1, q, invq);
 #pragma unroll
-        for (int e = 0; e < 16; ++e) lds[kLdsPoly4096 + 17 * Ti + e] = vb[e];
+        for (int e = 0; e < 16; ++e) lds[G::kLds + 17 * Ti + e] = vb[e];
         __syncthreads();
 
         // ---- pass 2: stages t = 16 .. 128 on n = 256 A + B + 16 e, i.e. LDS word 272 A + B + 17 e
         for (int c = 0; c < 2; ++c) {
-            double *s = lds + c * kLdsPoly4096 + 272 * Ai + Bi;
+            double *s = lds + c * G::kLds + 272 * Ai + Bi;
             double v[16];
 #pragma unroll
             for (int e = 0; e < 16; ++e) v[e] = s[17 * e];
@@ -554,7 +583,7 @@ __global__ __launch_bounds__(kThreads, 2) void mac_intt4096_kernel(const void *_
         }
         __syncthreads();
 
-        // ---- pass 3: stages t = 256 .. 2048 on n = T + 256 e, i.e. LDS word T + (T >> 4) + 272 e; then out
+        // ---- pass 3: stages t = 256 .. N / 2 on n = T + 256 e (and further columns of smaller degrees); then out
         // (the fifteen twiddles are the same for every thread: table entries 1 .. 15)
         const double *inv = inv_tables + (int64_t)limb * N;
         double tw3[15];
@@ -568,11 +597,11 @@ __global__ __launch_bounds__(kThreads, 2) void mac_intt4096_kernel(const void *_
         const double half_invq = 0.5 * invq;
         uint64_t *o = out + (int64_t)blk * 2 * N;
         for (int c = 0; c < 2; ++c) {
-            const double *s = lds + c * kLdsPoly4096 + Ti + (Ti >> 4);
+            const double *s = lds + c * G::kLds + Ti + (Ti >> 4);
             double v[16];
 #pragma unroll
-            for (int e = 0; e < 16; ++e) v[e] = s[272 * e];
-            gs16<LAZY>(v, tw3, q, invq);
+            for (int e = 0; e < 16; ++e) v[e] = s[G::word(e)];
+            gs16<LAZY, G::kLast>(v, tw3, q, invq);
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
                 double r;                                              // canonical: an integer in [0, q) (1/N is folded into the plaintexts)
@@ -586,13 +615,24 @@ __global__ __launch_bounds__(kThreads, 2) void mac_intt4096_kernel(const void *_
                 // 4096 outputs of one ciphertext and two limbs, 329 -> 323 us for four; the same hint on the plaintext
                 // loads costs 2 % where they fit the last-level cache)
                 __builtin_nontemporal_store((uint64_t)__double_as_longlong(r + 4503599627370496.0) & 0x000FFFFFFFFFFFFFull,
-                                            &o[c * N + Ti + 256 * e]);
+                                            &o[c * N + Ti + G::at(e)]);
             }
         }
-        if (next >= total) break;
+        if (next >= hi) break;
         blk = next;
         next = after_next;
     }
+}
+
+bool blocked(int64_t N) { return N >= kMinBlocked && N <= kMaxBlocked; }
+
+// f(integral_constant<int, N>) for a ring degree of the blocked kernels
+template <class F>
+void with_degree(int N, F &&f)
+{
+    if (N == 4096) f(std::integral_constant<int, 4096>{});
+    else if (N == 2048) f(std::integral_constant<int, 2048>{});
+    else f(std::integral_constant<int, 1024>{});
 }
 
 }  // namespace
@@ -600,10 +640,10 @@ __global__ __launch_bounds__(kThreads, 2) void mac_intt4096_kernel(const void *_
 struct pcmv_plan {
     int64_t Mp, Kp, N;
     int L, device;
-    uint32_t grid;     // work-groups of the persistent degree-4096 kernel: two per compute unit
-    uint32_t *queue;   // device: its work queue (one counter)
-    bool lazy;         // every prime is below 2^36: the degree-4096 transform runs without intermediate reductions
-    void *ptn;         // device [L][Mp][Kp]: plaintexts in the NTT domain (N doubles, or PtRaw<true> for degree 4096 and lazy)
+    uint32_t grid;     // work-groups of the persistent kernel: eight waves per compute unit
+    uint32_t *queue;   // device: its work queues' counters
+    bool lazy;         // every prime is below 2^36: the blocked transforms run without intermediate reductions
+    void *ptn;         // device [L][Mp][Kp]: plaintexts in the NTT domain (N doubles, or PtRaw<true> for blocked degrees and lazy)
     double *ctn;       // device [L][Kp][2][N]: scratch, the ciphertexts of one run in the NTT domain
     double *fwd, *inv; // device [L][N] twiddle tables
     LimbDev *lc;       // device [L]
@@ -657,20 +697,22 @@ pcmm_status pcmv_plan_create(pcmv_plan **out, int64_t Mp, int64_t Kp, int64_t N,
     const size_t ctn_bytes = (size_t)L * Kp * 2 * N * sizeof(double);
     const size_t tab_bytes = (size_t)L * N * sizeof(double);
     const size_t lc_bytes = (size_t)L * sizeof(LimbDev);
+    const size_t queue_bytes = kXcd * kQueueStride * sizeof(uint32_t);
     pcmm_status rc = PCMM_OK;
     if (hipMalloc((void **)&p->ptn, ptn_bytes) != hipSuccess || hipMalloc((void **)&p->ctn, ctn_bytes) != hipSuccess ||
         hipMalloc((void **)&p->fwd, tab_bytes) != hipSuccess || hipMalloc((void **)&p->inv, tab_bytes) != hipSuccess ||
-        hipMalloc((void **)&p->lc, lc_bytes) != hipSuccess || hipMalloc((void **)&p->queue, 256) != hipSuccess) {
+        hipMalloc((void **)&p->lc, lc_bytes) != hipSuccess || hipMalloc((void **)&p->queue, queue_bytes) != hipSuccess) {
         (void)hipGetLastError();
         rc = PCMM_ENOMEM;
     }
-    p->bytes = ptn_bytes + ctn_bytes + 2 * tab_bytes + lc_bytes + 256;
+    p->bytes = ptn_bytes + ctn_bytes + 2 * tab_bytes + lc_bytes + queue_bytes;
     if (rc == PCMM_OK) {
-        // the persistent degree-4096 kernel runs two work-groups per compute unit
+        // the persistent kernel runs two waves per SIMD: two work-groups of four waves per compute unit at degree 4096
         int cus = 0;
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus <= 0) rc = PCMM_EDEVICE;
         const int64_t total = (int64_t)L * Mp;
-        p->grid = (uint32_t)(total < 2 * (int64_t)cus ? total : 2 * (int64_t)cus);
+        const int64_t most = 2 * (int64_t)cus * (kMaxBlocked / N);
+        p->grid = (uint32_t)((total < most ? total : most) + kXcd - 1) / kXcd * kXcd;   // whole rounds over the XCDs
     }
     if (rc == PCMM_OK) {
         if (hipMemcpyAsync(p->fwd, fwd.data(), tab_bytes, hipMemcpyHostToDevice, st) != hipSuccess ||
@@ -681,9 +723,12 @@ pcmm_status pcmv_plan_create(pcmv_plan **out, int64_t Mp, int64_t Kp, int64_t N,
     if (rc == PCMM_OK) {
         // the plaintexts into the NTT domain, once (the paper's model conversion for PCMv, Section 5.3)
         const int64_t polys = (int64_t)L * Mp * Kp;
-        if (N == kN4096)
-            hipLaunchKernelGGL((p->lazy ? ntt4096_kernel<1, true> : ntt4096_kernel<1, false>), dim3((unsigned)polys), dim3(kThreads), 0,
-                               st, (const void *)pt_dev, p->ptn, p->fwd, p->lc, Mp * Kp, (uint32_t *)nullptr, 0u);
+        if (blocked(N))
+            with_degree((int)N, [&](auto n) {
+                constexpr int NN = decltype(n)::value;
+                hipLaunchKernelGGL((p->lazy ? ntt_blocked_kernel<NN, 1, true> : ntt_blocked_kernel<NN, 1, false>), dim3((unsigned)polys),
+                                   dim3(NN / 16), 0, st, (const void *)pt_dev, p->ptn, p->fwd, p->lc, Mp * Kp, (uint32_t *)nullptr, 0u);
+            });
         else
             hipLaunchKernelGGL((ntt_kernel<1>), dim3((unsigned)polys), dim3(kThreads), (size_t)N * sizeof(double), st,
                                (const void *)pt_dev, (double *)p->ptn, p->fwd, p->lc, (int)N, Mp * Kp);
@@ -708,26 +753,29 @@ pcmm_status pcmv_run(const pcmv_plan *plan, const uint64_t *ct_dev, uint64_t *ou
     hipStream_t st = (hipStream_t)stream;
     const int N = (int)plan->N;
     const int64_t ct_polys = (int64_t)plan->L * plan->Kp * 2;
-    if (N == kN4096)
-        hipLaunchKernelGGL((plan->lazy ? ntt4096_kernel<0, true> : ntt4096_kernel<0, false>), dim3((unsigned)ct_polys), dim3(kThreads),
-                           0, st, (const void *)ct_dev, plan->ctn, plan->fwd, plan->lc, plan->Kp * 2, plan->queue, 2u * plan->grid);
-    else
+    if (blocked(N)) {
+        hipError_t rc = hipSuccess;
+        with_degree(N, [&](auto n) {
+            constexpr int NN = decltype(n)::value;
+            hipLaunchKernelGGL((plan->lazy ? ntt_blocked_kernel<NN, 0, true> : ntt_blocked_kernel<NN, 0, false>), dim3((unsigned)ct_polys),
+                               dim3(NN / 16), 0, st, (const void *)ct_dev, plan->ctn, plan->fwd, plan->lc, plan->Kp * 2, plan->queue,
+                               2u * plan->grid / Blocked<NN>::kQueues);
+            rc = hipGetLastError();
+            if (rc != hipSuccess) return;
+            auto kern = plan->Kp == 1 ? (plan->lazy ? mac_intt_blocked_kernel<NN, true, true> : mac_intt_blocked_kernel<NN, false, true>)
+                                      : (plan->lazy ? mac_intt_blocked_kernel<NN, true, false> : mac_intt_blocked_kernel<NN, false, false>);
+            hipLaunchKernelGGL(kern, dim3(plan->grid), dim3(NN / 16), 0, st, plan->ptn, plan->ctn, out_dev, plan->inv, plan->lc,
+                               (uint32_t)plan->Mp, (int)plan->Kp, (uint32_t)(plan->L * plan->Mp), plan->queue);
+        });
+        if (rc != hipSuccess) return PCMM_EDEVICE;
+    } else {
         hipLaunchKernelGGL((ntt_kernel<0>), dim3((unsigned)ct_polys), dim3(kThreads), (size_t)N * sizeof(double), st,
                            (const void *)ct_dev, plan->ctn, plan->fwd, plan->lc, N, plan->Kp * 2);
-    if (hipGetLastError() != hipSuccess) return PCMM_EDEVICE;
-    if (N == kN4096)
-    {
-        const uint32_t total = (uint32_t)(plan->L * plan->Mp);
-        const uint32_t grid = plan->grid;
-        auto kern = plan->Kp == 1 ? (plan->lazy ? mac_intt4096_kernel<true, true> : mac_intt4096_kernel<false, true>)
-                                  : (plan->lazy ? mac_intt4096_kernel<true, false> : mac_intt4096_kernel<false, false>);
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), 0, st, plan->ptn, plan->ctn, out_dev, plan->inv, plan->lc,
-                           (uint32_t)plan->Mp, (int)plan->Kp, total, plan->queue);
+        if (hipGetLastError() != hipSuccess) return PCMM_EDEVICE;
+        hipLaunchKernelGGL(mac_intt_kernel, dim3((unsigned)((int64_t)plan->L * plan->Mp)), dim3(kThreads),
+                           (size_t)2 * N * sizeof(double), st, (const double *)plan->ptn, plan->ctn, out_dev, plan->inv, plan->lc, N, plan->Mp,
+                           (int)plan->Kp);
     }
-    else
-    hipLaunchKernelGGL(mac_intt_kernel, dim3((unsigned)((int64_t)plan->L * plan->Mp)), dim3(kThreads),
-                       (size_t)2 * N * sizeof(double), st, (const double *)plan->ptn, plan->ctn, out_dev, plan->inv, plan->lc, N, plan->Mp,
-                       (int)plan->Kp);
     return hipGetLastError() == hipSuccess ? PCMM_OK : PCMM_EDEVICE;
 }
 

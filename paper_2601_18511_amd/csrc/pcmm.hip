@@ -136,7 +136,20 @@ __global__ __launch_bounds__(256) void pack_w_kernel(const WT *__restrict__ W, i
 // Output layout Ad[limb][kb][ntile][nt][d][lane][16]; fragment (nt, d) of chunk (limb, kb, ntile)
 // holds digit d of A[limb][kb*64 + (lane/16)*16 + 0..15][(ntile*NT + nt)*16 + lane%16], zero outside
 // K x Ncols.  One block = 4 waves = 64 columns x 64 k; wave g takes k-group g, lane = column.
-template <int D>
+//
+// NT_ACCESS (pcmm_host::SplitNt): what streams past the caches.
+template <int NT_ACCESS>
+__device__ __forceinline__ uint64_t residue(const uint64_t *word)
+{
+    return NT_ACCESS == pcmm_host::kNtBoth ? __builtin_nontemporal_load(word) : *word;
+}
+template <int NT_ACCESS>
+__device__ __forceinline__ void store_digits(const v4i &v, int8_t *at)
+{
+    if constexpr (NT_ACCESS != pcmm_host::kNtNone) __builtin_nontemporal_store(v, reinterpret_cast<v4i *>(at));
+    else *reinterpret_cast<v4i *>(at) = v;
+}
+template <int D, int NT_ACCESS>
 __global__ __launch_bounds__(256) void split_kernel(const uint64_t *__restrict__ A, int8_t *__restrict__ Ad,
                                                     int64_t K, int64_t Ncols, int64_t nkb, int64_t ntiles,
                                                     int NT)
@@ -163,7 +176,7 @@ __global__ __launch_bounds__(256) void split_kernel(const uint64_t *__restrict__
 
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
-        uint64_t x = (k0 + j < K && n < Ncols) ? src[(int64_t)j * Ncols] : 0;
+        uint64_t x = (k0 + j < K && n < Ncols) ? residue<NT_ACCESS>(&src[(int64_t)j * Ncols]) : 0;
         uint64_t y = x + bias;
 #pragma unroll
         for (int d = 0; d < D; ++d) out[d][j >> 2] |= (uint32_t)((y >> (8 * d)) & 0xFF) << (8 * (j & 3));
@@ -179,7 +192,7 @@ __global__ __launch_bounds__(256) void split_kernel(const uint64_t *__restrict__
         v.y = (int)(out[d][1] ^ 0x80808080u);
         v.z = (int)(out[d][2] ^ 0x80808080u);
         v.w = (int)(out[d][3] ^ 0x80808080u);
-        *reinterpret_cast<v4i *>(chunk + (nt * D + d) * kFrag + (g * 16 + (int)(n & 15)) * 16) = v;
+        store_digits<NT_ACCESS>(v, chunk + (nt * D + d) * kFrag + (g * 16 + (int)(n & 15)) * 16);
     }
 }
 
@@ -193,6 +206,7 @@ __global__ __launch_bounds__(256) void split_kernel(const uint64_t *__restrict__
 // balanced digits of X (pcmm_host.hpp decides which primes qualify and derives the constants).
 // Bound: HBM, 16 bytes read and 9 written per pair of residues; about 45 vector instructions per pair, a third of what
 // the memory time hides.  Layout as in split_kernel with one 16-column fragment per tile (NT = 1) and nine digits.
+template <int NT_ACCESS>
 __global__ __launch_bounds__(256) void split_pair_kernel(const uint64_t *__restrict__ A, int8_t *__restrict__ Ad,
                                                          int64_t K, int64_t Ncols, int64_t nkb, int64_t ntiles,
                                                          PairConsts pcs)
@@ -214,8 +228,8 @@ __global__ __launch_bounds__(256) void split_pair_kernel(const uint64_t *__restr
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
         const bool in = k0 + j < K && n < Ncols;
-        x1[j] = in ? src1[(int64_t)j * Ncols] : 0;
-        x2[j] = in ? src2[(int64_t)j * Ncols] : 0;
+        x1[j] = in ? residue<NT_ACCESS>(&src1[(int64_t)j * Ncols]) : 0;
+        x2[j] = in ? residue<NT_ACCESS>(&src2[(int64_t)j * Ncols]) : 0;
     }
     uint32_t out[D][4];
 #pragma unroll
@@ -255,7 +269,7 @@ __global__ __launch_bounds__(256) void split_pair_kernel(const uint64_t *__restr
         v.y = (int)(out[d][1] ^ 0x80808080u);
         v.z = (int)(out[d][2] ^ 0x80808080u);
         v.w = (int)(out[d][3] ^ 0x80808080u);
-        *reinterpret_cast<v4i *>(chunk + d * kFrag + (g * 16 + (int)(n & 15)) * 16) = v;
+        store_digits<NT_ACCESS>(v, chunk + d * kFrag + (g * 16 + (int)(n & 15)) * 16);
     }
 }
 
@@ -271,6 +285,7 @@ struct GemmArgs {
     int64_t MB;             // padded M / 16
     int nkb;                // padded K / 64: k-steps in the layouts of Wp and Ad
     int kb0, nkbc;          // this launch contracts k-steps [kb0, kb0 + nkbc), nkbc >= 2
+    int nt_stores;          // C is stored non-temporally (pcmm_host::gemm_nt_stores)
     int accumulate;         // 0: C = result;  1: C = (C + result) mod q  (later slices of a long K)
     int mtiles, ntiles, L;
     int gn;                 // n-tiles per raster group
@@ -531,9 +546,9 @@ __global__ __launch_bounds__(WM * 64) __attribute__((amdgpu_waves_per_eu(1, ALON
     // or branching per output.
     uint64_t *Cl = a.C + (int64_t)(LP * limb) * a.M * a.Ncols;
     const uint32_t c_rowbytes = (uint32_t)a.Ncols * 8u;
-    // The whole epilogue exists twice, with and without the read-add of the previous contents of C,
+    // The whole epilogue exists three times, with the read-add of the previous contents of C and without it for both kinds of stores,
     // chosen once per wave: a branch per output would stop the scheduler from overlapping outputs.
-    auto store_block = [&](__amdgpu_buffer_rsrc_t crs, uint32_t c_lane, uint64_t (&res)[4], uint64_t q, auto accumulate_c) {
+    auto store_block = [&](__amdgpu_buffer_rsrc_t crs, uint32_t c_lane, uint64_t (&res)[4], uint64_t q, auto accumulate_c, auto nt_c) {
         if constexpr (decltype(accumulate_c)::value) {   // rows and columns outside C read as 0
             v2u old[4];
 #pragma unroll
@@ -548,9 +563,9 @@ __global__ __launch_bounds__(WM * 64) __attribute__((amdgpu_waves_per_eu(1, ALON
 #pragma unroll
         for (int r = 0; r < 4; ++r)
             __builtin_amdgcn_raw_buffer_store_b64((v2u){(uint32_t)res[r], (uint32_t)(res[r] >> 32)}, crs,
-                                                  c_lane + (uint32_t)r * c_rowbytes, 0, 0);
+                                                  c_lane + (uint32_t)r * c_rowbytes, 0, decltype(nt_c)::value ? 2 : 0);
     };
-    auto epilogue = [&](auto accumulate_c) {
+    auto epilogue = [&](auto accumulate_c, auto nt_c) {
     static_for<MT * NT>([&](auto ijc) {
         constexpr int i = decltype(ijc)::value / NT, j = decltype(ijc)::value % NT;
         // 16 x 16 blocks that lie wholly in the padding are skipped (wave-uniform)
@@ -574,8 +589,8 @@ __global__ __launch_bounds__(WM * 64) __attribute__((amdgpu_waves_per_eu(1, ALON
                 reduce_f64_pair<E, 4>(avs, lc.qd, lc.invq, lc2.qd, lc2.invq, res1, res2);
                 const __amdgpu_buffer_rsrc_t crs2 = __builtin_amdgcn_make_buffer_rsrc(
                     Cl + (a.M + m0) * a.Ncols, 0, rows_valid * c_rowbytes, 0x00020000);
-                store_block(crs, c_lane, res1, lc.q, accumulate_c);
-                store_block(crs2, c_lane, res2, lc2.q, accumulate_c);
+                store_block(crs, c_lane, res1, lc.q, accumulate_c, nt_c);
+                store_block(crs2, c_lane, res2, lc2.q, accumulate_c, nt_c);
                 return;
             }
             uint64_t res[4];
@@ -588,12 +603,13 @@ __global__ __launch_bounds__(WM * 64) __attribute__((amdgpu_waves_per_eu(1, ALON
             } else {
                 reduce_int<E, 4>(avs, lc, res);
             }
-            store_block(crs, c_lane, res, lc.q, accumulate_c);
+            store_block(crs, c_lane, res, lc.q, accumulate_c, nt_c);
         }
     });
     };
-    if (a.accumulate) epilogue(std::true_type{});
-    else epilogue(std::false_type{});
+    if (a.accumulate) epilogue(std::true_type{}, std::false_type{});
+    else if (a.nt_stores) epilogue(std::false_type{}, std::true_type{});
+    else epilogue(std::false_type{}, std::false_type{});
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -845,9 +861,14 @@ hipError_t launch_gemm(const pcmm_plan *p, const GemmArgs &ga, int64_t grid, hip
 hipError_t launch_split(const pcmm_plan *p, int8_t *Ad, const uint64_t *A, hipStream_t st)
 {
     const dim3 block(256);
+    const pcmm_host::SplitNt nt = pcmm_host::split_nt(p->L, p->K, p->Ncols, (uint64_t)(uintptr_t)A);
+    using pcmm_host::kNtBoth;
+    using pcmm_host::kNtNone;
+    using pcmm_host::kNtStores;
     if (p->pairs) {
         const dim3 grid((unsigned)((p->pair_ntiles * 16 + 63) / 64), (unsigned)p->ksteps, (unsigned)p->pairs);
-        hipLaunchKernelGGL(split_pair_kernel, grid, block, 0, st, A, Ad, p->K, p->Ncols, p->nkb, p->pair_ntiles, p->pcs);
+        const auto kern = nt == kNtBoth ? split_pair_kernel<kNtBoth> : nt == kNtStores ? split_pair_kernel<kNtStores> : split_pair_kernel<kNtNone>;
+        hipLaunchKernelGGL(kern, grid, block, 0, st, A, Ad, p->K, p->Ncols, p->nkb, p->pair_ntiles, p->pcs);
         const hipError_t rc = hipGetLastError();
         if (rc != hipSuccess) return rc;
     }
@@ -859,8 +880,9 @@ hipError_t launch_split(const pcmm_plan *p, int8_t *Ad, const uint64_t *A, hipSt
     dim3 grid((unsigned)colblocks, (unsigned)p->ksteps, (unsigned)single);
 #define PCMM_SPLIT_CASE(DD)                                                                              \
     case DD:                                                                                             \
-        hipLaunchKernelGGL((split_kernel<DD>), grid, block, 0, st, A, Ad, p->K, p->Ncols, p->nkb,     \
-                           p->ntiles, p->NT);                                                            \
+        hipLaunchKernelGGL((nt == kNtBoth ? split_kernel<DD, kNtBoth> : nt == kNtStores ? split_kernel<DD, kNtStores>   \
+                                                                                        : split_kernel<DD, kNtNone>),  \
+                           grid, block, 0, st, A, Ad, p->K, p->Ncols, p->nkb, p->ntiles, p->NT);         \
         break;
     switch (p->D) {
         PCMM_SPLIT_CASE(4)
@@ -931,6 +953,7 @@ pcmm_status run_impl(const pcmm_plan *p, int8_t *Ad, const uint64_t *A, uint64_t
         ga.Ncols = p->Ncols;
         ga.MB = p->MB;
         ga.nkb = (int)p->nkb;
+        ga.nt_stores = pcmm_host::gemm_nt_stores(p->M, p->K, p->S, p->Ncols, (uint64_t)(uintptr_t)C);
         ga.mtiles = (int)p->mtiles;
         // A contraction longer than the int32 accumulators can hold runs as several launches over
         // consecutive ranges of k; every launch after the first adds its result to C modulo q_j.

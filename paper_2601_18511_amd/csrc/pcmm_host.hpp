@@ -153,6 +153,28 @@ inline bool shortk_nt_stores(int64_t Ncols, uint64_t c_address, int64_t c_bytes,
     return c_bytes > from_mib << 20;
 }
 
+// What of the digit split goes past the caches: nothing, the digits, or the residues too.  Both where they exceed the 256 MiB
+// last-level cache by enough that nothing of them is found there again (split alone, cached -> non-temporal: 4096 x 4096 by
+// 4096 x 32768, four 36-bit limbs 1.25 -> 1.16 ms; 14336 values of k, three limbs 3.28 -> 3.06; whole pcmm_run, residues of 625 MiB
+// 305 -> 277 us, 512 MiB 1140 -> 1115; 281 MiB 185 -> 190, 188 MiB 153 -> 162, 78 MiB 46 -> 64, hence the line).  Rows of residues that
+// do not start on lines: the digits only, since neighbouring work-groups share lines of residues (12300 columns, 3000 values
+// of k, two limbs 0.201 -> 0.180 ms, with the residues 0.190).
+enum SplitNt : int { kNtNone = 0, kNtStores = 1, kNtBoth = 2 };
+inline SplitNt split_nt(int64_t L, int64_t K, int64_t Ncols, uint64_t a_address)
+{
+    if (8 * L * K * Ncols <= (int64_t)384 << 20) return kNtNone;
+    return ((uint64_t)Ncols * 8 | a_address) % 128 == 0 ? kNtBoth : kNtStores;
+}
+
+// Whether the GEMM kernel stores C non-temporally: rows on half lines, and a W of more than 48 MiB, which every group of n-tiles
+// reads again and cached stores push out of the last-level cache (GEMM alone, cached -> non-temporal, 36-bit limbs: 14336 x 4096 by
+// 4096 x 16384, two limbs 6.60 -> 6.37 ms; 12296 columns 5.13 -> 4.82; 28672 x 2500 by 2500 x 8192 4.65 -> 4.21; W of 39 MiB,
+// 10000 x 4096 4.47 -> 4.51, of 16 MiB, 4096 x 4096 7.63 -> 7.73; odd rows 1000 x 3000 by 3000 x 12301 320 -> 345 us).
+inline bool gemm_nt_stores(int64_t M, int64_t K, int S, int64_t Ncols, uint64_t c_address)
+{
+    return ((uint64_t)Ncols * 8 | c_address) % 64 == 0 && M * K * S > (int64_t)48 << 20;
+}
+
 // ---- the kernel that keeps the digits of a whole contraction in LDS (pcmm_resident.hip)
 constexpr int64_t kLdsBytes = 160 * 1024;   // of a compute unit
 struct ResidentTile {

@@ -143,6 +143,16 @@ int main()
         CHECK(!shortk_nt_stores(8200, 4104, 4096 * MiB, 2000, 2) && shortk_nt_stores(8200, 4160, 4096 * MiB, 2000, 2));
     }
 
+    // digit split: past the caches from 384 MiB of residues on, the residues only where their rows start on lines
+    CHECK(split_nt(4, 4096, 32768, 0) == kNtBoth && split_nt(4, 4096, 32764, 0) == kNtStores && split_nt(4, 4096, 32768, 64) == kNtStores);
+    CHECK(split_nt(3, 4096, 4096, 0) == kNtNone && split_nt(3, 4097, 4096, 0) == kNtBoth);
+    // GEMM: half lines and more than 48 MiB of W
+    CHECK(gemm_nt_stores(14336, 4096, 1, 32768, 0) && gemm_nt_stores(14336, 4096, 1, 12296, 64) && !gemm_nt_stores(14336, 4096, 1, 12300, 0));
+    CHECK(!gemm_nt_stores(14336, 4096, 1, 32768, 32) && !gemm_nt_stores(4096, 4096, 2, 32768, 0) && gemm_nt_stores(8192, 4096, 2, 32768, 0));
+    // resident digits: half lines, quarter lines from 60 products a block on
+    CHECK(resident_nt_stores(200, 8200, 0, 5, 1) && !resident_nt_stores(200, 8200, 8, 5, 1) && !resident_nt_stores(704, 8196, 0, 5, 1));
+    CHECK(resident_nt_stores(705, 8196, 0, 5, 1) && resident_nt_stores(320, 8196, 32, 6, 2) && !resident_nt_stores(2000, 8198, 0, 5, 1));
+
     // per-limb constants, from the smallest to the largest supported primes
     const uint64_t qs[] = {8388617ull, 16777213ull, 68719403009ull, 68718428161ull, 1125899903827969ull,
                            (((uint64_t)1 << 55) - 55), (((uint64_t)1 << 61) - 1), 4611686018427387847ull, 4611686018326724609ull};

@@ -22,6 +22,18 @@ typedef unsigned int v2u __attribute__((ext_vector_type(2)));
 constexpr int kFrag = pcmm_host::kFragBytes;   // bytes of one 16 x 64 int8 MFMA operand fragment
 constexpr int kXcd = 8;       // accelerator complex dies, each with its own L2
 
+// strip, part of the rows and limb of work-group `bid` (pcmm_host::StripRaster); false: none
+__device__ __forceinline__ bool strip_of(const pcmm_host::StripRaster &r, int64_t bid, int &strip, int &mpart, int &limb)
+{
+    const int64_t i = bid / kXcd;
+    const int64_t t = (bid % kXcd) * r.per_xcd + (r.whole ? i % r.per_xcd : i);
+    if (t >= r.total) return false;
+    strip = (int)(t % r.nstrips);
+    mpart = r.whole ? (int)(i / r.per_xcd) : (int)((t / r.nstrips) % r.mparts);
+    limb = (int)(r.whole ? t / r.nstrips : t / ((int64_t)r.mparts * r.nstrips));
+    return true;
+}
+
 // ------------------------------------------------------------------------------------------------
 // modular helpers (device)
 // ------------------------------------------------------------------------------------------------

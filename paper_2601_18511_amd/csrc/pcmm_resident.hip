@@ -41,12 +41,9 @@ using pcmm_host::ResidentTile;
 struct KArgs {
     pcmm_resident::Args a;
     int ksteps;           // k-steps of 64 that are cut and contracted
-    int nstrips;          // strips per limb
-    int mparts;           // parts the rows are cut into (work-groups per strip)
     int groups;           // groups of MT row blocks in all
     int groups_per_part;
-    int64_t per_xcd;      // work-groups per XCD
-    int64_t total;        // L * nstrips * mparts
+    pcmm_host::StripRaster raster;
 };
 
 template <int D, int S, int NT, int MT, int EPI, bool NT_STORES>
@@ -58,12 +55,8 @@ __global__ __launch_bounds__(512, 2) void gemm_resident_kernel(KArgs ka)
     const pcmm_resident::Args &a = ka.a;
     extern __shared__ __attribute__((aligned(16))) int8_t dig[];   // [k-step][NT][D][lane][16]
 
-    const int64_t bid = blockIdx.x;
-    const int64_t t = (bid % kXcd) * ka.per_xcd + bid / kXcd;
-    if (bid / kXcd >= ka.per_xcd || t >= ka.total) return;
-    const int strip = (int)(t % ka.nstrips);
-    const int mpart = (int)((t / ka.nstrips) % ka.mparts);
-    const int limb = (int)(t / ((int64_t)ka.mparts * ka.nstrips));
+    int strip, mpart, limb;
+    if (!strip_of(ka.raster, blockIdx.x, strip, mpart, limb)) return;
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -263,7 +256,7 @@ hipError_t launch_tile(const KArgs &ka, const ResidentTile &tile, hipStream_t st
     if (lds > pcmm_host::kLdsBytes) return hipErrorInvalidValue;
     const bool nt = pcmm_host::resident_nt_stores(ka.a.K, ka.a.Ncols, (uint64_t)(uintptr_t)ka.a.C, D, S);
     const auto kern = nt ? gemm_resident_kernel<D, S, NT, MT, EPI, true> : gemm_resident_kernel<D, S, NT, MT, EPI, false>;
-    const dim3 g((unsigned)(ka.per_xcd * kXcd)), b((unsigned)(tile.waves * 64));
+    const dim3 g((unsigned)ka.raster.grid), b((unsigned)(tile.waves * 64));
     hipLaunchKernelGGL(kern, g, b, (size_t)lds, st, ka);
     return hipGetLastError();
 }
@@ -277,13 +270,11 @@ hipError_t launch(const Args &a, const ResidentTile &tile, int D, int S, int epi
     KArgs ka;
     ka.a = a;
     ka.ksteps = (int)pcmm_host::resident_ksteps(a.K);
-    ka.nstrips = (int)((a.Ncols + 16 * tile.NT - 1) / (16 * tile.NT));
     ka.groups = (int)((a.M + 16 * tile.MT - 1) / (16 * tile.MT));
     ka.groups_per_part = tile.groups_per_part;
-    ka.mparts = (ka.groups + ka.groups_per_part - 1) / ka.groups_per_part;
-    ka.total = (int64_t)a.L * ka.nstrips * ka.mparts;
-    if (ka.ksteps > a.nkb || ka.total > 0x7fffff00LL) return hipErrorInvalidValue;
-    ka.per_xcd = (ka.total + kXcd - 1) / kXcd;
+    ka.raster = pcmm_host::strip_raster(a.L, (a.Ncols + 16 * tile.NT - 1) / (16 * tile.NT),
+                                        (ka.groups + ka.groups_per_part - 1) / ka.groups_per_part);
+    if (ka.ksteps > a.nkb || ka.raster.grid > 0x7fffffffLL) return hipErrorInvalidValue;
 #define PCMM_RESIDENT_CASE(DD, SS, NN, EE) \
     if (D == DD && S == SS && tile.NT == NN && (epi == EE || (EE == EPI_F64_G4 && epi == EPI_F64_G4P))) \
         return launch_tile<DD, SS, NN, EE>(ka, tile, st);

@@ -37,11 +37,8 @@ constexpr int RS = 4;   // 16-row blocks of W per LDS stage
 
 struct KArgs {
     pcmm_shortk::Args a;
-    int nstrips;          // 64-column strips per limb
-    int mparts;           // parts the rows are cut into (work-groups per strip)
     int stages_per_part;  // LDS stages (RS row blocks each) per part
-    int64_t per_xcd;      // work-groups per XCD
-    int64_t total;        // L * nstrips * mparts
+    pcmm_host::StripRaster raster;   // of 64-column strips
 };
 
 // MODE: the grouping reduce_f64 uses (0: groups of three accumulators; 2: groups of four, pairs joined in int32)
@@ -61,16 +58,10 @@ __global__ __launch_bounds__(256, D == 7 && S == 2 ? 3 : 4) void gemm_shortk_ker
 
     __shared__ __attribute__((aligned(16))) int8_t lds[2][STAGE];
 
-    // which strip: work-groups are dealt round-robin to the 8 XCDs; each XCD walks its own contiguous
-    // range, strips fastest, so that the work-groups resident together store to the same rows side by side (against
-    // the parts of a strip next to each other: 8192 x 64 by 64 x 8192 132 -> 101 us; 777 x 96 by 96 x 20001, four
-    // limbs 202 -> 183 us; equal where a strip has one part)
-    const int64_t bid = blockIdx.x;
-    const int64_t t = (bid % kXcd) * ka.per_xcd + bid / kXcd;
-    if (bid / kXcd >= ka.per_xcd || t >= ka.total) return;
-    const int strip = (int)(t % ka.nstrips);
-    const int mpart = (int)((t / ka.nstrips) % ka.mparts);
-    const int limb = (int)(t / ((int64_t)ka.mparts * ka.nstrips));
+    // which strip (strips side by side at a time against the parts of a strip next to each other: 8192 x 64 by 64 x 8192 132 ->
+    // 101 us; 777 x 96 by 96 x 20001, four limbs 202 -> 183 us; equal where a strip has one part)
+    int strip, mpart, limb;
+    if (!strip_of(ka.raster, blockIdx.x, strip, mpart, limb)) return;
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -227,9 +218,9 @@ template <int D, int S, int MODE>
 void launch_mode(const KArgs &ka, int64_t grid, hipStream_t st)
 {
     const dim3 g((unsigned)grid), b(256);
-    const bool once = ka.mparts == 1;
+    const bool once = ka.raster.mparts == 1;
     const bool nt = pcmm_host::shortk_nt_stores(ka.a.Ncols, (uint64_t)(uintptr_t)ka.a.C, (int64_t)ka.a.L * ka.a.M * ka.a.Ncols * 8,
-                                                (int64_t)ka.a.L * ka.nstrips, ka.mparts);
+                                                (int64_t)ka.a.L * ka.raster.nstrips, ka.raster.mparts);
     const auto kern = once ? (nt ? gemm_shortk_kernel<D, S, MODE, true, true> : gemm_shortk_kernel<D, S, MODE, true, false>)
                            : (nt ? gemm_shortk_kernel<D, S, MODE, false, true> : gemm_shortk_kernel<D, S, MODE, false, false>);
     hipLaunchKernelGGL(kern, g, b, 0, st, ka);
@@ -264,22 +255,20 @@ hipError_t launch(const Args &a, int D, int S, int epi, hipStream_t st)
     if (!covers(D, S, epi, 2)) return hipErrorInvalidValue;
     KArgs ka;
     ka.a = a;
-    ka.nstrips = (int)((a.Ncols + 63) / 64);
+    const int64_t nstrips = (a.Ncols + 63) / 64;
     const int64_t stages = ((a.M + 15) / 16 + RS - 1) / RS;        // stages that hold a row of W
     // Enough work-groups to balance the 1024 resident ones, as few as possible otherwise: every part of a strip reads
     // and cuts the strip's residues again.  Up to 512 strips, where that repeats most, 1536 work-groups, else 3072.
     // Measured with 1536 / 3072 / 6144: 128 strips (4096 x 128 by 128 x 8192) 56 / 69 / 82 us; 256 strips (1024 x 128
     // by 128 x 8192, two limbs) 36 / 41 / 60 us; 626 strips (4096 x 128 by 128 x 20000, two limbs) 273 / 261 / 277 us;
     // 2048 strips (1000 x 80 by 80 x 65536, two limbs) 249 / 210 / 223 us.
-    const int64_t strips = (int64_t)a.L * ka.nstrips;
+    const int64_t strips = (int64_t)a.L * nstrips;
     const int64_t target = strips <= 512 ? 1536 : 3072;
     const int64_t mparts = std::min<int64_t>(stages, std::max<int64_t>(1, (target + strips - 1) / strips));
     ka.stages_per_part = (int)((stages + mparts - 1) / mparts);
-    ka.mparts = (int)((stages + ka.stages_per_part - 1) / ka.stages_per_part);
-    ka.total = strips * ka.mparts;
-    if (ka.total > 0x7fffff00LL) return hipErrorInvalidValue;
-    ka.per_xcd = (ka.total + kXcd - 1) / kXcd;
-    const int64_t grid = ka.per_xcd * kXcd;
+    ka.raster = pcmm_host::strip_raster(a.L, nstrips, (stages + ka.stages_per_part - 1) / ka.stages_per_part);
+    const int64_t grid = ka.raster.grid;
+    if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
 #define PCMM_SHORTK_CASE(DD, SS) \
     if (D == DD && S == SS) return launch_ds<DD, SS>(ka, epi, grid, st);
     PCMM_SHORTK_CASE(4, 1)

@@ -153,6 +153,22 @@ int main()
     CHECK(resident_nt_stores(200, 8200, 0, 5, 1) && !resident_nt_stores(200, 8200, 8, 5, 1) && !resident_nt_stores(704, 8196, 0, 5, 1));
     CHECK(resident_nt_stores(705, 8196, 0, 5, 1) && resident_nt_stores(320, 8196, 32, 6, 2) && !resident_nt_stores(2000, 8198, 0, 5, 1));
 
+    // strip rasters: every (limb, strip, part) exactly once, in both forms
+    for (int64_t L = 1; L <= 3; ++L)
+        for (int64_t n = 1; n <= 70; n += 3)
+            for (int64_t m = 1; m <= 5; ++m) {
+                const StripRaster r = strip_raster(L, n, m);
+                std::vector<int> seen((size_t)(L * n * m), 0);
+                for (int64_t bid = 0; bid < r.grid; ++bid) {       // as strip_of on the device
+                    const int64_t i = bid / 8, t = (bid % 8) * r.per_xcd + (r.whole ? i % r.per_xcd : i);
+                    if (t >= r.total) continue;
+                    const int64_t strip = t % n, part = r.whole ? i / r.per_xcd : (t / n) % m, limb = r.whole ? t / n : t / (m * n);
+                    CHECK(limb < L && part < m);
+                    ++seen[(size_t)((limb * n + strip) * m + part)];
+                }
+                for (int x : seen) CHECK(x == 1);
+            }
+
     // per-limb constants, from the smallest to the largest supported primes
     const uint64_t qs[] = {8388617ull, 16777213ull, 68719403009ull, 68718428161ull, 1125899903827969ull,
                            (((uint64_t)1 << 55) - 55), (((uint64_t)1 << 61) - 1), 4611686018427387847ull, 4611686018326724609ull};

@@ -1026,7 +1026,7 @@ pcmm_status pcmm_plan_create(pcmm_plan **out, int64_t M, int64_t K, int64_t Ncol
     // set-up for pcmm_run_noalloc: this device's address of the static digit scratch, asked for once
     if (!static_scratch_ptr(device)) { delete p; return PCMM_EDEVICE; }
 
-    const size_t wp_bytes = g.wp_bytes, ad_bytes = p->shortk || p->resident.NT ? 0 : g.ad_bytes;   // scratch the plan owns
+    const size_t wp_bytes = g.wp_bytes + pcmm_host::kWpSlack, ad_bytes = p->shortk || p->resident.NT ? 0 : g.ad_bytes;   // scratch the plan owns
     const size_t lc_bytes = (size_t)L * sizeof(LimbConst);
     int *err_dev = nullptr;
     pcmm_status rc = PCMM_OK;

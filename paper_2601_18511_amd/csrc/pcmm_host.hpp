@@ -223,6 +223,11 @@ constexpr int resident_ahead(int D, int S, int NT, int MT)
 }
 // k-steps that are cut and contracted
 inline int64_t resident_ksteps(int64_t K) { return K > 64 ? (K + 63) / 64 : 2; }
+// rows of residues in k-step kb: 0 in one of padding
+constexpr int64_t resident_rows(int64_t K, int64_t kb) { return K <= kb * 64 ? 0 : K - kb * 64 < 64 ? K - kb * 64 : 64; }
+// Bytes behind the packed weights that belong to their allocation: the last row group's blocks beyond MB in the last k-step of the
+// last slice (fewer than MT of them, MT <= 4) are fetched and not used.
+constexpr int64_t kWpSlack = 3 * kFragBytes;
 
 // Whether C is stored non-temporally.  Rows on half lines of 128 bytes: always (1000 x 777 by 777 x 12288, three 45-bit limbs
 // 207 -> 179 us; 4096 x 500 by 500 x 8192, four 36-bit limbs 412 -> 317).  At other places lines are shared with the neighbouring

@@ -72,14 +72,22 @@ __global__ __launch_bounds__(512, 2) void gemm_resident_kernel(KArgs ka)
         auto load = [&](uint64_t (&x)[16], int u) {
             const int kb = u / NT, nt = u % NT;
             const int64_t n = n0 + nt * 16 + (lane & 15);
-            const uint32_t rows = (uint32_t)max((int64_t)0, min((int64_t)64, a.K - (int64_t)kb * 64));   // 0: a k-step of padding
+            const uint32_t rows = (uint32_t)pcmm_host::resident_rows(a.K, kb);   // 0: a k-step of padding
             const uint32_t off = n < a.Ncols ? (uint32_t)((lane >> 4) * 16) * rowbytes + (uint32_t)n * 8u : 0x80000000u;
             const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
                 const_cast<uint64_t *>(a.A + ((int64_t)limb * a.K + (int64_t)kb * 64) * a.Ncols), 0, rows * rowbytes, 0x00020000);
-#pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                const v2u w = (v2u)__builtin_amdgcn_raw_buffer_load_b64(rs, off, (int)((uint32_t)j * rowbytes), 0);
+            auto word = [&](int j, uint32_t lane_off, uint32_t uniform_off) {
+                const v2u w = (v2u)__builtin_amdgcn_raw_buffer_load_b64(rs, lane_off, (int)uniform_off, 0);
                 x[j] = (uint64_t)w[0] | ((uint64_t)w[1] << 32);
+            };
+            // The range check counts the lane's offset; whether it counts the uniform one too is not the same in all documents.
+            // So that one stays inside the descriptor, and a last k-step with fewer rows has its row offsets in the lanes.
+            if (rows == 64) {
+#pragma unroll
+                for (int j = 0; j < 16; ++j) word(j, off, (uint32_t)j * rowbytes);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 16; ++j) word(j, off + (uint32_t)j * rowbytes, 0);
             }
         };
         auto cut = [&](const uint64_t (&x)[16], int u) {
@@ -106,7 +114,8 @@ __global__ __launch_bounds__(512, 2) void gemm_resident_kernel(KArgs ka)
     int g = wave;
     if (g >= g_end) return;
 
-    // ---- W: one descriptor per slice, a scalar byte offset for row group and k-step
+    // ---- W: one descriptor per slice, a scalar byte offset for row group and k-step.  A group's blocks beyond MB read the next
+    // k-step's first ones, behind the last k-step the slack of the packed array (pcmm_host::kWpSlack): their rows are dropped below.
     const uint32_t slice_bytes = (uint32_t)(a.nkb * a.MB * kFrag);
     const uint32_t kstride = (uint32_t)a.MB * (uint32_t)kFrag;
     const uint32_t loff = (uint32_t)lane * 16u;
@@ -140,9 +149,9 @@ __global__ __launch_bounds__(512, 2) void gemm_resident_kernel(KArgs ka)
                 (v4i)__builtin_amdgcn_raw_buffer_load_b128(wrs[f / MT], loff, (int)(woff + k * kstride + (f % MT) * kFrag), 0);
     });
 
-    // One k-step in NT parts of 16 columns.  wnext: byte offset of the W fragments to request (the next k-step's, or the next
-    // row group's first).
-    auto step = [&](auto phase, auto first, int kb, uint32_t wnext) {
+    // One k-step in NT parts of 16 columns.  wnext.x: byte offset of the W fragments to request (a later k-step's, or one of the
+    // next row group); wnext.y: 0, or an offset out of range for every lane where there is no next group (nothing is fetched).
+    auto step = [&](auto phase, auto first, int kb, uint2 wnext) {
         constexpr int CUR = decltype(phase)::value, NXT = (CUR + PF) % U;
         constexpr bool FIRST = decltype(first)::value;
         constexpr int CNT = D * NW * NT;              // MFMAs
@@ -158,7 +167,7 @@ __global__ __launch_bounds__(512, 2) void gemm_resident_kernel(KArgs ka)
                     static_for<n_hi - n_lo>([&](auto oc) {
                         constexpr int n = n_lo + decltype(oc)::value;
                         wreg[NXT][n / MT][n % MT] =
-                            (v4i)__builtin_amdgcn_raw_buffer_load_b128(wrs[n / MT], loff, (int)(wnext + (n % MT) * kFrag), 0);
+                            (v4i)__builtin_amdgcn_raw_buffer_load_b128(wrs[n / MT], loff + wnext.y, (int)(wnext.x + (n % MT) * kFrag), 0);
                     });
                     // W fragments forwards for one digit and backwards for the next: consecutive MFMAs share an operand
                     constexpr int f = ((j * D + d) & 1) ? NW - 1 - decltype(fc)::value : decltype(fc)::value;
@@ -174,10 +183,11 @@ __global__ __launch_bounds__(512, 2) void gemm_resident_kernel(KArgs ka)
     };
     for (;;) {
         const int g_next = g + nw;
-        const uint32_t wfirst = g_next < g_end ? first_offset(g_next) : 0x80000000u;   // none: out of range, reads as 0
+        const uint32_t wfirst = first_offset(g_next < g_end ? g_next : g);
+        const uint32_t none = g_next < g_end ? 0u : 0x80000000u;      // a slice is smaller
         auto wahead = [&](int kb) {                   // the k-step PF after kb, perhaps of the next group
             const int k = kb + PF;
-            return k < nks ? woff + (uint32_t)k * kstride : wfirst + (uint32_t)(k - nks) * kstride;
+            return k < nks ? make_uint2(woff + (uint32_t)k * kstride, 0u) : make_uint2(wfirst + (uint32_t)(k - nks) * kstride, none);
         };
 #pragma unroll
         for (int d = 0; d < D; ++d) b[d] = *reinterpret_cast<const v4i *>(&dig[d * kFrag + lane * 16]);

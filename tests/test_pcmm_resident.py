@@ -39,6 +39,15 @@ int main()
         CHECK(L * ((N + 16 * t.NT - 1) / (16 * t.NT)) * mparts <= 0x7fffff00L);
         // the epilogues the kernel is built for
         CHECK(g.epi == epi::EPI_INT ? g.D >= 7 : g.E <= 6 ? g.epi == epi::EPI_F64 : g.epi == epi::EPI_F64_G4 || g.epi == epi::EPI_F64_G4P);
+        // every byte of W that a lane may ask for belongs to the allocation, by the scalar offset alone: row groups, blocks beyond the
+        // last row, k-steps requested ahead (those of the next group, or of the same one again behind the last)
+        const int64_t w_end = ((S - 1) * g.nkb + (ks - 1)) * g.MB + (groups - 1) * t.MT + t.MT;
+        CHECK(w_end * kFragBytes <= (int64_t)g.wp_bytes + kWpSlack);
+        // every residue row that is asked for by a scalar offset exists
+        for (int64_t kb = 0; kb < ks; ++kb) {
+            const int64_t rows = resident_rows(K, kb);
+            CHECK(rows == 0 ? kb * 64 >= K : kb * 64 + rows == (rows == 64 ? kb * 64 + 64 : K) && kb * 64 + rows <= K);
+        }
         // byte offsets: a k-step of residues, a block of outputs, and W up to the groups past the last row
         CHECK(64 * N * 8 <= (int64_t)1 << 31 && ((ks + 2) * g.MB + (groups + 8) * t.MT) * kFragBytes < (int64_t)1 << 32);
         ++used; parts += mparts > 1; four += t.waves == 4;

@@ -264,7 +264,7 @@ inline ResidentTile resident_tile(int64_t M, int64_t K, int64_t Ncols, int64_t L
             const int64_t slots = waves == 4 ? 512 : 256;
             for (int64_t p = 1; p <= 8 && p <= groups; ++p) {
                 const int64_t per_part = (groups + p - 1) / p, wgs = strips * ((groups + per_part - 1) / per_part);
-                if (wgs > 0x7fffff00LL) continue;
+                if ((wgs + 8 * p) * waves * 64 >= (int64_t)1 << 32) continue;   // a launch counts its threads in 32 bits (the raster rounds up)
                 const double wg = 2300.0 + 1400.0 * ks * NT / waves + (double)((per_part + waves - 1) / waves) * (3.1 * mfma + epilogue);
                 const double full = (double)wgs / slots, rounds = 0.4 * (double)((wgs + slots - 1) / slots) + 0.6 * (full > 1.0 ? full : 1.0);
                 const double t = rounds * wg * (NT == 1 ? 1.15 : 1.0);

@@ -12,6 +12,7 @@ import pcmm_inputs as pi
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 HOST_CHECK = r"""
+#include <initializer_list>
 #include <stdio.h>
 #include "pcmm_host.hpp"
 using namespace pcmm_host;
@@ -22,9 +23,9 @@ int main()
     const long Ns[] = {1, 16, 33, 4096, 12300, 32768, 1 << 22};
     const int bitss[] = {24, 31, 33, 36, 41, 45, 48, 50, 51, 55, 58, 62};
     long used = 0, parts = 0, four = 0;
-    for (long M : Ms) for (long K : Ks) for (long N : Ns) for (int bits : bitss) for (int wb = 8; wb <= 16; wb += 8) for (int L = 1; L <= 4; ++L) {
-        uint64_t q[4];
-        for (int j = 0; j < 4; ++j) q[j] = ((uint64_t)1 << bits) - 1 - 2 * j;
+    for (long M : Ms) for (long K : Ks) for (long N : Ns) for (int bits : bitss) for (int wb = 8; wb <= 16; wb += 8) for (int L : {1, 2, 3, 4, 64}) {
+        uint64_t q[64];
+        for (int j = 0; j < L; ++j) q[j] = ((uint64_t)1 << bits) - 1 - 2 * j;
         Geometry g;
         if (plan_geometry(M, K, N, L, q, bits, wb, 0, &g) != PCMM_OK) continue;
         const ResidentTile &t = g.resident;
@@ -36,7 +37,8 @@ int main()
         CHECK(t.NT == 1 || (t.NT == 2 && D + S - 1 <= 6));
         const int64_t groups = (M + 16 * t.MT - 1) / (16 * t.MT), mparts = (groups + t.groups_per_part - 1) / t.groups_per_part;
         CHECK(t.groups_per_part >= 1 && t.groups_per_part <= groups);
-        CHECK(L * ((N + 16 * t.NT - 1) / (16 * t.NT)) * mparts <= 0x7fffff00L);
+        const StripRaster r = strip_raster(L, (N + 16 * t.NT - 1) / (16 * t.NT), mparts);
+        CHECK(r.grid <= 0x7fffffffL && r.grid * t.waves * 64 < (int64_t)1 << 32);
         // the epilogues the kernel is built for
         CHECK(g.epi == epi::EPI_INT ? g.D >= 7 : g.E <= 6 ? g.epi == epi::EPI_F64 : g.epi == epi::EPI_F64_G4 || g.epi == epi::EPI_F64_G4P);
         // every byte of W that a lane may ask for belongs to the allocation, by the scalar offset alone: row groups, blocks beyond the

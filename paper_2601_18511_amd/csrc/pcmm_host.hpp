@@ -180,19 +180,24 @@ inline bool gemm_nt_stores(int64_t M, int64_t K, int S, int64_t Ncols, uint64_t 
 // together store to the same rows side by side and the parts of a strip find its residues in their XCD's L2.  Few strips that are no
 // multiple of eight would leave XCDs idle: where more than a sixteenth would be, all (part, strip) pairs are cut into eight runs.
 // Measured against those runs for all: 128 x 128 by 128 x 8192, two limbs 9.2 -> 8.0 us; 512 x 64 by 64 x 4096, two limbs 11.1 -> 10.8.
+// Every XCD then reads all of W.  With far more rows than columns (heavy_w) that is what counts, and the runs, which give an XCD an
+// eighth of the rows, are better: 14336 x 512 by 512 x 128, one 36-bit limb 13.5 -> 8.7 us, 65536 x 512 by 512 x 256 62.5 -> 43.9;
+// the line is where neither is ahead by more than a few percent (65536 x 200 by 200 x 256, four limbs 110 -> 122 with runs;
+// 14336 x 1250 by 1250 x 256 29.7 -> 25.6, on the other side of it).
+inline bool heavy_w(int64_t M, int S, int64_t L, int64_t Ncols) { return M * S > 64 * L * Ncols; }
 struct StripRaster {
     int nstrips, mparts;      // strips per limb, parts per strip
     int whole;                // 1: all parts of a strip on one XCD
     int64_t per_xcd, total;   // strips (whole) or pairs, per XCD and in all
     int64_t grid;
 };
-inline StripRaster strip_raster(int64_t L, int64_t nstrips, int64_t mparts)
+inline StripRaster strip_raster(int64_t L, int64_t nstrips, int64_t mparts, bool heavy)
 {
     StripRaster r;
     r.nstrips = (int)nstrips;
     r.mparts = (int)mparts;
     const int64_t strips = L * nstrips, per = (strips + 7) / 8;
-    r.whole = 16 * strips >= 15 * 8 * per;
+    r.whole = !heavy && 16 * strips >= 15 * 8 * per;
     r.total = r.whole ? strips : strips * mparts;
     r.per_xcd = (r.total + 7) / 8;
     r.grid = r.per_xcd * 8 * (r.whole ? mparts : 1);
@@ -240,7 +245,9 @@ inline bool resident_nt_stores(int64_t K, int64_t Ncols, uint64_t c_address, int
     return at % 64 == 0 || (at % 32 == 0 && resident_ksteps(K) * D * S >= 60);
 }
 
-// The tile for C = W A of L limbs, or NT = 0 where none fits.  The candidates are the strip widths, work-group sizes and numbers of row parts that fit; the estimate, per work-group, is a
+// The tile for C = W A of L limbs, or NT = 0 where none fits.  The candidates are the strip widths, work-group sizes and numbers of row
+// parts that fit, up to eight parts, more where eight would leave compute units idle (eight -> more, one 36-bit limb: 65536 x 256 by
+// 256 x 16 42 -> 6.6 us, digit split and GEMM kernel 11.6; 14336 x 1000 by 1000 x 16 29 -> 11.3, 15.3).  The estimate, per work-group, is a
 // start, the digits that each wave cuts, and the rounds of row groups each wave runs (MFMAs of two waves sharing a SIMD, and the
 // epilogue), times the rounds of work-groups, a last partial round counting 0.4 of a full one; strips of 16 columns count
 // 15 % more, since each output row is stored in pieces half as long.  The constants are a fit to 2600 shapes (129 to 2048 values
@@ -262,7 +269,8 @@ inline ResidentTile resident_tile(int64_t M, int64_t K, int64_t Ncols, int64_t L
         for (int waves = 4; waves <= 8; waves += 4) {
             if (waves == 4 && lds > kLdsBytes / 2) continue;
             const int64_t slots = waves == 4 ? 512 : 256;
-            for (int64_t p = 1; p <= 8 && p <= groups; ++p) {
+            const int64_t most = slots / strips > 8 ? slots / strips : 8;   // few strips: parts to fill the chip
+            for (int64_t p = 1; p <= most && p <= groups; ++p) {
                 const int64_t per_part = (groups + p - 1) / p, wgs = strips * ((groups + per_part - 1) / per_part);
                 if ((wgs + 8 * p) * waves * 64 >= (int64_t)1 << 32) continue;   // a launch counts its threads in 32 bits (the raster rounds up)
                 const double wg = 2300.0 + 1400.0 * ks * NT / waves + (double)((per_part + waves - 1) / waves) * (3.1 * mfma + epilogue);
@@ -398,10 +406,13 @@ inline pcmm_status plan_geometry(int64_t M, int64_t K, int64_t Ncols, int32_t L,
     // rows of C that start inside half lines, where the GEMM kernel's raster joins lines better once there are many rows (14093 x
     // 475 by 475 x 19613 714 -> 900 us; 960 x 704 by 704 x 2937, int16 W 65 -> 69; up to 512 rows 1.47 times as fast); and the
     // integer epilogue of int16 W with few rows (64 x 832 by 832 x 16384, four 58-bit limbs 5 % slower).
+    // A long W and few columns: limb pairs read W once for two limbs (65536 x 1000 by 1000 x 16, four 36-bit limbs, resident -> GEMM
+    // kernel 46 -> 35 us; 65536 x 1250 by 1250 x 48 86 -> 74; 40000 x 1000 by 1000 x 16 30 -> 30, W of 38 MiB).
     g->resident = ResidentTile{0, 0, 0, 0};
+    const bool paired_long_w = g->pairs && M * K > (int64_t)40 << 20 && L * Ncols < 2048;
     const bool shortk = g->nkb == 2 && D <= 7 && g->epi != epi::EPI_INT;
     const bool inside_half_lines = Ncols % 8 != 0 && !(M <= 512 || (S == 1 && M <= 2048 && K <= 1024));
-    if (!shortk && !inside_half_lines && !(g->epi == epi::EPI_INT && S == 2 && M <= 100))
+    if (!shortk && !inside_half_lines && !paired_long_w && !(g->epi == epi::EPI_INT && S == 2 && M <= 100))
         g->resident = resident_tile(M, K, Ncols, L, D, S);
 
     g->w_kstride = (uint32_t)(g->MB * kFragBytes);

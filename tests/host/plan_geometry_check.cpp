@@ -157,7 +157,7 @@ int main()
     for (int64_t L = 1; L <= 3; ++L)
         for (int64_t n = 1; n <= 70; n += 3)
             for (int64_t m = 1; m <= 5; ++m) {
-                const StripRaster r = strip_raster(L, n, m);
+                const StripRaster r = strip_raster(L, n, m, n % 2);
                 std::vector<int> seen((size_t)(L * n * m), 0);
                 for (int64_t bid = 0; bid < r.grid; ++bid) {       // as strip_of on the device
                     const int64_t i = bid / 8, t = (bid % 8) * r.per_xcd + (r.whole ? i % r.per_xcd : i);

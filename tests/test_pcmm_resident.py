@@ -37,7 +37,7 @@ int main()
         CHECK(t.NT == 1 || (t.NT == 2 && D + S - 1 <= 6));
         const int64_t groups = (M + 16 * t.MT - 1) / (16 * t.MT), mparts = (groups + t.groups_per_part - 1) / t.groups_per_part;
         CHECK(t.groups_per_part >= 1 && t.groups_per_part <= groups);
-        const StripRaster r = strip_raster(L, (N + 16 * t.NT - 1) / (16 * t.NT), mparts);
+        const StripRaster r = strip_raster(L, (N + 16 * t.NT - 1) / (16 * t.NT), mparts, heavy_w(M, S, L, N));
         CHECK(r.grid <= 0x7fffffffL && r.grid * t.waves * 64 < (int64_t)1 << 32);
         // the epilogues the kernel is built for
         CHECK(g.epi == epi::EPI_INT ? g.D >= 7 : g.E <= 6 ? g.epi == epi::EPI_F64 : g.epi == epi::EPI_F64_G4 || g.epi == epi::EPI_F64_G4P);
@@ -52,6 +52,10 @@ int main()
         }
         // byte offsets: a k-step of residues, a block of outputs, and W up to the groups past the last row
         CHECK(64 * N * 8 <= (int64_t)1 << 31 && ((ks + 2) * g.MB + (groups + 8) * t.MT) * kFragBytes < (int64_t)1 << 32);
+        // many rows and few strips: the parts fill the compute units (within what whole row groups allow), and no XCD reads all of W
+        const int64_t strips = L * ((N + 16 * t.NT - 1) / (16 * t.NT)), slots = t.waves == 4 ? 512 : 256;
+        if (groups >= 8192) CHECK(strips * mparts * 2 > 256 || mparts * 2 > slots / strips);
+        if (groups >= 8192 && N <= 33 && L < 64) CHECK(!r.whole);
         ++used; parts += mparts > 1; four += t.waves == 4;
     }
     printf("%s\n", used > 1000 && parts > 10 && four > 100 ? "1" : "0");

@@ -19,7 +19,7 @@ using namespace pcmm_host;
 #define CHECK(c) do { if (!(c)) { printf("check failed: %s (M %ld K %ld N %ld L %d bits %d w %d)\n", #c, (long)M, (long)K, (long)N, L, bits, wb); return 1; } } while (0)
 int main()
 {
-    const long Ms[] = {1, 16, 64, 100, 513, 2049, 14336, 1 << 24}, Ks[] = {1, 64, 65, 128, 129, 192, 320, 512, 513, 777, 1024, 1089, 1280, 2048, 2049, 4096};
+    const long Ms[] = {1, 16, 64, 100, 513, 2049, 14336, 1 << 20, 1 << 24}, Ks[] = {1, 64, 65, 128, 129, 192, 320, 512, 513, 777, 1024, 1089, 1280, 2048, 2049, 4096};
     const long Ns[] = {1, 16, 33, 4096, 12300, 32768, 1 << 22};
     const int bitss[] = {24, 31, 33, 36, 41, 45, 48, 50, 51, 55, 58, 62};
     long used = 0, parts = 0, four = 0;

@@ -157,7 +157,7 @@ int main()
     for (int64_t L = 1; L <= 3; ++L)
         for (int64_t n = 1; n <= 70; n += 3)
             for (int64_t m = 1; m <= 5; ++m) {
-                const StripRaster r = strip_raster(L, n, m, n % 2);
+                const StripRaster r = strip_raster(L, n, m, n % 2, n % 5 ? 32 : 128);
                 std::vector<int> seen((size_t)(L * n * m), 0);
                 for (int64_t bid = 0; bid < r.grid; ++bid) {       // as strip_of on the device
                     const int64_t i = bid / 8, t = (bid % 8) * r.per_xcd + (r.whole ? i % r.per_xcd : i);
@@ -168,6 +168,9 @@ int main()
                 }
                 for (int x : seen) CHECK(x == 1);
             }
+    // whole strips, unless an XCD would run another round of work-groups for them
+    CHECK(strip_raster(2, 128, 4, false, 128).whole && strip_raster(2, 42, 4, false, 128).whole);
+    CHECK(!strip_raster(2, 42, 12, false, 128).whole && !strip_raster(3, 33, 5, false, 64).whole && !strip_raster(2, 128, 4, true, 128).whole);
 
     // per-limb constants, from the smallest to the largest supported primes
     const uint64_t qs[] = {8388617ull, 16777213ull, 68719403009ull, 68718428161ull, 1125899903827969ull,

@@ -176,32 +176,34 @@ inline bool gemm_nt_stores(int64_t M, int64_t K, int S, int64_t Ncols, uint64_t 
 }
 
 // Raster of the kernels that give strips of columns to work-groups and may cut the rows into parts: work-group b runs on XCD b % 8.
-// Each XCD takes an eighth of the strips (counted over all limbs) and all their parts, strips fastest, so that the work-groups resident
-// together store to the same rows side by side and the parts of a strip find its residues in their XCD's L2.  Few strips that are no
-// multiple of eight would leave XCDs idle: where more than a sixteenth would be, or an XCD with one strip more than the others would run
-// another round of work-groups, all (part, strip) pairs are cut into eight runs (slots: work-groups resident on an XCD.  Whole strips
-// in one more round, runs without it: 736 x 128 by 128 x 2640, two limbs 12.4 and 10.5 us; 877 x 392 by 392 x 528, int16 W, three
-// 45-bit limbs 14.6 and 10.4; over 240 shapes at most 1.15 times the better of the two, 1.39 without that condition).
-// Measured against those runs for all: 128 x 128 by 128 x 8192, two limbs 9.2 -> 8.0 us; 512 x 64 by 64 x 4096, two limbs 11.1 -> 10.8.
-// Every XCD then reads all of W.  With far more rows than columns (heavy_w) that is what counts, and the runs, which give an XCD an
-// eighth of the rows, are better: 14336 x 512 by 512 x 128, one 36-bit limb 13.5 -> 8.7 us, 65536 x 512 by 512 x 256 62.5 -> 43.9;
-// the line is where neither is ahead by more than a few percent (65536 x 200 by 200 x 256, four limbs 110 -> 122 with runs;
-// 14336 x 1250 by 1250 x 256 29.7 -> 25.6, on the other side of it).
+// Whole strips: each XCD takes an eighth of the strips (counted over all limbs) and all their parts, strips fastest, so that the parts of a
+// strip find its residues in their XCD's L2.  Runs: all (part, strip) pairs, strips fastest, cut into eight runs, so that the work-groups
+// resident together store to the same rows side by side, but the residues of a limb are read by each of the 8 / L XCDs that its run spans.
+// Whole strips where those further reads are at least a fifth of the stores, K (8 - L) / L > M / 5 (over 1500 shapes of at most 128 values of k
+// and 1466 longer ones whose rows are cut, whole strips against runs: up to 0.2 the same on average and up to 1.26 times as long,
+// 1792 x 121 by 121 x 2864, four limbs 36.6 and 44.3 us; from 0.3 on 2 to 9 % faster, never more than 5 % slower, 128 x 128 by 128 x 8192, two
+// limbs 9.2 and 8.0 us), unless
+// - the strips are few and no multiple of eight, so that more than a sixteenth of the XCDs' time would idle, or an XCD with one strip more
+//   than the others would run another round of work-groups (slots: work-groups resident on an XCD.  736 x 128 by 128 x 2640, two limbs
+//   12.4 and 10.5 us; 877 x 392 by 392 x 528, int16 W, three 45-bit limbs 14.6 and 10.4);
+// - W counts most (heavy_w, far more rows than columns), of which runs give an XCD an eighth of the rows to read: 14336 x 512 by 512 x 128,
+//   one 36-bit limb 13.5 -> 8.7 us with runs, 65536 x 512 by 512 x 256 62.5 -> 43.9, 14336 x 1250 by 1250 x 256 29.7 -> 25.6.
 inline bool heavy_w(int64_t M, int S, int64_t L, int64_t Ncols) { return M * S > 64 * L * Ncols; }
+inline bool whole_strips(int64_t M, int64_t K, int64_t Ncols, int64_t L, int S) { return 5 * K * (8 - L) > M * L && !heavy_w(M, S, L, Ncols); }
 struct StripRaster {
     int nstrips, mparts;      // strips per limb, parts per strip
     int whole;                // 1: all parts of a strip on one XCD
     int64_t per_xcd, total;   // strips (whole) or pairs, per XCD and in all
     int64_t grid;
 };
-inline StripRaster strip_raster(int64_t L, int64_t nstrips, int64_t mparts, bool heavy, int64_t slots)
+inline StripRaster strip_raster(int64_t L, int64_t nstrips, int64_t mparts, bool whole, int64_t slots)
 {
     StripRaster r;
     r.nstrips = (int)nstrips;
     r.mparts = (int)mparts;
     const int64_t strips = L * nstrips, per = (strips + 7) / 8;
     const auto rounds = [&](int64_t wgs) { return (wgs + slots - 1) / slots; };
-    r.whole = !heavy && 16 * strips >= 15 * 8 * per && rounds(per * mparts) <= rounds((strips * mparts + 7) / 8);
+    r.whole = whole && 16 * strips >= 15 * 8 * per && rounds(per * mparts) <= rounds((strips * mparts + 7) / 8);
     r.total = r.whole ? strips : strips * mparts;
     r.per_xcd = (r.total + 7) / 8;
     r.grid = r.per_xcd * 8 * (r.whole ? mparts : 1);

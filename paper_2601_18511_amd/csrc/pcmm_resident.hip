@@ -283,7 +283,7 @@ hipError_t launch(const Args &a, const ResidentTile &tile, int D, int S, int epi
     ka.groups = (int)((a.M + 16 * tile.MT - 1) / (16 * tile.MT));
     ka.groups_per_part = tile.groups_per_part;
     ka.raster = pcmm_host::strip_raster(a.L, (a.Ncols + 16 * tile.NT - 1) / (16 * tile.NT),
-                                        (ka.groups + ka.groups_per_part - 1) / ka.groups_per_part, pcmm_host::heavy_w(a.M, S, a.L, a.Ncols),
+                                        (ka.groups + ka.groups_per_part - 1) / ka.groups_per_part, pcmm_host::whole_strips(a.M, a.K, a.Ncols, a.L, S),
                                         tile.waves == 4 ? 64 : 32);
     if (ka.ksteps > a.nkb || ka.raster.grid > 0x7fffffffLL) return hipErrorInvalidValue;
 #define PCMM_RESIDENT_CASE(DD, SS, NN, EE) \

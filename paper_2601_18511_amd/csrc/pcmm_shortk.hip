@@ -267,7 +267,7 @@ hipError_t launch(const Args &a, int D, int S, int epi, hipStream_t st)
     const int64_t mparts = std::min<int64_t>(stages, std::max<int64_t>(1, (target + strips - 1) / strips));
     ka.stages_per_part = (int)((stages + mparts - 1) / mparts);
     ka.raster = pcmm_host::strip_raster(a.L, nstrips, (stages + ka.stages_per_part - 1) / ka.stages_per_part,
-                                          pcmm_host::heavy_w(a.M, S, a.L, a.Ncols), D == 7 && S == 2 ? 96 : 128);   // three or four waves on a SIMD
+                                          pcmm_host::whole_strips(a.M, a.K, a.Ncols, a.L, S), D == 7 && S == 2 ? 96 : 128);   // three or four waves on a SIMD
     const int64_t grid = ka.raster.grid;
     if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
 #define PCMM_SHORTK_CASE(DD, SS) \

@@ -37,7 +37,7 @@ int main()
         CHECK(t.NT == 1 || (t.NT == 2 && D + S - 1 <= 6));
         const int64_t groups = (M + 16 * t.MT - 1) / (16 * t.MT), mparts = (groups + t.groups_per_part - 1) / t.groups_per_part;
         CHECK(t.groups_per_part >= 1 && t.groups_per_part <= groups);
-        const StripRaster r = strip_raster(L, (N + 16 * t.NT - 1) / (16 * t.NT), mparts, heavy_w(M, S, L, N), t.waves == 4 ? 64 : 32);
+        const StripRaster r = strip_raster(L, (N + 16 * t.NT - 1) / (16 * t.NT), mparts, whole_strips(M, K, N, L, S), t.waves == 4 ? 64 : 32);
         CHECK(r.grid <= 0x7fffffffL && r.grid * t.waves * 64 < (int64_t)1 << 32);
         // the epilogues the kernel is built for
         CHECK(g.epi == epi::EPI_INT ? g.D >= 7 : g.E <= 6 ? g.epi == epi::EPI_F64 : g.epi == epi::EPI_F64_G4 || g.epi == epi::EPI_F64_G4P);

@@ -149,7 +149,7 @@ def mean(xs: Sequence[float]) -> float:
     return sum(xs) / len(xs)
 
 
-SPLIT = r"^split_kernel<|^split_pair_kernel$"
+SPLIT = r"^split_kernel<|^split_pair_kernel(<|$)"
 
 
 def run_mean(values: Dict[str, List[float]], kernels: Sequence[str]) -> float:
@@ -179,15 +179,22 @@ def copy_scale(directories: Sequence[str], counter: str, copy_kib: float) -> Opt
     return best[1], copy_kib / best[1]
 
 
-def workload_figures(name: str) -> dict:
-    """Algorithmic ops and bytes of a workload of pcmm_inputs (per pcmm_run), and the names of its kernels."""
+def workload_figures(name: str, kernel: Optional[str] = None) -> dict:
+    """Algorithmic ops and bytes (per pcmm_run) of a workload of pcmm_inputs, or of the product that "MxKxNcols_LxBITS_int8" (or
+    int16) names, and its MFMA kernel: `kernel`, or the one that the workloads run."""
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     if root not in sys.path:
         sys.path.insert(0, root)
     import pcmm_inputs as pi
 
-    w = pi.WORKLOADS[name]
-    fused = w.K <= 128 and w.prime_bits <= 50            # gemm_shortk_kernel reads the residues and cuts the digits itself
+    product = re.fullmatch(r"(\d+)x(\d+)x(\d+)_(\d+)x(\d+)_int(8|16)", name)
+    if product:
+        M, K, Ncols, L, bits, w_bits = (int(x) for x in product.groups())
+        w = pi.Workload(name, M, K, Ncols // 2, L, bits, w_bits)
+    else:
+        w = pi.WORKLOADS[name]
+    kernel = kernel or ("gemm_shortk_kernel" if w.K <= 128 and w.prime_bits <= 50 else "gemm_kernel")
+    fused = kernel != "gemm_kernel"                      # reads the residues and cuts the digits itself
     digits_bytes = w.K * w.Ncols * (8 * w.L if fused else w.digit_planes)
     return {
         "desc": "W %dx%d int%d, A %dx%d uint64 residues, L=%d primes of %d bits, %d digit planes, S=%d slices"
@@ -196,14 +203,14 @@ def workload_figures(name: str) -> dict:
         "gemm_bytes": float(digits_bytes + w.M * w.K * w.slices + 8 * w.M * w.Ncols * w.L),
         "gemm_parts": (digits_bytes, w.M * w.K * w.slices, 8 * w.M * w.Ncols * w.L),
         "split_bytes": float(w.K * w.Ncols * (8 * w.L + w.digit_planes)),
-        "mfma_kernel": "gemm_shortk_kernel" if fused else "gemm_kernel",
+        "mfma_kernel": kernel,
     }
 
 
 def trace_summary(workload: str, fig: dict, trace: Dict[str, List[float]], commands: Sequence[str]) -> str:
-    mine = pick(trace, r"gemm_kernel|gemm_shortk_kernel|split_kernel|split_pair_kernel|transpose_u64_kernel|mfma_probe_kernel")
+    mine = pick(trace, r"gemm_kernel|gemm_shortk_kernel|gemm_resident_kernel|split_kernel|split_pair_kernel|transpose_u64_kernel|mfma_probe_kernel")
     lines = ["rocprofv3 kernel trace of the PCMM kernels on the %s workload" % workload,
-             "(%s; one pcmm_run = the split kernels + the MFMA kernels, or gemm_shortk_kernel alone)" % fig["desc"], ""]
+             "(%s; one pcmm_run = the split kernels + the MFMA kernels, or gemm_shortk_kernel or gemm_resident_kernel alone)" % fig["desc"], ""]
     lines += ["commands (from /tmp with TMPDIR=/tmp on the MI355X box, R = repository root):"] + ["  " + c for c in commands] + [""]
     lines.append("%-46s %6s %12s %12s %12s" % ("kernel", "calls", "avg_ms", "min_ms", "max_ms"))
     for k in mine:
@@ -370,7 +377,9 @@ def streaming_summary(trace_dir: Optional[str], fetch_dir: str, write_dir: str, 
 # --------------------------------------------------------------------------------------------------
 def main(argv: Optional[Sequence[str]] = None) -> int:
     ap = argparse.ArgumentParser(description=__doc__.split("\n\n")[0])
-    ap.add_argument("--workload", required=True, help="name in pcmm_inputs.WORKLOADS")
+    ap.add_argument("--workload", required=True, help="name in pcmm_inputs.WORKLOADS, or a product as MxKxNcols_LxBITS_int8 (or int16)")
+    ap.add_argument("--kernel", choices=["gemm_kernel", "gemm_shortk_kernel", "gemm_resident_kernel"],
+                    help="the MFMA kernel that the product runs, if not the one a workload of its K and primes does")
     ap.add_argument("--trace", help="output directory of a rocprofv3 --kernel-trace run")
     ap.add_argument("--pmc", action="append", default=[], help="output directory of a rocprofv3 --pmc run (repeatable)")
     ap.add_argument("--command", action="append", default=[], help="a command line to quote in the summaries (repeatable)")
@@ -381,7 +390,7 @@ def main(argv: Optional[Sequence[str]] = None) -> int:
     ap.add_argument("--note", action="append", default=[], help="a line to add to the streaming summary (repeatable)")
     args = ap.parse_args(argv)
 
-    fig = workload_figures(args.workload)
+    fig = workload_figures(args.workload, args.kernel)
     stem = "%s%s_%s" % (args.out_prefix, fig["mfma_kernel"], args.workload)
     written = []
 

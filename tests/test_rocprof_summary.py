@@ -143,11 +143,26 @@ def test_streaming_summary_lists_the_transform_kernels_of_both_decode_shapes(tmp
     assert abs(float(one[-1]) - 2 * 268435456 / 0.2e-3 / 1e9) < 1.0
 
 
-def test_a_run_of_limb_pairs_and_a_single_limb_is_added_up(tmp_path):
+def test_a_product_that_runs_as_one_kernel(tmp_path):
+    """Sizes in place of a workload's name; the kernel that keeps all digits in LDS reads residues and has no digit planes."""
+    k = "void (anonymous namespace)::gemm_resident_kernel<6, 1, 2, 3, 0, true>((anonymous namespace)::KArgs)"
+    _write_csv(str(tmp_path / "kt" / "h" / "1_kernel_trace.csv"), ["Dispatch_Id", "Kernel_Name", "Start_Timestamp", "End_Timestamp"],
+               [[i, k, 0, 200000] for i in range(4)])
+    name = "1000x777x12300_3x45_int8"
+    fig = rs.workload_figures(name, "gemm_resident_kernel")
+    assert fig["gemm_bytes"] == 3 * 8 * 12300 * (777 + 1000) + 1000 * 777 and fig["int8_ops"] == 2.0 * 1000 * 777 * 12300 * 3 * 6
+    out = str(tmp_path) + os.sep
+    assert rs.main(["--workload", name, "--kernel", "gemm_resident_kernel", "--trace", str(tmp_path / "kt"), "--out-prefix", out]) == 0
+    text = open(out + "gemm_resident_kernel_%s_kernel_trace.txt" % name).read()
+    assert "gemm_resident_kernel: average 0.200 ms" in text and "= %.0f TOP/s" % (fig["int8_ops"] / 0.2e-3 / 1e12) in text
+
+
+@pytest.mark.parametrize("nt", ["", "<2>"])              # the split of a limb pair, as it was built and as it is built
+def test_a_run_of_limb_pairs_and_a_single_limb_is_added_up(tmp_path, nt):
     """Three limbs: one run launches the pair and the single instantiation of both kernels."""
     gk, sk = "void (anonymous namespace)::gemm_kernel<4, 4, %s>((anonymous namespace)::GemmArgs)", "(anonymous namespace)::split%s(unsigned long const*)"
     pair, single = gk % "1, 9, 1, 5", gk % "2, 5, 1, 0"
-    spair, ssingle = sk % "_pair_kernel", "void " + sk % "_kernel<5>"
+    spair, ssingle = sk % ("_pair_kernel" + nt), "void " + sk % "_kernel<5>"
     w = 4096 * 14336 * 32768
     ops, planes = 2.0 * w * 14, 14336 * 32768 * 14
     runs = [(spair, 1e6), (ssingle, 0.5e6), (pair, 14e6), (single, 7e6)]        # ns
@@ -161,7 +176,7 @@ def test_a_run_of_limb_pairs_and_a_single_limb_is_added_up(tmp_path):
     fig = rs.workload_figures("ffn_down")
     assert fig["int8_ops"] == ops and fig["gemm_parts"][0] == planes
     text = rs.trace_summary("ffn_down", fig, rs.read_kernel_trace(str(tmp_path / "kt")), [])
-    assert {"split_pair_kernel", "split_kernel<5>", "gemm_kernel<4, 4, 1, 9, 1, 5>", "gemm_kernel<4, 4, 2, 5, 1, 0>"} <= set(names(text))
+    assert {"split_pair_kernel" + nt, "split_kernel<5>", "gemm_kernel<4, 4, 1, 9, 1, 5>", "gemm_kernel<4, 4, 2, 5, 1, 0>"} <= set(names(text))
     assert "average 21.000 ms (min 21.000 ms, median 21.000 ms) over 3 runs of 2 launches" in text
     assert "= %.0f TOP/s" % (ops / 21e-3 / 1e12) in text
     assert "average 1.500 ms (min 1.500 ms)" in text
@@ -182,4 +197,4 @@ def test_a_run_of_limb_pairs_and_a_single_limb_is_added_up(tmp_path):
     text = rs.counter_summary("ffn_down", fig, counters, durations, [])
     assert "gemm_kernel<4, 4, 1, 9, 1, 5> + gemm_kernel<4, 4, 2, 5, 1, 0>" in text
     assert "1.00 GHz" in text and "70.0 %" in text                                     # (0.8 x 14 + 0.5 x 7) / 21
-    assert rs.STREAMING.search("split_pair_kernel")
+    assert rs.STREAMING.search("split_pair_kernel" + nt)

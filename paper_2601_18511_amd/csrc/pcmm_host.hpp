@@ -311,6 +311,45 @@ struct Geometry {
     uint32_t a_kstride;        // bytes between k-steps of one limb's digit chunks
 };
 
+// Which of the two ways a contraction takes whose digits fit LDS is decided by an estimate of both in microseconds.  Their form: rounds of
+// work-groups (a last partial one counting more than its share) times the clocks of one at 2 GHz, and the memory traffic, most of which runs
+// beside them (rows of C that start inside lines cost more); the digit split in front of the GEMM kernel.  The constants are a fit to
+// 3600 shapes measured both ways (16 to 30000 rows, 129 to 2560 values of k, 16 to 40000 columns, 24 to 62 bits, both widths of W), logarithmic
+// deviation 0.15 and 0.12.  Taking the resident kernel where its estimate is below 0.92 of the other's is 0.66 times the GEMM kernel's time on
+// average, 0.4 % behind the better of the two, longer than the GEMM kernel by more than 3 % at 37 of the shapes and by more than 10 % at 10
+// (always taking it: 168 and 85, where strips are a few more than whole rounds, 1500 x 777 by 777 x 4100, two 36-bit limbs 69 -> 85 us, or
+// one wave a SIMD contracts, 64 x 832 by 832 x 16384, four 58-bit limbs of int16 W 5 to 16 % slower).
+constexpr double kResidentMargin = 0.92;
+inline double rounds_of(double full, double whole, double part) { return part * whole + (1.0 - part) * full; }
+inline double beside(double a, double b, double exposed) { return a > b ? a + exposed * b : b + exposed * a; }
+inline double ceil_of(double x) { return (double)(int64_t)x < x ? (double)(int64_t)x + 1.0 : (double)(int64_t)x; }
+inline double resident_us(const ResidentTile &t, int64_t M, int64_t K, int64_t Ncols, int64_t L, int D, int S)
+{
+    const int64_t ks = resident_ksteps(K), groups = (M + 16 * t.MT - 1) / (16 * t.MT), mparts = (groups + t.groups_per_part - 1) / t.groups_per_part;
+    const double mfma = 16.0 * ks * t.MT * t.NT * D * S, epilogue = t.MT * t.NT * (32.0 * (D + S - 1) + 360.0);
+    // a work-group: start, digits, the MFMAs of the waves that share a SIMD, and each wave's epilogues
+    const int wgs_cu = t.waves == 4 ? 2 : 1;
+    const double wg = 2900.0 + 1000.0 * ks * t.NT / t.waves + mfma * ((t.groups_per_part * wgs_cu + 3) / 4) +
+                      (double)((t.groups_per_part + t.waves - 1) / t.waves) * (0.98 * epilogue + 0.082 * mfma);
+    const double full = (double)(L * ((Ncols + 16 * t.NT - 1) / (16 * t.NT)) * mparts) / (256 * wgs_cu);
+    // of two work-groups a compute unit, one alone takes half the time of both
+    const double rounds = wgs_cu == 2 ? rounds_of(full, 0.5 * ceil_of(2.0 * full), 0.9) : rounds_of(full, ceil_of(full), 0.97);
+    const double compute = rounds * wg / 2000.0 * (t.NT == 1 ? 1.2 : 1.0);
+    const double memory = 8e-6 * L * Ncols * (M * (Ncols % 16 == 0 ? 0.13 : Ncols % 8 == 0 ? 0.17 : 0.25) + 0.16 * K);
+    return 0.9 + beside(compute, memory, 0.42);
+}
+inline double gemm_us(const Geometry &g, int64_t M, int64_t K, int64_t Ncols, int64_t L)
+{
+    // work-groups a few more than whole rounds cost little: slots become free at different times
+    auto products = [&](int64_t limbs, int64_t ntiles, int per_block) {       // per_block: int8 products of a row block and n-tile
+        const double full = (double)(limbs * g.mtiles * ntiles) / 512;
+        return rounds_of(full, ceil_of(full), full > 1.0 && ceil_of(full) - full > 0.9 ? 0.1 : 0.48) * (7700.0 + g.ksteps * (780.0 + 22.4 * g.MT * per_block)) * (g.WM == 2 ? 0.86 : 1.0) / 2000.0;
+    };
+    const double compute = products(g.pairs, g.pair_ntiles, kPairDigits) + products(L - 2 * g.pairs, g.ntiles, g.NT * g.D * g.S);
+    const double memory = 8e-6 * L * M * Ncols * (Ncols % 8 == 0 ? 0.21 : 0.29);
+    return 7.6 + 0.16e-6 * (8 + g.D) * L * K * Ncols + beside(compute, memory, 0.26);
+}
+
 // Validates the arguments of pcmm_plan_create that need no device and derives the geometry.
 inline pcmm_status plan_geometry(int64_t M, int64_t K, int64_t Ncols, int32_t L, const uint64_t *primes_host,
                                  int32_t prime_bits, int32_t w_bits, int32_t device, Geometry *g)
@@ -406,20 +445,18 @@ inline pcmm_status plan_geometry(int64_t M, int64_t K, int64_t Ncols, int32_t L,
     g->pair_gn = g->mtiles <= 16 && K <= 2048 ? 16 : 8;
 
     // Contractions whose digits fit LDS run as one kernel that cuts the digits itself (those of at most 128 values of k below
-    // 2^50 as pcmm_shortk's).  Measured over 2200 shapes of 129 to 2048 values of k against digit split and GEMM kernel: 1.43 times
-    // as fast on average, none slower (128 x 384 by 384 x 4096, two limbs 22 -> 10 us; 4096 x 500 by 500 x 8192, four limbs
-    // 467 -> 311; 9536 x 1454 by 1454 x 8192, two limbs 1000 -> 948), but for two cases that keep the old kernels:
-    // rows of C that start inside half lines, where the GEMM kernel's raster joins lines better once there are many rows (14093 x
-    // 475 by 475 x 19613 714 -> 900 us; 960 x 704 by 704 x 2937, int16 W 65 -> 69; up to 512 rows 1.47 times as fast); and the
-    // integer epilogue of int16 W with few rows (64 x 832 by 832 x 16384, four 58-bit limbs 5 % slower).
+    // 2^50 as pcmm_shortk's) where that is the faster way: by the estimates, or whenever a strip has no more than one row group
+    // and four waves, where it always is (48 x 131 by 131 x 8208, two 56-bit limbs 24 -> 13 us).
     // A long W and few columns: limb pairs read W once for two limbs (65536 x 1000 by 1000 x 16, four 36-bit limbs, resident -> GEMM
     // kernel 46 -> 35 us; 65536 x 1250 by 1250 x 48 86 -> 74; 40000 x 1000 by 1000 x 16 30 -> 30, W of 38 MiB).
     g->resident = ResidentTile{0, 0, 0, 0};
-    const bool paired_long_w = g->pairs && M * K > (int64_t)40 << 20 && L * Ncols < 2048;
     const bool shortk = g->nkb == 2 && D <= 7 && g->epi != epi::EPI_INT;
-    const bool inside_half_lines = Ncols % 8 != 0 && !(M <= 512 || (S == 1 && M <= 2048 && K <= 1024));
-    if (!shortk && !inside_half_lines && !paired_long_w && !(g->epi == epi::EPI_INT && S == 2 && M <= 100))
-        g->resident = resident_tile(M, K, Ncols, L, D, S);
+    const bool paired_long_w = g->pairs && M * K > (int64_t)40 << 20 && L * Ncols < 2048;
+    if (!shortk && !paired_long_w) {
+        const ResidentTile t = resident_tile(M, K, Ncols, L, D, S);
+        if (t.NT && ((M <= 16 * t.MT && t.waves == 4) || resident_us(t, M, K, Ncols, L, D, S) < kResidentMargin * gemm_us(*g, M, K, Ncols, L)))
+            g->resident = t;
+    }
 
     g->w_kstride = (uint32_t)(g->MB * kFragBytes);
     g->a_kstride = (uint32_t)(g->ntiles * g->NT * D * kFragBytes);

@@ -1,5 +1,6 @@
 """Contractions whose digits fit LDS (pcmm_resident.hip): the tile that the plan chooses, on the host, and the products against the
-oracle on the GPU, bit-exact, at the edges of row groups, strips and k-steps and for every kernel variant."""
+oracle on the GPU, bit-exact, at the edges of row groups, strips and k-steps (SHAPES, strips of 16 columns) and for every kernel variant with
+several row groups a wave (TURNS)."""
 import os
 import shutil
 import subprocess
@@ -8,6 +9,8 @@ import numpy as np
 import pytest
 
 import pcmm_inputs as pi
+import plan_forms
+from seeded_products import check, run
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -103,6 +106,69 @@ SHAPES = [
     (3000, 200, 64, 36, 1, 8),        # few strips: the rows are cut into parts
     (5000, 130, 32, 50, 1, 16),
 ]
+
+
+# Waves that take several row groups one after the other, a line for each (digits, slices, strip width, epilogue) and in it each remainder that the
+# k-steps leave in the sets of W registers; whole half lines, so that the address of C decides between the two kinds of stores
+TURNS = [
+    (513, 200, 2040, 30, 3, 8), (513, 300, 2040, 30, 3, 8), (600, 350, 3000, 30, 2, 8), (513, 129, 3000, 30, 2, 8),
+    (2100, 193, 3000, 30, 1, 8), (257, 257, 4096, 28, 4, 8), (2049, 350, 3000, 24, 1, 8), (2100, 129, 3000, 28, 1, 8),
+    (777, 193, 2000, 30, 2, 16), (777, 320, 2040, 28, 2, 16), (777, 350, 2040, 30, 2, 16), (777, 129, 2000, 30, 2, 16),
+    (257, 129, 4096, 30, 4, 16), (193, 200, 4096, 28, 4, 16), (2500, 257, 2000, 28, 1, 16),
+    (513, 193, 2040, 38, 3, 8), (600, 257, 2000, 36, 3, 8), (513, 350, 3000, 36, 2, 8), (513, 150, 2040, 33, 3, 8),
+    (300, 193, 4096, 36, 4, 8), (300, 129, 4096, 32, 4, 8),
+    (777, 193, 2000, 36, 2, 16), (777, 300, 1000, 35, 4, 16), (2049, 350, 2000, 38, 1, 16), (777, 129, 2000, 38, 2, 16),
+    (2500, 193, 1000, 33, 2, 16), (193, 129, 4096, 38, 4, 16),
+    (777, 193, 1000, 45, 4, 8), (777, 257, 2000, 40, 2, 8), (777, 350, 1000, 45, 4, 8), (1000, 129, 3000, 45, 1, 8),
+    (513, 200, 2000, 40, 4, 8), (2500, 257, 2000, 42, 1, 8), (2500, 350, 2000, 40, 1, 8), (513, 129, 4096, 42, 2, 8),
+    (193, 129, 2040, 40, 4, 16), (193, 193, 2000, 40, 4, 16), (200, 300, 2040, 45, 4, 16),
+    (513, 129, 4096, 48, 1, 8), (513, 200, 2000, 50, 2, 8), (513, 257, 4096, 50, 1, 8),
+    (600, 150, 1000, 52, 4, 8), (513, 193, 2000, 52, 2, 8), (600, 257, 2040, 52, 2, 8),
+    (200, 129, 4096, 49, 2, 16), (193, 200, 2000, 50, 4, 16), (200, 257, 4096, 48, 2, 16),
+    (200, 129, 2040, 52, 4, 16), (513, 193, 4096, 52, 1, 16), (600, 257, 2000, 52, 2, 16),
+    (513, 129, 1000, 55, 4, 8), (513, 193, 2000, 55, 2, 8), (513, 257, 2040, 55, 2, 8),
+    (193, 129, 4096, 55, 2, 16), (193, 193, 2000, 62, 4, 16), (193, 320, 2000, 62, 4, 16),
+]
+# as many digits as LDS holds, by the digit count; and one strip of 32 columns of them
+FULL_LDS = [(64, 2560, 4096, 30, 1, 8), (300, 2497, 40, 28, 1, 16), (64, 2048, 100, 38, 1, 8), (100, 1664, 72, 45, 1, 8), (100, 1408, 40, 50, 1, 8),
+            (70, 1280, 40, 60, 1, 8), (1000, 1280, 4096, 30, 4, 8), (1000, 1024, 4096, 36, 4, 8), (777, 832, 4096, 45, 4, 8)]
+
+
+def test_the_faster_of_the_two_ways_runs(tmp_path):
+    """Shapes on either side of the estimates that choose between this kernel and the digit split with the GEMM kernel, each measured both ways."""
+    if shutil.which("g++") is None:
+        pytest.skip("no g++")
+    gemm = [(1500, 777, 4100, 36, 2, 8), (2048, 1024, 4100, 36, 2, 8), (2500, 1024, 4100, 36, 2, 8), (600, 777, 4100, 36, 2, 16),
+            (2048, 1284, 848, 36, 5, 16), (4627, 1839, 1352, 36, 2, 8), (4895, 255, 8208, 62, 2, 16), (17, 832, 16384, 58, 4, 16)]
+    resident = [(1000, 777, 12300, 45, 3, 8), (128, 128, 64, 60, 2, 8), (64, 300, 4096, 58, 2, 16), (600, 300, 4096, 36, 2, 16),
+                (48, 131, 8208, 56, 2, 8), (1000, 1024, 12300, 36, 2, 8), (51, 196, 14240, 48, 5, 8)]
+    assert all(line.startswith("gemm") for line in plan_forms.describe(gemm, tmp_path)), plan_forms.describe(gemm, tmp_path)
+    assert all(line.startswith("resident") for line in plan_forms.describe(resident, tmp_path)), plan_forms.describe(resident, tmp_path)
+
+
+def test_turns_reach_every_variant(tmp_path):
+    """Over a grid of shapes: every variant that a plan runs with several row groups a wave is among those of TURNS."""
+    if shutil.which("g++") is None:
+        pytest.skip("no g++")
+
+    def variants(shapes):
+        lines = [line.replace("g4p", "g4").split() for line in plan_forms.describe(shapes, tmp_path)]      # one kernel for both
+        return {(f[1], f[2], f[3], f[4], f[6]) for f in lines if f[0] == "resident" and f[7] == "turns"}
+
+    grid = [(M, K, N, bits, L, w_bits) for M in (193, 257, 513, 1000, 2100, 4096) for K in (129, 200, 260, 330, 400, 500, 777, 1024, 1400, 2500)
+            for N in (512, 2000, 4096, 12288) for bits in (28, 36, 44, 49, 53, 60) for L in (1, 2, 4) for w_bits in (8, 16)]
+    missing = variants(grid) - variants(TURNS)
+    assert not missing, sorted(missing)
+    assert {v[:4] for v in variants(TURNS)} == {v[:4] for v in variants(grid)} and len({v[:4] for v in variants(TURNS)}) == 17
+    lines = [line.split() for line in plan_forms.describe(TURNS, tmp_path)]
+    assert all(f[0] == "resident" and f[7] == "turns" for f in lines) and all(shape[2] % 8 == 0 for shape in TURNS)
+    assert all(line.startswith("resident") for line in plan_forms.describe(FULL_LDS, tmp_path))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,K,Ncols,bits,L,w_bits", TURNS + FULL_LDS)
+def test_several_row_groups_a_wave(gpu_device, M, K, Ncols, bits, L, w_bits):
+    check(*run(gpu_device, M, K, Ncols, bits, L, w_bits, M % 2 == 0, offsets=(32, 33)))
 
 
 @pytest.mark.gpu

@@ -814,8 +814,12 @@ hipError_t launch_gemm_ds(const pcmm_plan *p, const GemmArgs &ga, int64_t grid, 
         else return hipErrorInvalidValue;
     } else if (p->epi == EPI_F64_G4 || p->epi == EPI_F64_G4P) {
         if constexpr (D <= 7 && D + S - 1 >= 7) {
-            if (p->epi == EPI_F64_G4) launch_alone_or_not<WM, MT, NT, D, S, EPI_F64_G4>(ga, g, st);
-            else launch_alone_or_not<WM, MT, NT, D, S, EPI_F64_G4P>(ga, g, st);
+            // the grouping of short contractions (G4P) only for four waves: those of few rows, if they come here at all, have
+            // accumulators small enough for either grouping
+            if constexpr (WM == 4) {
+                if (p->epi == EPI_F64_G4P) launch_alone_or_not<WM, MT, NT, D, S, EPI_F64_G4P>(ga, g, st);
+                else launch_alone_or_not<WM, MT, NT, D, S, EPI_F64_G4>(ga, g, st);
+            } else launch_alone_or_not<WM, MT, NT, D, S, EPI_F64_G4>(ga, g, st);
         } else return hipErrorInvalidValue;
     } else {
         if constexpr (D >= 7) {

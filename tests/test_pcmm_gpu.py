@@ -358,7 +358,8 @@ def test_block_identity_on_the_gpu(gpu_device):
         assert (acc == full[:, u * 96:(u + 1) * 96, :]).all()
 
 
-def test_plan_reuse_and_two_plans_interleaved(gpu_device):
+@pytest.mark.parametrize("K1,K2,digit_planes", [(256, 128, False), (2100, 2600, True)])   # one kernel a run; digit split and GEMM kernel
+def test_plan_reuse_and_two_plans_interleaved(gpu_device, K1, K2, digit_planes):
     """One plan run on two different inputs, and a second plan in between: scratch is per plan."""
     import torch
 
@@ -367,11 +368,13 @@ def test_plan_reuse_and_two_plans_interleaved(gpu_device):
 
     rng = np.random.default_rng(8)
     primes = pi.ntt_primes(36, 1 << 13, 2)
-    W1, W2 = _rand_W(rng, 100, 256, 8), _rand_W(rng, 60, 128, 8)
-    A1a, A1b, A2 = _rand_A(rng, 256, 300, primes), _rand_A(rng, 256, 300, primes), _rand_A(rng, 128, 40, primes)
+    W1, W2 = _rand_W(rng, 100, K1, 8), _rand_W(rng, 60, K2, 8)
+    A1a, A1b, A2 = _rand_A(rng, K1, 300, primes), _rand_A(rng, K1, 300, primes), _rand_A(rng, K2, 40, primes)
     p1 = pkg.pcmm_plan_create(torch.from_numpy(W1).to(gpu_device), primes, 36, 300)
     p2 = pkg.pcmm_plan_create(torch.from_numpy(W2).to(gpu_device), primes, 36, 40)
     assert pkg.pcmm_plan_workspace_bytes(p1) > 0
+    for plan, K, N in ((p1, K1, 300), (p2, K2, 40)):                       # digit scratch: five bytes a residue
+        assert (pkg.pcmm_plan_workspace_bytes(plan) >= 128 * K + 2 * K * N * 5 * 9 // 10) == digit_planes
 
     def run(plan, A, M):
         A_dev = torch.from_numpy(A.view(np.int64)).to(gpu_device)
@@ -434,7 +437,8 @@ def test_mfma_probe_reports_a_plausible_rate(gpu_device):
     assert tops0 >= 0.9 * tops
 
 
-def test_pcmm_run_inside_a_hip_graph_replays_correctly(gpu_device):
+@pytest.mark.parametrize("K", [320, 2100])         # one kernel; the digit split and the GEMM kernel
+def test_pcmm_run_inside_a_hip_graph_replays_correctly(gpu_device, K):
     """pcmm_run only enqueues kernels (no allocation, no memset, no synchronisation), so it can be
     captured; every replay, with eager work and synchronisations in between, must match the oracle."""
     import torch
@@ -444,9 +448,9 @@ def test_pcmm_run_inside_a_hip_graph_replays_correctly(gpu_device):
 
     rng = np.random.default_rng(77)
     primes = pi.ntt_primes(36, 1 << 13, 2)
-    W = _rand_W(rng, 130, 320, 8)
+    W = _rand_W(rng, 130, K, 8)
     plan = pkg.pcmm_plan_create(torch.from_numpy(W).to(gpu_device), primes, 36, 200)
-    A_dev = torch.zeros((2, 320, 200), dtype=torch.int64, device=gpu_device)
+    A_dev = torch.zeros((2, K, 200), dtype=torch.int64, device=gpu_device)
     C_dev = torch.zeros((2, 130, 200), dtype=torch.int64, device=gpu_device)
     side = torch.cuda.Stream()
     side.wait_stream(torch.cuda.current_stream())
@@ -458,7 +462,7 @@ def test_pcmm_run_inside_a_hip_graph_replays_correctly(gpu_device):
     with torch.cuda.graph(graph):
         pkg.pcmm_run(plan, A_dev, C_dev)          # current stream is the capture stream here
     for rep in range(3):
-        A = _rand_A(rng, 320, 200, primes)
+        A = _rand_A(rng, K, 200, primes)
         A_dev.copy_(torch.from_numpy(A.view(np.int64)))
         C_dev.fill_(-1)                            # eager work between replays
         torch.cuda.synchronize()
@@ -497,7 +501,8 @@ def test_seeded_sweep_of_small_shapes(gpu_device):
         assert (got == want).all(), (M, K, Ncols, bits, L, wbits, int((got != want).sum()))
 
 
-def test_two_plans_on_two_streams_at_once(gpu_device):
+@pytest.mark.parametrize("shapes", [((320, 1024, 2048), (192, 768, 4096)), ((320, 2100, 2048), (100, 2600, 1000))])   # the second: with digit scratch
+def test_two_plans_on_two_streams_at_once(gpu_device, shapes):
     """Runs of different plans may overlap in time (each plan has its own digit scratch): two plans enqueued
     alternately on two streams of the default priority, three rounds, every result exact."""
     import torch
@@ -507,7 +512,6 @@ def test_two_plans_on_two_streams_at_once(gpu_device):
 
     rng = np.random.default_rng(21)
     primes = pi.ntt_primes(36, 1 << 13, 3)
-    shapes = ((320, 1024, 2048), (192, 768, 4096))
     Ws = [_rand_W(rng, M, K, 8) for M, K, _ in shapes]
     As = [[_rand_A(rng, K, N, primes) for _ in range(3)] for _, K, N in shapes]
     streams = [torch.cuda.Stream(device=gpu_device), torch.cuda.Stream(device=gpu_device)]

@@ -12,7 +12,7 @@ import pcmm_inputs as pi
 pytestmark = pytest.mark.gpu
 
 
-def _both(W, A, primes, bits, dev):
+def _both(W, A, primes, bits, dev, digit_planes=None):
     """C from pcmm_run and C from pcmm_run_noalloc for the same plan and input."""
     import torch
 
@@ -23,6 +23,9 @@ def _both(W, A, primes, bits, dev):
     A_dev = torch.from_numpy(A.view(np.int64)).to(dev)
     C_ref = torch.full((L, W.shape[0], Ncols), -1, dtype=torch.int64, device=dev)
     C_new = torch.full((L, W.shape[0], Ncols), -2, dtype=torch.int64, device=dev)
+    if digit_planes is not None:               # whether the plan owns digit scratch, beside which its other buffers are small here
+        made = pkg.pcmm_plan_workspace_bytes(plan) >= pkg.pcmm_plan_digits(plan) * A.size
+        assert made == digit_planes
     pkg.pcmm_run(plan, A_dev, C_ref)
     pkg.pcmm_run_noalloc(plan, A_dev, C_new)
     torch.cuda.synchronize()
@@ -40,15 +43,20 @@ def _case(rng, M, K, Ncols, bits, L, wbits):
     return W, A, primes
 
 
-def test_two_calls_in_a_row_the_second_smaller(gpu_device):
-    """The static buffer keeps the first call's digits; the second, smaller call must not see them."""
+@pytest.mark.parametrize("shapes,digit_planes", [
+    (((300, 1000, 1000, 36, 2, 8), (70, 100, 50, 50, 3, 16)), False),      # kernels that cut the digits themselves
+    (((40, 2600, 3000, 30, 1, 8), (40, 1700, 1000, 44, 1, 8), (33, 1500, 333, 50, 1, 16)), True),
+    (((40, 2100, 2000, 36, 2, 8), (33, 2049, 333, 36, 3, 8)), True),       # limb pairs, then three limbs singly
+])
+def test_two_calls_in_a_row_the_second_smaller(gpu_device, shapes, digit_planes):
+    """The static buffer keeps an earlier call's digits; a later, smaller call must not see them."""
     from oracle import pcmm_oracle
 
     rng = np.random.default_rng(77)
-    for shape in ((300, 1000, 1000, 36, 2, 8), (70, 100, 50, 50, 3, 16)):
+    for shape in shapes:
         print("pcmm_run_noalloc case", shape, flush=True)
         W, A, primes = _case(rng, *shape)
-        ref, new = _both(W, A, primes, shape[3], gpu_device)
+        ref, new = _both(W, A, primes, shape[3], gpu_device, digit_planes)
         assert (new == ref).all(), int((new != ref).sum())
         assert (new == pcmm_oracle(W, A, primes)).all()
 
@@ -59,9 +67,13 @@ def test_tiny_workload(gpu_device):
     assert (new == ref).all()
 
 
-@pytest.mark.parametrize("K,L,bits", [(192, 1, 36), (192, 2, 36), (256, 3, 45)])
-def test_largest_digit_planes_that_fill_the_static_buffer(gpu_device, K, L, bits):
-    """More than 128 values of k, so that digit planes are made: one limb, a limb pair, three limbs of six digits."""
+@pytest.mark.parametrize("K,L,bits,digit_planes", [
+    (192, 1, 36, False), (192, 2, 36, False), (256, 3, 45, False),         # no digit planes are made; the limit is the documented one
+    (2600, 1, 30, True), (2100, 1, 36, True), (2176, 2, 36, True),         # four digits, five, a limb pair
+    (1700, 3, 45, True), (1500, 1, 53, True), (1400, 2, 61, True),         # six, seven, eight
+])
+def test_largest_digit_planes_that_fill_the_static_buffer(gpu_device, K, L, bits, digit_planes):
+    """Contractions short enough to run as one kernel, and ones that fill the buffer with digit planes to its last columns."""
     import torch
 
     import paper_2601_18511_amd as pkg
@@ -69,10 +81,11 @@ def test_largest_digit_planes_that_fill_the_static_buffer(gpu_device, K, L, bits
 
     rng = np.random.default_rng(K + L)
     limit, D = pkg.pcmm.NOALLOC_SCRATCH_BYTES, -(-bits // 8)
-    ncols_fit = limit // (L * 256 * D) // 32 * 32
-    assert L * 256 * ncols_fit * D <= limit < L * 256 * (ncols_fit + 32) * D
+    K_padded = -(-K // 128) * 128
+    ncols_fit = limit // (L * K_padded * D) // 32 * 32
+    assert L * K_padded * ncols_fit * D <= limit < L * K_padded * (ncols_fit + 32) * D
     W, A, primes = _case(rng, 5, K, ncols_fit, bits, L, 8)
-    ref, new = _both(W, A, primes, bits, gpu_device)
+    ref, new = _both(W, A, primes, bits, gpu_device, digit_planes)
     assert (new == ref).all(), int((new != ref).sum())
     assert (new == pcmm_oracle(W, A, primes)).all()
 

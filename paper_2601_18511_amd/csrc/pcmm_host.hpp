@@ -187,8 +187,9 @@ inline bool gemm_nt_stores(int64_t M, int64_t K, int S, int64_t Ncols, uint64_t 
 //   than the others would run another round of work-groups (slots: work-groups resident on an XCD.  736 x 128 by 128 x 2640, two limbs
 //   12.4 and 10.5 us; 877 x 392 by 392 x 528, int16 W, three 45-bit limbs 14.6 and 10.4);
 // - W counts most (heavy_w, far more rows than columns), of which runs give an XCD an eighth of the rows to read: 14336 x 512 by 512 x 128,
-//   one 36-bit limb 13.5 -> 8.7 us with runs, 65536 x 512 by 512 x 256 62.5 -> 43.9, 14336 x 1250 by 1250 x 256 29.7 -> 25.6.
-inline bool heavy_w(int64_t M, int S, int64_t L, int64_t Ncols) { return M * S > 64 * L * Ncols; }
+//   one 36-bit limb 13.3 -> 8.5 us with runs, 65536 x 512 by 512 x 256 63.0 -> 45.5, 14336 x 1250 by 1250 x 256 30.0 -> 26.3.  By rows of W's
+//   slices per column: 8 to 16 equal (30 shapes), 16 to 64 whole strips 2 to 8 % slower (23), beyond 64 1.24 times as long and more (7).
+inline bool heavy_w(int64_t M, int S, int64_t L, int64_t Ncols) { return M * S > 16 * L * Ncols; }
 inline bool whole_strips(int64_t M, int64_t K, int64_t Ncols, int64_t L, int S) { return 5 * K * (8 - L) > M * L && !heavy_w(M, S, L, Ncols); }
 struct StripRaster {
     int nstrips, mparts;      // strips per limb, parts per strip

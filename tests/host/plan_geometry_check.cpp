@@ -172,7 +172,7 @@ int main()
     CHECK(strip_raster(2, 128, 4, true, 128).whole && strip_raster(2, 42, 4, true, 128).whole);
     CHECK(!strip_raster(2, 42, 12, true, 128).whole && !strip_raster(3, 33, 5, true, 64).whole && !strip_raster(2, 128, 4, false, 128).whole);
     CHECK(whole_strips(128, 128, 8192, 2, 1) && whole_strips(1000, 777, 12300, 3, 1) && !whole_strips(1792, 121, 2864, 4, 2));
-    CHECK(!whole_strips(1678, 28, 2992, 1, 1) && !whole_strips(14336, 512, 128, 1, 1) && !whole_strips(64, 2000, 8192, 8, 1));
+    CHECK(!whole_strips(1678, 28, 2992, 1, 1) && !whole_strips(14336, 512, 128, 1, 1) && !whole_strips(14336, 1250, 256, 1, 1) && !whole_strips(64, 2000, 8192, 8, 1));
 
     // per-limb constants, from the smallest to the largest supported primes
     const uint64_t qs[] = {8388617ull, 16777213ull, 68719403009ull, 68718428161ull, 1125899903827969ull,

@@ -78,7 +78,8 @@ pcmm_status pcmm_plan_create(pcmm_plan **out, int64_t M, int64_t K, int64_t Ncol
  * Device bytes the plan owns: the converted weights (1 or 2 bytes per entry of W, where the paper's
  * converted PCMM tiles take 8, Section 5.3 and Table "model-conversion-memory"), the digit scratch of
  * one run (digits bytes per residue of A; none for contractions that run as one kernel, which cuts the
- * digits itself: K <= 128 and primes below 2^50, and most K up to 1000 to 2000) and the per-limb constants.  0 for NULL.
+ * digits itself: K <= 128 and primes below 2^50, and many K up to 1280 (eight digits) to 2560 (four)) and the per-limb
+ * constants.  0 for NULL.
  */
 size_t pcmm_plan_workspace_bytes(const pcmm_plan *plan);
 
@@ -110,7 +111,8 @@ pcmm_status pcmm_run(const pcmm_plan *plan, const uint64_t *A_dev, uint64_t *C_d
 /*
  * Same operation as pcmm_run (Section 5.1, B = W.A), but brackets each kernel with HIP events on `stream`, synchronises, and
  * reports the kernel durations in milliseconds: ms_out[0] = digit-split kernel (next to nothing for
- * contractions that run as one kernel, which cuts the digits itself), ms_out[1] = MFMA + epilogue kernel (all its launches together when K is cut into ranges).  ms_out is a host array of 2 floats.  For measurement harnesses.
+ * contractions that run as one kernel, which cuts the digits itself), ms_out[1] = MFMA + epilogue kernel (all its
+ * launches together when K is cut into ranges).  ms_out is a host array of 2 floats.  For measurement harnesses.
  */
 pcmm_status pcmm_run_profiled(const pcmm_plan *plan, const uint64_t *A_dev, uint64_t *C_dev,
                               void *stream, float *ms_out);

@@ -141,10 +141,12 @@ constexpr bool odd_ksteps(int S, int MT) { return S * MT < 8; }
 // limbs: cached 1.91 ms, non-temporal 2.62).  Rows that start on half lines: cached stores are better while the memory-side
 // cache still joins the halves, non-temporal ones beyond (cached -> non-temporal: 300 x 64 by 64 x 42936, two limbs, 197 MiB
 // 61 -> 69 us; 768 x 128 by 128 x 14632, five limbs, 429 MiB 187 -> 115; 3000 x 80 by 80 x 42936, two limbs, 1.9 GiB 670 ->
-// 534).  Where that is depends on the raster: strips of two parts cross over at about 224 MiB (194 MiB 95 -> 79, 203 MiB
+// 534).  Where that is depends on the parts: strips of two cross over at about 224 MiB (194 MiB 95 -> 79, 203 MiB
 // 113 -> 122, 283 MiB 114 -> 71), others above 768 strips at about 400 (294 MiB 79 -> 79, 382 MiB 101 -> 114, 438 MiB
 // 211 -> 152), fewer strips at about 640 (327 MiB 82 -> 89, 569 MiB 153 -> 161, 695 MiB 205 -> 183).  Over 230 shapes of 192 MiB to
-// 2 GiB: 9 % faster than cached stores throughout, 3 % than non-temporal ones, 1 % behind the better of the two each time.
+// 2 GiB: 9 % faster than cached stores throughout, 3 % than non-temporal ones, 1 % behind the better of the two each time.  (Measured
+// before strip_raster; with it, over 96 shapes of 150 MiB to 1.2 GiB, 2 % behind, at most 13 % but for one shape, 768 x 128 by 128 x
+// 13656, five limbs, 400 MiB, 166 us cached and 108 non-temporal, and nowhere more than 6 % slower than before it.)
 inline bool shortk_nt_stores(int64_t Ncols, uint64_t c_address, int64_t c_bytes, int64_t strips, int64_t parts)
 {
     if (Ncols % 16 == 0) return true;
@@ -155,10 +157,10 @@ inline bool shortk_nt_stores(int64_t Ncols, uint64_t c_address, int64_t c_bytes,
 
 // What of the digit split goes past the caches: nothing, the digits, or the residues too.  Both where they exceed the 256 MiB
 // last-level cache by enough that nothing of them is found there again (split alone, cached -> non-temporal: 4096 x 4096 by
-// 4096 x 32768, four 36-bit limbs 1.25 -> 1.16 ms; 14336 values of k, three limbs 3.28 -> 3.06; whole pcmm_run, residues of 625 MiB
-// 305 -> 277 us, 512 MiB 1140 -> 1115; 281 MiB 185 -> 190, 188 MiB 153 -> 162, 78 MiB 46 -> 64, hence the line).  Rows of residues that
-// do not start on lines: the digits only, since neighbouring work-groups share lines of residues (12300 columns, 3000 values
-// of k, two limbs 0.201 -> 0.180 ms, with the residues 0.190).
+// 4096 x 32768, four 36-bit limbs 1.25 -> 1.16 ms; 14336 values of k, three limbs 3.28 -> 3.06).  Whole pcmm_run over 96 shapes of 199 to
+// 640 MiB of residues, against cached: from 429 MiB on 0.90 to 1.01 with aligned rows (both) and 0.91 to 1.00 with others (digits only,
+// since neighbouring work-groups share lines of residues; both 0.96 to 1.00); at 299 to 384 MiB 0.93 to 0.99 and 0.93 to 1.00; at
+// 199 MiB 0.98 to 1.06 and 0.99 to 1.07; 78 MiB 46 -> 64 us.  The line is on the safe side of where the two are equal.
 enum SplitNt : int { kNtNone = 0, kNtStores = 1, kNtBoth = 2 };
 inline SplitNt split_nt(int64_t L, int64_t K, int64_t Ncols, uint64_t a_address)
 {
@@ -166,10 +168,13 @@ inline SplitNt split_nt(int64_t L, int64_t K, int64_t Ncols, uint64_t a_address)
     return ((uint64_t)Ncols * 8 | a_address) % 128 == 0 ? kNtBoth : kNtStores;
 }
 
-// Whether the GEMM kernel stores C non-temporally: rows on half lines, and a W of more than 48 MiB, which every group of n-tiles
-// reads again and cached stores push out of the last-level cache (GEMM alone, cached -> non-temporal, 36-bit limbs: 14336 x 4096 by
+// Whether the GEMM kernel stores C non-temporally: rows on half lines, and a W of more than 48 MiB (both slices of int16 W), which every group
+// of n-tiles reads again and cached stores push out of the last-level cache (GEMM alone, cached -> non-temporal, 36-bit limbs: 14336 x 4096 by
 // 4096 x 16384, two limbs 6.60 -> 6.37 ms; 12296 columns 5.13 -> 4.82; 28672 x 2500 by 2500 x 8192 4.65 -> 4.21; W of 39 MiB,
-// 10000 x 4096 4.47 -> 4.51, of 16 MiB, 4096 x 4096 7.63 -> 7.73; odd rows 1000 x 3000 by 3000 x 12301 320 -> 345 us).
+// 10000 x 4096 4.47 -> 4.51, of 16 MiB, 4096 x 4096 7.63 -> 7.73; odd rows 1000 x 3000 by 3000 x 12301 320 -> 345 us; at 56 MiB
+// 10874 x 2700 by 2700 x 4104, int16 W, seven digits 1176 -> 1175 us, 7168 x 4096 by 4096 x 4096, int16 W, integer epilogue
+// 1342 -> 1324, 14336 x 4096 by 4096 x 4096, int8 W, integer epilogue 1645 -> 1648, a limb pair 7168 x 8192 by 8192 x 2048 836 -> 820).
+// With 8192 columns or fewer they are 1 to 4 % faster from 16 MiB of W on too; the line is where they also are with 32768.
 inline bool gemm_nt_stores(int64_t M, int64_t K, int S, int64_t Ncols, uint64_t c_address)
 {
     return ((uint64_t)Ncols * 8 | c_address) % 64 == 0 && M * K * S > (int64_t)48 << 20;
@@ -242,9 +247,9 @@ constexpr int64_t resident_rows(int64_t K, int64_t kb) { return K <= kb * 64 ? 0
 constexpr int64_t kWpSlack = 3 * kFragBytes;
 
 // Whether C is stored non-temporally.  Rows on half lines of 128 bytes: always (1000 x 777 by 777 x 12288, three 45-bit limbs
-// 207 -> 179 us; 4096 x 500 by 500 x 8192, four 36-bit limbs 412 -> 317).  At other places lines are shared with the neighbouring
+// 234 -> 202 us; 4096 x 500 by 500 x 8192, four 36-bit limbs 421 -> 302).  At other places lines are shared with the neighbouring
 // strip and cached stores join them in L2 (over 860 shapes non-temporal ones 15 to 30 % slower), except on quarter lines from 60
-// products a 16 x 16 block on, where the strips drift apart before they could be joined (1000 x 777 by 777 x 12300 236 -> 217;
+// products a 16 x 16 block on, where the strips drift apart before they could be joined (1000 x 777 by 777 x 12300 242 -> 215;
 // over 190 shapes 0 to 6 % faster).
 inline bool resident_nt_stores(int64_t K, int64_t Ncols, uint64_t c_address, int D, int S)
 {
@@ -254,12 +259,13 @@ inline bool resident_nt_stores(int64_t K, int64_t Ncols, uint64_t c_address, int
 
 // The tile for C = W A of L limbs, or NT = 0 where none fits.  The candidates are the strip widths, work-group sizes and numbers of row
 // parts that fit, up to eight parts, more where eight would leave compute units idle (eight -> more, one 36-bit limb: 65536 x 256 by
-// 256 x 16 42 -> 6.6 us, digit split and GEMM kernel 11.6; 14336 x 1000 by 1000 x 16 29 -> 11.3, 15.3).  The estimate, per work-group, is a
+// 256 x 16 42 -> 6.3 us, digit split and GEMM kernel 11.2; 14336 x 1000 by 1000 x 16 29 -> 11.5, 15.1).  The estimate, per work-group, is a
 // start, the digits that each wave cuts, and the rounds of row groups each wave runs (MFMAs of two waves sharing a SIMD, and the
 // epilogue), times the rounds of work-groups, a last partial round counting 0.4 of a full one; strips of 16 columns count
 // 15 % more, since each output row is stored in pieces half as long.  The constants are a fit to 2600 shapes (129 to 2048 values
-// of k, all digit counts); the tile it picks is 1 % behind the fastest candidate on average.  (Limb pairs, nine digits for two limbs, were candidates too and gained
-// nothing here: a tenth of the MFMAs less, but two reductions of nine accumulators for every output pair.)
+// of k, all digit counts) that ranks these candidates; the tile it picks is 1 % behind the fastest of them on average.  (Limb pairs,
+// nine digits for two limbs, were candidates too and gained nothing here: a tenth of the MFMAs less, but two reductions of nine
+// accumulators for every output pair.)
 inline ResidentTile resident_tile(int64_t M, int64_t K, int64_t Ncols, int64_t L, int D, int S)
 {
     ResidentTile best = {0, 0, 0, 0};
@@ -322,6 +328,7 @@ struct Geometry {
 // one wave a SIMD contracts, 64 x 832 by 832 x 16384, four 58-bit limbs of int16 W 5 to 16 % slower).
 constexpr double kResidentMargin = 0.92;
 inline double rounds_of(double full, double whole, double part) { return part * whole + (1.0 - part) * full; }
+// two kinds of work of which the shorter is hidden but for a part
 inline double beside(double a, double b, double exposed) { return a > b ? a + exposed * b : b + exposed * a; }
 inline double ceil_of(double x) { return (double)(int64_t)x < x ? (double)(int64_t)x + 1.0 : (double)(int64_t)x; }
 inline double resident_us(const ResidentTile &t, int64_t M, int64_t K, int64_t Ncols, int64_t L, int D, int S)
@@ -344,7 +351,8 @@ inline double gemm_us(const Geometry &g, int64_t M, int64_t K, int64_t Ncols, in
     // work-groups a few more than whole rounds cost little: slots become free at different times
     auto products = [&](int64_t limbs, int64_t ntiles, int per_block) {       // per_block: int8 products of a row block and n-tile
         const double full = (double)(limbs * g.mtiles * ntiles) / 512;
-        return rounds_of(full, ceil_of(full), full > 1.0 && ceil_of(full) - full > 0.9 ? 0.1 : 0.48) * (7700.0 + g.ksteps * (780.0 + 22.4 * g.MT * per_block)) * (g.WM == 2 ? 0.86 : 1.0) / 2000.0;
+        const double rounds = rounds_of(full, ceil_of(full), full > 1.0 && ceil_of(full) - full > 0.9 ? 0.1 : 0.48);
+        return rounds * (7700.0 + g.ksteps * (780.0 + 22.4 * g.MT * per_block)) * (g.WM == 2 ? 0.86 : 1.0) / 2000.0;
     };
     const double compute = products(g.pairs, g.pair_ntiles, kPairDigits) + products(L - 2 * g.pairs, g.ntiles, g.NT * g.D * g.S);
     const double memory = 8e-6 * L * M * Ncols * (Ncols % 8 == 0 ? 0.21 : 0.29);

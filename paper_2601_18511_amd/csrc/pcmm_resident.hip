@@ -1,5 +1,5 @@
-// PCMM for contractions whose digits fit LDS (more than the 128 values of k of pcmm_shortk.hip, up to 1000 to 2000) on MI355X
-// (gfx950): C_j = W . A_j mod q_j.
+// PCMM for contractions whose digits fit LDS (at most 64 floor(160 / D) values of k, 1280 for eight digits to 2560 for
+// four, where pcmm_shortk.hip does not run and an estimate says that this is the faster way) on MI355X (gfx950): C_j = W . A_j mod q_j.
 //
 // Design.  A work-group owns a strip of 16 NT columns of one limb.  It reads the strip's residues, cuts them into
 // balanced digits and keeps the MFMA operand fragments of ALL k-steps in LDS (NT D KiB a k-step); then its waves walk down the
@@ -15,13 +15,13 @@
 // traffic counts most), one beyond.  Accumulators are ordinary registers written by the MFMA builtin: the epilogue needs no
 // moves, and the first k-step starts them from an inline zero (144 moves a row group otherwise, 4 to 8 % at 13 k-steps).
 //
-// Measured (whole pcmm_run, split and GEMM kernel -> this one): 1000 x 777 by 777 x 12300, three 45-bit limbs 345 -> 217 us;
-// 1000 x 300 by 300 x 8192, four 36-bit limbs 124 -> 75; 4096 x 1024 by 1024 x 16384, four 36-bit limbs 1390 -> 1110;
-// 2048 x 600 by 600 x 16384, int16 W, two 60-bit limbs 735 -> 630.  Of the first one the stores' bytes and residues take
+// Measured (whole pcmm_run in rows of calls, split and GEMM kernel -> this one): 1000 x 777 by 777 x 12300, three 45-bit limbs
+// 328 -> 215 us (on other buffers each call 315 -> 230); 1000 x 300 by 300 x 8192, four 36-bit limbs 116 -> 72; 4096 x 1024 by
+// 1024 x 16384, four 36-bit limbs 1360 -> 1160; 128 x 384 by 384 x 4096, two 36-bit limbs 21 -> 8.  Of the first one the stores' bytes and residues take
 // 97 us at 5.5 TB/s and the MFMAs 94 us; what is left is the cutting at the start of a work-group, during which its waves run no
 // MFMAs, and the last, partial round of work-groups.  What the stores cost beside the MFMAs decides more than either: cached
-// ones of whole lines take 207 us where non-temporal ones take 179 (12288 columns).
-// Built, measured and dropped: W fragments one k-step ahead only (208 -> 198 us for three, 12288 columns); non-temporal loads of
+// ones of whole lines take 234 us where non-temporal ones take 202 (12288 columns).
+// Built, measured and dropped: W fragments one k-step ahead only (three: 5 % faster); non-temporal loads of
 // the residues (4 to 10 % slower: neighbouring strips share lines and parts of a strip re-read them); digits kept in
 // registers across the epilogue (spills, and 10 to 40 % slower).
 #include <hip/hip_runtime.h>

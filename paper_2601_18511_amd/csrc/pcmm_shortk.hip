@@ -261,13 +261,15 @@ hipError_t launch(const Args &a, int D, int S, int epi, hipStream_t st)
     // and cuts the strip's residues again.  Up to 512 strips, where that repeats most, 1536 work-groups, else 3072.
     // Measured with 1536 / 3072 / 6144: 128 strips (4096 x 128 by 128 x 8192) 56 / 69 / 82 us; 256 strips (1024 x 128
     // by 128 x 8192, two limbs) 36 / 41 / 60 us; 626 strips (4096 x 128 by 128 x 20000, two limbs) 273 / 261 / 277 us;
-    // 2048 strips (1000 x 80 by 80 x 65536, two limbs) 249 / 210 / 223 us.
+    // 2048 strips (1000 x 80 by 80 x 65536, two limbs) 249 / 210 / 223 us.  With the present raster, over 160 shapes, against these
+    // targets: 768 work-groups 0.99 to 1.05 of the time by the number of strips, 1536 0.99 to 1.04, 3072 0.99 to 1.02, 6144 1.01 to 1.06.
     const int64_t strips = (int64_t)a.L * nstrips;
     const int64_t target = strips <= 512 ? 1536 : 3072;
     const int64_t mparts = std::min<int64_t>(stages, std::max<int64_t>(1, (target + strips - 1) / strips));
     ka.stages_per_part = (int)((stages + mparts - 1) / mparts);
+    const int64_t slots = D == 7 && S == 2 ? 96 : 128;            // of an XCD: three or four waves on a SIMD
     ka.raster = pcmm_host::strip_raster(a.L, nstrips, (stages + ka.stages_per_part - 1) / ka.stages_per_part,
-                                          pcmm_host::whole_strips(a.M, a.K, a.Ncols, a.L, S), D == 7 && S == 2 ? 96 : 128);   // three or four waves on a SIMD
+                                        pcmm_host::whole_strips(a.M, a.K, a.Ncols, a.L, S), slots);
     const int64_t grid = ka.raster.grid;
     if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
 #define PCMM_SHORTK_CASE(DD, SS) \

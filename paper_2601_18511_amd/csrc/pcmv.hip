@@ -379,7 +379,8 @@ __global__ __launch_bounds__(N / 16) void ntt_blocked_kernel(const void *__restr
     using G = Blocked<N>;
     __shared__ double lds[G::kLds];
     const int64_t p = blockIdx.x;
-    if (queue && p == 0 && threadIdx.x < Blocked<N>::kQueues) queue[threadIdx.x * kQueueStride] = queue_start;   // the work queues of the kernel that follows
+    if (queue && p == 0 && threadIdx.x < G::kQueues)                     // the work queues of the kernel that follows
+        queue[threadIdx.x * kQueueStride] = queue_start;
     const int limb = (int)(p / polys_per_limb);
     const int64_t within = p % polys_per_limb;
     const double q = lc[limb].q, invq = lc[limb].invq;

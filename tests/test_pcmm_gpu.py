@@ -199,6 +199,8 @@ def test_short_contraction_with_rows_on_half_lines(gpu_device, offset):
     ],
 )
 def test_odd_counts_of_ksteps_and_waves_of_padding(gpu_device, M, K, Ncols, bits, L, wbits):
+    """The tiles named here are those of the GEMM kernel.  Most of these contractions fit LDS and run as one kernel where that is the faster
+    way; every form of the GEMM kernel has shapes of its own in test_pcmm_gemm.py."""
     from oracle import pcmm_oracle
 
     rng = np.random.default_rng(M + K * 3 + Ncols)
@@ -229,6 +231,7 @@ def test_odd_counts_of_ksteps_and_waves_of_padding(gpu_device, M, K, Ncols, bits
     ],
 )
 def test_odd_counts_of_ksteps_in_two_wave_work_groups(gpu_device, M, K, Ncols, bits, L, wbits):
+    """As above: the work-groups named here are those of the GEMM kernel, whose forms test_pcmm_gemm.py reaches one by one."""
     from oracle import pcmm_oracle
 
     rng = np.random.default_rng(M * 5 + K + Ncols)
